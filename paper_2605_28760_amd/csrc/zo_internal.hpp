@@ -154,6 +154,9 @@ struct ProbeGemmArgs {
   int64_t uimg_bytes, pimg_bytes, xs_bytes;
 };
 hipError_t launch_probe_gemm_bf16(const ProbeGemmArgs& a, hipStream_t st);
+// ---- zo_gemm_small.hip: the same products on smaller tiles, for calls with few rows --------------
+int small_gemm_tile(int T, int m);   // which of its tiles suits the call; -1: the 256x256 kernel
+hipError_t launch_probe_gemm_small(const ProbeGemmArgs& a, int tile, hipStream_t st);
 
 struct HeadScoreArgs {
   const uint16_t* H; int64_t ldh;

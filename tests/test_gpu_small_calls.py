@@ -1,0 +1,61 @@
+"""Calls with few rows, which run on smaller tiles and their own side-down pass: the kernels a call takes must not
+show in its results."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_28760_amd import workloads as wl
+from paper_2605_28760_amd.runner import DeviceWorkload
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _layer(seed, lens, seq_cand, m, n, r, R, act, bias):
+    """One bf16 probe linear over sequences of the given lengths; candidates 0..5 = (+, -) of three directions,
+    6 = centre."""
+    rng = np.random.default_rng(seed)
+    cu = np.zeros(len(lens) + 1, np.int32)
+    cu[1:] = np.cumsum(lens)
+    X = wl.as_bf16_values(rng.standard_normal((int(cu[-1]), n)).astype(np.float32))
+    W = wl.as_bf16_values((rng.standard_normal((m, n)) / np.sqrt(n)).astype(np.float32))
+    P = (rng.standard_normal((m, R)) * 1e-2).astype(np.float32) if R else None
+    Vb = (rng.standard_normal((n, R)) * 1e-2).astype(np.float32) if R else None
+    b = (rng.standard_normal(m) * 0.3).astype(np.float32) if bias else None
+    layer = wl.Layer("layer", m, n, 6, W, act, P, Vb, R, X, b)
+    return wl.Workload("small-calls", 9, "bf16", r, 0.25, cu, np.array(seq_cand, np.int32),
+                       np.array([0, 0, 1, 1, 2, 2, -1], np.int32), np.array([1, -1, 1, -1, 1, -1, 0], np.float32),
+                       np.arange(3, dtype=np.uint64) + np.uint64(77 + seed), [layer], False)
+
+
+# (weight rows, row count of the small call): each pair takes another tile, from 32x32 to 128x128, at the edges of
+# the tile and of the weight rows; the full batch takes the 256x256 kernel
+@pytest.mark.parametrize("m,rows,full", [(520, 1, 16500), (520, 33, 16500), (512, 500, 16500), (504, 1000, 16500),
+                                         (16384, 20, 700), (520, 1999, 16500), (512, 4000, 16500), (32768, 31, 400),
+                                         (512, 8001, 16500)])
+@pytest.mark.parametrize("n,r,R,act,bias", [(64, 16, 0, 0, False), (320, 33, 72, 1, True), (448, 4, 200, 2, False)])
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+def test_small_call_has_the_bits_of_a_large_one(m, rows, full, n, r, R, act, bias, out):
+    if act == 2 and m % 16:
+        m = (m + 15) // 16 * 16
+    rng = np.random.default_rng(m + rows)
+    # sequences of the small call first (ragged, all kinds, one empty), then filler of all kinds
+    lens, left = [], rows
+    while left > 0:
+        lens.append(min(left, int(rng.integers(1, max(2, rows // 3 + 2)))))
+        left -= lens[-1]
+    lens.insert(len(lens) // 2, 0)
+    keep = len(lens)
+    left = full - rows
+    while left > 0:
+        lens.append(min(left, 300))
+        left -= lens[-1]
+    w = _layer(rows, lens, [i % 8 - 1 for i in range(len(lens))], m, n, r, R, act, bias)
+    big = DeviceWorkload(w, DEV, out_dtype=out)
+    order = np.arange(keep)[::-1].copy()   # the small call packs them the other way round
+    sub = wl.subset_sequences(w, order)
+    small = DeviceWorkload(sub, DEV, out_dtype=out)
+    a = big.probe_linear(0)[torch.from_numpy(np.asarray(sub.meta["rows"])).to(DEV)]
+    b = small.probe_linear(0)
+    torch.cuda.synchronize()
+    assert sub.T == rows and torch.equal(a, b)
