@@ -332,7 +332,6 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
   tabs.n_tn = plan.n_tn; tabs.slot_cap = plan.slot_cap; tabs.kt_cap = plan.kt_cap; tabs.SPD = plan.SPD; tabs.RpT = plan.RpT;
   // a batch without candidates (or probes and bank both absent) is a plain GEMM
   const bool has_side = batch->n_cands > 0;
-  if (has_side && in_dtype != ZO_BF16) ZO_HIP(zo::launch_seq_tables(bd, eps, tabs, st), "batch tables");
 
   if (in_dtype == ZO_BF16) {
     uint16_t* Uimg = (uint16_t*)(ws + plan.Uimg);
@@ -380,7 +379,7 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
     a.Uf = (float*)(ws + plan.Uf); a.Vf = (float*)(ws + plan.Vf);
     a.P = bank ? bank->P : nullptr; a.Vb = bank ? bank->Vb : nullptr;
     a.Tside = (float*)(ws + plan.Tside);
-    if (has_side) ZO_HIP(zo::launch_factors_f32(bd, tensor_id, m, n, r, (float*)(ws + plan.Uf), (float*)(ws + plan.Vf), st), "fp32 factors");
+    a.batch = bd; a.eps = eps; a.tensor_id = tensor_id; a.tabs = tabs;
     ZO_HIP(zo::launch_probe_f32(a, st), "fp32 probe linear");
   }
   return ZO_OK;

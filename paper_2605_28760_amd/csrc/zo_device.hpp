@@ -56,15 +56,6 @@ __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float& z0, 
   z1 = rho * __builtin_amdgcn_sinf(ub);
 }
 
-// Standard normal for flat index e of the stream (seed, tensor_id).
-__device__ __forceinline__ float factor_normal(uint64_t seed, uint32_t tensor_id, uint64_t e) {
-  const uint4 w = factor_block(seed, tensor_id, e >> 2);
-  const bool second = (e & 2) != 0;
-  float z0, z1;
-  box_muller(second ? w.z : w.x, second ? w.w : w.y, z0, z1);
-  return (e & 1) ? z1 : z0;
-}
-
 // ---- bfloat16 ------------------------------------------------------------------
 __device__ __forceinline__ bf16_t f32_to_bf16(float x) {
   uint32_t u = __float_as_uint(x);

@@ -23,7 +23,7 @@ constexpr int side_lds_bytes(int nbb, int rb, int w) { return w * (2 * rb * 2048
 // (64-row items next to eight bank blocks).
 constexpr int side_waves_of(int nbb, int rb) { return side_lds_bytes(nbb, rb, kSideWaves) <= 160 * 1024 ? kSideWaves : kSideWaves - 1; }
 constexpr int kSideMaxBlocks = 9; // 16-column blocks a side-down wave accumulates at once
-constexpr int kSimtTile = 64;     // tile edge of the fp32 vector-ALU kernels
+constexpr int kSimtTile = 64;     // vocabulary rows per tile of the fp32 head kernel
 
 struct BatchDev {
   int T, S, C, K;
@@ -98,13 +98,13 @@ hipError_t launch_philox_words(uint64_t seed, uint32_t tensor_id, uint64_t first
 hipError_t launch_factor_fill(uint64_t seed, uint32_t tensor_id, int64_t rows, int r, int bf16,
                               void* out, hipStream_t st);
 hipError_t launch_tok_index(const BatchDev& b, int32_t* tok_seq, int32_t* tok_cand, hipStream_t st);
-hipError_t launch_seq_tables(const BatchDev& b, float eps, const SeqTables& t, hipStream_t st);
+// everything an fp32 probe linear prepares, in one launch: sequence tables (no side-down items are used), token ->
+// sequence map, and the factors Uf [K][m][r], Vf [K][n][r]
+hipError_t launch_probe_prep_f32(const BatchDev& b, float eps, const SeqTables& t, uint32_t tensor_id, int m, int n, int r,
+                                 float* Uf, float* Vf, hipStream_t st);
 // bf16 operand images.  For the GEMM's side K tiles: Uimg [K * SPD][m_img][32] (32-column blocks of U,
 // 64-byte rows), Pimg [RpT][m_img][64] (64-column blocks of P, 128-byte rows); rows >= m and columns
 // beyond the rank are zero.  For the side-down pass: Vt [K][RP][n] (V transposed), Vbt [Rp][n].
-// fp32 factors: Uf [K][m][r], Vf [K][n][r]
-hipError_t launch_factors_f32(const BatchDev& b, uint32_t tensor_id, int m, int n, int r,
-                              float* Uf, float* Vf, hipStream_t st);
 
 // ---- zo_side.hip --------------------------------------------------------------
 struct SideDownArgs {
@@ -173,7 +173,7 @@ struct HeadScoreArgs {
 int head_vocab_tiles_bf16(int vocab);
 hipError_t launch_head_score_bf16(const HeadScoreArgs& a, hipStream_t st);
 
-// ---- zo_simt.hip (fp32 on the vector ALU) ------------------------------------------
+// ---- zo_f32.hip (fp32 operands) ---------------------------------------------------------
 struct ProbeF32Args {
   const float* X; int64_t ldx;
   const float* W; int64_t ldw;
@@ -183,7 +183,8 @@ struct ProbeF32Args {
   float* Y; int64_t ldy;
   int has_side;
   const int32_t* tok_seq; const int32_t* seq_kind; const float* seq_scale;
-  const float* Uf; const float* Vf;  // [K][m][r], [K][n][r]
+  float* Uf; float* Vf;              // [K][m][r], [K][n][r]: written by the preparation, then read
+  BatchDev batch; float eps; uint32_t tensor_id; SeqTables tabs;   // what the preparation needs
   const float* P; const float* Vb;   // bank, ld R_cap
   float* Tside;                      // [T][r+R]
 };

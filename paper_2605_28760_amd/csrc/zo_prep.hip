@@ -191,15 +191,6 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
   if (tid == 0) t.n_items[1] = min(kt_carry, t.kt_cap);
 }
 
-__global__ __launch_bounds__(1024) void k_seq_tables(BatchDev b, float eps, SeqTables t) { seq_tables_block(b, eps, t); }
-
-hipError_t launch_seq_tables(const BatchDev& b, float eps, const SeqTables& t, hipStream_t st) {
-  hipLaunchKernelGGL(k_seq_tables, dim3(1), dim3(1024), 0, st, b, eps, t);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_tok_index(b, t.tok_seq, nullptr, st);
-}
-
 // ---- operand images ----------------------------------------------------------------------
 // Four consecutive columns c0 .. c0+3 of row i of a [rows x r] factor: entries c >= r are zero.
 // Entry (i, c) is element e = i*r + c of the stream, i.e. lane e%4 of block e/4; the four entries
@@ -284,21 +275,43 @@ __device__ __forceinline__ void image_P_at(int64_t idx, const float* P, int R_ca
   Pimg[((int64_t)(j >> 6) * m_img + i) * 64 + (j & 63)] = f32_to_bf16(i < m && j < R_used ? P[(int64_t)i * R_cap + j] : 0.0f);
 }
 
-__global__ void k_factors_f32(BatchDev b, uint32_t tid, int rows, int r, float* out) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t per_dir = (int64_t)rows * r;
-  if (idx >= per_dir * b.K) return;
-  const int k = (int)(idx / per_dir);
-  const uint64_t seed = ((tid & 1u) && b.seed_v) ? b.seed_v[k] : b.seed[k];   // odd stream id: V
-  out[idx] = factor_normal(seed, tid, (uint64_t)(idx - (int64_t)k * per_dir));
+// ---- everything an fp32 probe linear prepares, in one launch ----------------------------------
+// Four consecutive entries 4q .. 4q+3 of a factor stream (one Philox block) of direction k into out[k][rows*r].
+// idx runs over [K][ceil(rows*r/4)].
+__device__ __forceinline__ void factor_f32_at(const BatchDev& b, const uint64_t* seeds, int64_t idx, uint32_t tid, int rows,
+                                              int r, float* out) {
+  const int64_t per_dir = (int64_t)rows * r, quads = (per_dir + 3) / 4;
+  if (idx >= quads * b.K) return;
+  const int k = (int)(idx / quads);
+  const int64_t q = idx - (int64_t)k * quads;
+  const uint4 w = factor_block(seeds[k], tid, (uint64_t)q);
+  float z[4];
+  box_muller(w.x, w.y, z[0], z[1]);
+  box_muller(w.z, w.w, z[2], z[3]);
+#pragma unroll
+  for (int l = 0; l < 4; ++l)
+    if (q * 4 + l < per_dir) out[(int64_t)k * per_dir + q * 4 + l] = z[l];
 }
 
-hipError_t launch_factors_f32(const BatchDev& b, uint32_t tensor_id, int m, int n, int r,
-                              float* Uf, float* Vf, hipStream_t st) {
-  if (b.K == 0) return hipSuccess;
-  const int64_t nu = (int64_t)b.K * m * r, nv = (int64_t)b.K * n * r;
-  hipLaunchKernelGGL(k_factors_f32, dim3((unsigned)((nu + 255) / 256)), dim3(256), 0, st, b, tensor_id & ~1u, m, r, Uf);
-  hipLaunchKernelGGL(k_factors_f32, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, st, b, tensor_id | 1u, n, r, Vf);
+// Block roles, in order: [sequence tables: 1] [token -> sequence map] [U] [V].
+__global__ __launch_bounds__(1024) void k_probe_prep_f32(BatchDev b, float eps, SeqTables t, uint32_t tensor_id, int m, int n,
+                                                         int r, float* Uf, float* Vf, int nb_tok, int nb_U) {
+  int blk = blockIdx.x;
+  if (blk == 0) { seq_tables_block(b, eps, t); return; }
+  blk -= 1;
+  if (blk < nb_tok) { tok_index_at(b, blk * 1024 + threadIdx.x, t.tok_seq, nullptr); return; }
+  blk -= nb_tok;
+  if (blk < nb_U) { factor_f32_at(b, b.seed, (int64_t)blk * 1024 + threadIdx.x, tensor_id & ~1u, m, r, Uf); return; }
+  blk -= nb_U;
+  factor_f32_at(b, b.seed_v ? b.seed_v : b.seed, (int64_t)blk * 1024 + threadIdx.x, tensor_id | 1u, n, r, Vf);
+}
+
+hipError_t launch_probe_prep_f32(const BatchDev& b, float eps, const SeqTables& t, uint32_t tensor_id, int m, int n, int r,
+                                 float* Uf, float* Vf, hipStream_t st) {
+  auto blocks = [&](int rows) { return (int)(((((int64_t)rows * r + 3) / 4) * b.K + 1023) / 1024); };
+  const int nb_tok = (b.T + 1023) / 1024, nb_U = blocks(m), nb_V = blocks(n);
+  hipLaunchKernelGGL(k_probe_prep_f32, dim3(1 + nb_tok + nb_U + nb_V), dim3(1024), 0, st, b, eps, t, tensor_id, m, n, r, Uf,
+                     Vf, nb_tok, nb_U);
   return hipGetLastError();
 }
 

@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import zo_oracle as zo
 from paper_2605_28760_amd import workloads as wl
 from paper_2605_28760_amd.runner import DeviceWorkload
+from zo_testlib import assert_close, oracle_layer, to_np
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -59,3 +61,33 @@ def test_small_call_has_the_bits_of_a_large_one(m, rows, full, n, r, R, act, bia
     b = small.probe_linear(0)
     torch.cuda.synchronize()
     assert sub.T == rows and torch.equal(a, b)
+
+
+# widths with and without whole groups of four columns, K slabs that end early, tiles of 32 and of 64 (the second row
+# count of a pair takes the larger tile), a vocabulary that ends inside a tile and inside a wave's rows
+@pytest.mark.parametrize("n,m,vocab,r,R,act", [(256, 256, 512, 4, 0, 0), (130, 200, 77, 3, 9, 1), (63, 96, 1000, 10, 0, 2),
+                                               (388, 260, 65, 1, 33, 0)])
+def test_fp32_call_on_either_tile_size(n, m, vocab, r, R, act):
+    """fp32 results against the 64-bit oracle at rel 1e-5, and the rows of a call on the larger tiles bit-equal to a
+    small call's."""
+    lens = [1, 33, 0, 70, 16] + [250] * 28
+    w = _layer(n + m, lens, [i % 8 - 1 for i in range(len(lens))], m, n, r, R, act, bool(R))
+    rng = np.random.default_rng(vocab)
+    m_out = m // 2 if act == 2 else m
+    w.dtype, w.eps, w.chain = "f32", 1e-2, True
+    w.X, w.layers[0].X = w.layers[0].X, None
+    w.head = (rng.standard_normal((vocab, m_out)) / np.sqrt(m_out)).astype(np.float32)
+    w.targets = rng.integers(-1, vocab, size=w.T).astype(np.int32)
+    big = DeviceWorkload(w, DEV)
+    big.step(update=False)
+    want = oracle_layer(w, 0, w.X)
+    assert_close(to_np(big.Y[0]), want, 1e-5, "Y")
+    tok = zo.token_nll(to_np(big.Y[0]), w.head, w.targets)
+    assert_close(to_np(big.tok_nll), tok, 1e-5, "tok_nll")
+    sub = wl.subset_sequences(w, np.arange(5))
+    small = DeviceWorkload(sub, DEV)
+    small.step(update=False)
+    torch.cuda.synchronize()
+    for a, b in ((big.Y[0], small.Y[0]), (big.tok_nll, small.tok_nll)):
+        assert torch.equal(a[:sub.T], b)
+    assert torch.equal(big.seq_nll[:5], small.seq_nll)
