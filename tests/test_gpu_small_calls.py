@@ -4,9 +4,11 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import zo_block as ob
 from oracle import zo_oracle as zo
+from paper_2605_28760_amd import binding as zb
 from paper_2605_28760_amd import workloads as wl
-from paper_2605_28760_amd.runner import DeviceWorkload
+from paper_2605_28760_amd.runner import DeviceBatch, DeviceWorkload
 from zo_testlib import assert_close, oracle_layer, to_np
 
 pytestmark = pytest.mark.gpu
@@ -91,3 +93,25 @@ def test_fp32_call_on_either_tile_size(n, m, vocab, r, R, act):
     for a, b in ((big.Y[0], small.Y[0]), (big.tok_nll, small.tok_nll)):
         assert torch.equal(a[:sub.T], b)
     assert torch.equal(big.seq_nll[:5], small.seq_nll)
+
+
+@pytest.mark.parametrize("lens", [[1, 31, 32, 33, 64, 0, 96], [127, 128, 129], [160, 161, 255, 257, 1]])
+@pytest.mark.parametrize("scale,grow", [(128 ** -0.5, 0.0), (-(128 ** -0.5), 0.0), (0.0, 0.0), (0.1, 0.02), (0.1, -0.02)])
+def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
+    """Lengths around the 32 keys of a step, the 32 rows of a wave and the 128 of a workgroup; negative and zero
+    scales; scores that grow along the sequence, so that the running maximum is raised again and again, or shrink, so
+    that it never is.  Weights and outputs are bf16: 2e-2 as for every bf16 output here."""
+    H, Hkv, dh = 4, 2, 128
+    rng = np.random.default_rng(sum(lens))
+    T = sum(lens)
+    cu = np.zeros(len(lens) + 1, np.int32)
+    cu[1:] = np.cumsum(lens)
+    pos = np.concatenate([np.arange(n) for n in lens])[:, None]
+    q = wl.as_bf16_values((rng.standard_normal((T, H * dh)) + (grow != 0)).astype(np.float32))
+    k = wl.as_bf16_values((rng.standard_normal((T, Hkv * dh)) + grow * pos).astype(np.float32))
+    v = wl.as_bf16_values(rng.standard_normal((T, Hkv * dh)).astype(np.float32))
+    b = DeviceBatch(cu, np.full(len(lens), -1), np.zeros(0), np.zeros(0), np.zeros(0, np.uint64), DEV)
+    dev = [torch.from_numpy(x).to(DEV, torch.bfloat16) for x in (q, k, v)]
+    out = torch.empty((T, H * dh), device=DEV, dtype=torch.bfloat16)
+    zb.zo_attention(b.struct, dev[0], H * dh, dev[1], Hkv * dh, dev[2], Hkv * dh, H, Hkv, dh, scale, zb.ZO_BF16, out, H * dh)
+    assert_close(to_np(out), ob.attention(q, k, v, cu, H, Hkv, dh, scale, "bf16"), 2e-2, "attention")
