@@ -81,29 +81,42 @@ hipError_t launch_tok_index(const BatchDev& b, int32_t* tok_seq, int32_t* tok_ca
 }
 
 // Exclusive prefix sum of one value per thread over a block of 1024 threads; *total = the block's sum.
-__device__ __forceinline__ int block_scan_1024(int v, int* s_scan, int* total) {
-  const int tid = threadIdx.x;
-  s_scan[tid] = v;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int u = (tid >= off) ? s_scan[tid - off] : 0;
-    __syncthreads();
-    s_scan[tid] += u;
-    __syncthreads();
+__device__ __forceinline__ int block_scan_1024(int v, int* s_wave, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(incl, off);
+    if (lane >= off) incl += u;
   }
-  const int incl = s_scan[tid];
-  *total = s_scan[1023];
+  __syncthreads();   // the previous scan's totals have been read
+  if (lane == 63) s_wave[wave] = incl;
   __syncthreads();
-  return incl - v;
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int x = s_wave[w];
+    before += w < wave ? x : 0;
+    all += x;
+  }
+  *total = all;
+  return before + incl - v;
 }
 
 // Per-sequence kind / scale, the list of side-down work items (chunks of at
 // most item_rows rows of one sequence) and, for the bf16 GEMM, the side K tiles of
 // every token tile.  One workgroup; sequences and tiles are scanned in blocks of
 // 1024 so the item order follows the row order.
+//
+// This workgroup is the longest chain of a preparation launch, so what it looks up repeatedly (bounds and kinds of
+// the first 1024 sequences) sits in LDS, and the directions a tile has met in one 64-bit mask: 34 sequences on 6 tiles
+// took 12 us with every look-up in global memory and tree scans of 20 barriers, whatever else the launch did.
 __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, const SeqTables& t) {
-  __shared__ int s_scan[1024];
+  constexpr int kCached = 1024;
+  __shared__ int s_wave[16];
+  __shared__ int s_cu[kCached + 1], s_kind[kCached];
   const int tid = threadIdx.x;
+  const bool cached = b.S <= kCached;
   int carry = 0;
   for (int base = 0; base < b.S; base += 1024) {
     const int s = base + tid;
@@ -111,8 +124,9 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
     float scale = 0.0f;
     if (s < b.S) {
       row0 = b.cu[s];
-      len = max(b.cu[s + 1] - row0, 0);
+      const int next = b.cu[s + 1];
       const int c = b.seq_cand[s];
+      len = max(next - row0, 0);
       if (c >= 0 && c < b.C) {
         const int d = b.cand_dir[c];
         const float sg = b.cand_sign[c];
@@ -121,11 +135,16 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
       }
       t.seq_kind[s] = kind;
       t.seq_scale[s] = scale;
+      if (cached) {
+        s_cu[s] = row0;
+        s_cu[s + 1] = next;   // (the neighbour writes the same value)
+        s_kind[s] = kind;
+      }
       // (a foreground sequence has no side term: no items, none of its rows is read by the side-down pass)
       nchunk = kind == kKindForeground ? 0 : (len + t.item_rows - 1) / t.item_rows;
     }
     int total;
-    const int first = carry + block_scan_1024(nchunk, s_scan, &total);
+    const int first = carry + block_scan_1024(nchunk, s_wave, &total);
     for (int j = 0; j < nchunk; ++j) {
       if (first + j < t.max_items) {
         SideItem it;
@@ -146,6 +165,8 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
   // those sequences (the sum over the tiles is at most the tiles plus the sequences).  Kinds written by
   // other threads of this workgroup above are visible after the barriers of the scans.
   __syncthreads();
+  const int32_t* cu = cached ? s_cu : b.cu;
+  const int32_t* kinds = cached ? s_kind : t.seq_kind;
   int slot_carry = 0, kt_carry = 0;
   for (int base = 0; base < t.n_tn; base += 1024) {
     const int tn = base + tid;
@@ -153,23 +174,29 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
     if (tn < t.n_tn) {
       t0 = tn * kTileN;
       t1 = min(b.T, t0 + kTileN);
-      s_first = seq_of_row(b.cu, b.S, t0);
-      s_last = seq_of_row(b.cu, b.S, t1 - 1);
+      s_first = seq_of_row(cu, b.S, t0);
+      s_last = seq_of_row(cu, b.S, t1 - 1);
       bound = min(min(s_last - s_first + 1, b.K), kTileN) * t.SPD;   // a tile meets at most kTileN non-empty sequences
     }
     int total;
-    const int slot0 = slot_carry + block_scan_1024(bound, s_scan, &total);
+    const int slot0 = slot_carry + block_scan_1024(bound, s_wave, &total);
     slot_carry += total;
     int q = 0, n_kt = 0, n_bank = 0;
     if (tn < t.n_tn) {
       bool any = false;
+      uint64_t met = 0;   // directions met so far, when there are at most 64
       for (int s = s_first; s <= s_last; ++s) {
-        if (min(b.cu[s + 1], t1) <= max(b.cu[s], t0)) continue;   // no row of s in this tile
-        const int kind = t.seq_kind[s];
+        if (min(cu[s + 1], t1) <= max(cu[s], t0)) continue;   // no row of s in this tile
+        const int kind = kinds[s];
         if (kind >= kKindCentre) any = true;
         if (kind < 0) continue;
         bool seen = false;
-        for (int j = 0; j < q && !seen; ++j) seen = t.tile_slots[slot0 + j * t.SPD] == kind * t.SPD;
+        if (b.K <= 64) {
+          seen = (met >> kind) & 1;
+          met |= 1ull << kind;
+        } else {
+          for (int j = 0; j < q && !seen; ++j) seen = t.tile_slots[slot0 + j * t.SPD] == kind * t.SPD;
+        }
         if (!seen && slot0 + (q + 1) * t.SPD <= t.slot_cap) {
           for (int blk = 0; blk < t.SPD; ++blk) t.tile_slots[slot0 + q * t.SPD + blk] = kind * t.SPD + blk;
           ++q;
@@ -178,7 +205,7 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
       n_bank = any ? t.RpT : 0;
       n_kt = (q * t.SPD + 1) / 2 + n_bank;
     }
-    const int kt0 = kt_carry + block_scan_1024(n_kt, s_scan, &total);
+    const int kt0 = kt_carry + block_scan_1024(n_kt, s_wave, &total);
     kt_carry += total;
     if (tn < t.n_tn) {
       TileHdr h;
@@ -235,44 +262,67 @@ __device__ __forceinline__ void split3(int64_t idx, int64_t per_a, int inner, in
   }
 }
 
-// idx runs over [K][m_img][RP32/4]: one thread writes four neighbouring entries of a row of U (8 bytes) into
+// idx runs over [K][m_img][SPD * 4]: one thread writes eight neighbouring entries of a row of U (16 bytes) into
 // the image [K * SPD][m_img][32]; rows >= m and columns >= r are zero
 __device__ __forceinline__ void image_U_at(const BatchDev& b, int64_t idx, uint32_t tid_u, int m, int m_img, int r, int SPD,
                                            bf16_t* Uimg) {
-  const int quads = SPD * 8;
-  const int64_t per_dir = (int64_t)m_img * quads;
+  const int groups = SPD * 4;
+  const int64_t per_dir = (int64_t)m_img * groups;
   if (idx >= per_dir * b.K) return;
   int k, i, c0;
-  split3(idx, per_dir, quads, k, i, c0);
-  c0 *= 4;
-  float z[4] = {0.f, 0.f, 0.f, 0.f};
-  if (i < m && c0 < r) factor_quad(b.seed[k], tid_u, i, r, c0, z);
-  *reinterpret_cast<uint2*>(Uimg + (((int64_t)k * SPD + (c0 >> 5)) * m_img + i) * 32 + (c0 & 31)) =
-      make_uint2(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]));
+  split3(idx, per_dir, groups, k, i, c0);
+  c0 *= 8;
+  float z[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  if (i < m && c0 < r) {
+    factor_quad(b.seed[k], tid_u, i, r, c0, z[0]);
+    if (c0 + 4 < r) factor_quad(b.seed[k], tid_u, i, r, c0 + 4, z[1]);
+  }
+  *reinterpret_cast<u32x4*>(Uimg + (((int64_t)k * SPD + (c0 >> 5)) * m_img + i) * 32 + (c0 & 31)) =
+      u32x4{pack_bf16x2(z[0][0], z[0][1]), pack_bf16x2(z[0][2], z[0][3]), pack_bf16x2(z[1][0], z[1][1]), pack_bf16x2(z[1][2], z[1][3])};
 }
 
-// idx runs over [K][RP/4][n]: one thread writes entry i of four neighbouring rows of V^T
+// idx runs over [K][RP/4][n/2]: one thread writes entries i, i+1 of four neighbouring rows of V^T (n is even)
 __device__ __forceinline__ void image_Vt_at(const BatchDev& b, int64_t idx, uint32_t tid_v, int n, int r, int RP, bf16_t* Vt) {
-  const int quads = RP >> 2;
-  const int64_t per_dir = (int64_t)n * quads;
+  const int quads = RP >> 2, half = n >> 1;
+  const int64_t per_dir = (int64_t)half * quads;
   if (idx >= per_dir * b.K) return;
   int k, c0, i;
-  split3(idx, per_dir, n, k, c0, i);
+  split3(idx, per_dir, half, k, c0, i);
   c0 *= 4;
-  float z[4] = {0.f, 0.f, 0.f, 0.f};
-  if (c0 < r) factor_quad(b.seed_v ? b.seed_v[k] : b.seed[k], tid_v, i, r, c0, z);
+  i *= 2;
+  float z[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  if (c0 < r) {
+    const uint64_t seed = b.seed_v ? b.seed_v[k] : b.seed[k];
+    factor_quad(seed, tid_v, i, r, c0, z[0]);
+    factor_quad(seed, tid_v, i + 1, r, c0, z[1]);
+  }
 #pragma unroll
-  for (int l = 0; l < 4; ++l) Vt[((int64_t)k * RP + c0 + l) * n + i] = f32_to_bf16(z[l]);
+  for (int l = 0; l < 4; ++l) *reinterpret_cast<uint32_t*>(Vt + ((int64_t)k * RP + c0 + l) * n + i) = pack_bf16x2(z[0][l], z[1][l]);
 }
 
-// idx runs over [m_img][RpT * 64]: image [RpT][m_img][64] of P; rows >= m and columns >= R_used are zero
+// idx runs over [m_img][RpT * 8]: one thread writes eight neighbouring entries (16 bytes) of the image [RpT][m_img][64]
+// of P; rows >= m and columns >= R_used are zero
 __device__ __forceinline__ void image_P_at(int64_t idx, const float* P, int R_cap, int R_used, int RpT, int m, int m_img,
                                            bf16_t* Pimg) {
-  const int cols = RpT * 64;
-  if (idx >= (int64_t)m_img * cols) return;
+  const int groups = RpT * 8;
+  if (idx >= (int64_t)m_img * groups) return;
   int zero, i, j;
-  split3(idx, (int64_t)m_img * cols, cols, zero, i, j);
-  Pimg[((int64_t)(j >> 6) * m_img + i) * 64 + (j & 63)] = f32_to_bf16(i < m && j < R_used ? P[(int64_t)i * R_cap + j] : 0.0f);
+  split3(idx, (int64_t)m_img * groups, groups, zero, i, j);
+  j *= 8;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (i < m) {
+    const float* src = P + (int64_t)i * R_cap + j;
+    if (j + 8 <= R_used && ((uintptr_t)src & 15u) == 0) {
+      const float4 a = reinterpret_cast<const float4*>(src)[0], c = reinterpret_cast<const float4*>(src)[1];
+      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (j + e < R_used) v[e] = src[e];
+    }
+  }
+  *reinterpret_cast<u32x4*>(Pimg + ((int64_t)(j >> 6) * m_img + i) * 64 + (j & 63)) =
+      u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
 }
 
 // ---- everything an fp32 probe linear prepares, in one launch ----------------------------------
@@ -363,9 +413,9 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   a.m_img = m_img;
   auto blocks = [](int64_t n_elems) { return (int)((n_elems + 1023) / 1024); };
   a.nb_tok = blocks(b.T);
-  a.nb_U = blocks((int64_t)b.K * m_img * (tabs.SPD * 8));
-  a.nb_Vt = blocks((int64_t)b.K * n * (RP / 4));
-  a.nb_P = Rp > 0 ? blocks((int64_t)m_img * tabs.RpT * 64) : 0;
+  a.nb_U = blocks((int64_t)b.K * m_img * (tabs.SPD * 4));
+  a.nb_Vt = blocks((int64_t)b.K * (n / 2) * (RP / 4));
+  a.nb_P = Rp > 0 ? blocks((int64_t)m_img * tabs.RpT * 8) : 0;
   a.vbt_tiles_n = (n + 31) / 32;
   a.nb_Vbt = Rp > 0 ? a.vbt_tiles_n * ((Rp + 31) / 32) : 0;
   const int64_t total = 1 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Vbt;
