@@ -24,6 +24,15 @@ int side_ksplit(int n) {
   return s < 1 ? 1 : s;
 }
 
+// The one-launch pass has a wave per 16 rows, 16 side columns and K range and reads X once per 16 columns; the staged
+// pass reads X once, but has a few workgroups only when the batch is small.  The line lies at 2400 waves.  Whole calls
+// on 512 output features, us, staged -> one launch: 4096 columns and 144 side columns 36 -> 24 at 38 rows, 52 -> 47 at
+// 1058 (2381 waves), 54 -> 59 at 2042 (4595); 5120 and 80: 41 -> 28 at 200, 58 -> 58 at 2042 (2553); 20480 and 80: 87 ->
+// 68 at 200, 136 -> 133 at 1058 (2645); 1024 and 48: 28 -> 22 at 1058, 43 -> 42 at 8364 (3137).
+bool side_small_call(int T, int n, int columns) {
+  return (int64_t)((T + 15) / 16) * (columns / 16) * side_ksplit(n) <= 2400;
+}
+
 // Rows per item (64, 48, 32 or 16; how rows are grouped into items does not enter any row's arithmetic).  The
 // workgroups of a pass (seven or eight items each, times the K ranges) run in rounds of one workgroup per
 // compute unit, and a round that is mostly empty takes as long as a full one.  A workgroup's time per K step
@@ -155,7 +164,9 @@ ProbePlan plan_probe(int T, int S, int K, int m, int n, int r, int R, zo_dtype d
   p.n_items = c.take(16);
   // (the choice of the item size does not enter the layout below: a workspace query, which has no batch, and
   // the call agree on every offset)
-  p.item_rows = dt == ZO_BF16 ? zo::side_item_rows(host_cu, host_seq_cand, S, T, n, R) : zo::kSideRows;
+  if (dt != ZO_BF16) p.item_rows = zo::kSideRows;
+  else if (zo::side_small_call(T, n, round16(r) + round16(R))) p.item_rows = 16;
+  else p.item_rows = zo::side_item_rows(host_cu, host_seq_cand, S, T, n, R);
   p.max_items = (T + p.item_rows - 1) / p.item_rows + S;
   // (sized for the smallest items, so that a workspace sized for a large batch also serves a smaller one)
   p.items = c.take(((size_t)(T + 15) / 16 + S) * sizeof(zo::SideItem));
@@ -330,6 +341,7 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
   tabs.item_rows = plan.item_rows;
   tabs.tile_hdr = nullptr; tabs.tile_slots = nullptr; tabs.kt_tile = nullptr;
   tabs.n_tn = plan.n_tn; tabs.slot_cap = plan.slot_cap; tabs.kt_cap = plan.kt_cap; tabs.SPD = plan.SPD; tabs.RpT = plan.RpT;
+  tabs.Xs = nullptr;
   // a batch without candidates (or probes and bank both absent) is a plain GEMM
   const bool has_side = batch->n_cands > 0;
 
@@ -349,6 +361,7 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
       tabs.tile_hdr = (zo::TileHdr*)(ws + plan.tile_hdr);
       tabs.tile_slots = (int32_t*)(ws + plan.tile_slots);
       tabs.kt_tile = (int32_t*)(ws + plan.kt_tile);
+      if (zo::side_small_call(T, n, plan.RP + plan.Rp)) tabs.Xs = Xs;
       ZO_HIP(zo::launch_probe_prep_bf16(bd, eps, tabs, tensor_id, m, n, r, plan.RP, plan.Rp, R > 0 ? bank->P : nullptr,
                                         R > 0 ? bank->Vb : nullptr, R > 0 ? bank->R_cap : 0, R, plan.m_img, Uimg, Vt, Pimg,
                                         Vbt, st),

@@ -69,6 +69,8 @@ struct SeqTables {
   int32_t n_tn, slot_cap, kt_cap;
   int32_t SPD;         // 32-column blocks per direction
   int32_t RpT;         // bank K tiles of a tile with candidates
+  uint16_t* Xs;        // non-null for the one-launch side-down pass: the preparation clears the token-side images and
+                       // writes Vt and Vbt in the order of the matrix instruction's operands
 };
 
 // number of compute units of the current device (256 on MI355X; cached per device)
@@ -104,7 +106,8 @@ hipError_t launch_probe_prep_f32(const BatchDev& b, float eps, const SeqTables& 
                                  float* Uf, float* Vf, hipStream_t st);
 // bf16 operand images.  For the GEMM's side K tiles: Uimg [K * SPD][m_img][32] (32-column blocks of U,
 // 64-byte rows), Pimg [RpT][m_img][64] (64-column blocks of P, 128-byte rows); rows >= m and columns
-// beyond the rank are zero.  For the side-down pass: Vt [K][RP][n] (V transposed), Vbt [Rp][n].
+// beyond the rank are zero.  For the side-down pass: Vt [K][RP][n] (V transposed), Vbt [Rp][n] (or
+// both in operand order, see SeqTables::Xs).
 
 // ---- zo_side.hip --------------------------------------------------------------
 struct SideDownArgs {
@@ -125,6 +128,8 @@ struct SideDownArgs {
 // K ranges of the side-down pass for an input width n: never a function of the batch, so that the
 // summation order of a row's side term does not depend on what else is in the batch.
 int side_ksplit(int n);
+// Whether a call takes the one-launch side-down pass (columns = RP + Rp).
+bool side_small_call(int T, int n, int columns);
 // Rows per side-down work item (64, 48, 32 or 16) for a batch of T rows, input width n and bank rank R; how rows
 // are grouped into items does not enter any row's arithmetic.
 int side_item_rows(const int32_t* host_cu, const int32_t* host_seq_cand, int S, int T, int n, int R);

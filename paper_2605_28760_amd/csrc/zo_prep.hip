@@ -281,8 +281,17 @@ __device__ __forceinline__ void image_U_at(const BatchDev& b, int64_t idx, uint3
       u32x4{pack_bf16x2(z[0][0], z[0][1]), pack_bf16x2(z[0][2], z[0][3]), pack_bf16x2(z[1][0], z[1][1]), pack_bf16x2(z[1][2], z[1][3])};
 }
 
+// Where entry i of row c of a transposed factor (V^T or Vb^T, rows padded to blocks of 16) lives: row-major, or in
+// the order of the side-down matrix instruction's operands (frag_major): [block of 16 rows][32 columns][lane][8], lane =
+// row % 16 + 16 * (column / 8 % 4).  Entries i .. i+7 of a multiple of 8 are neighbours either way.
+__device__ __forceinline__ int64_t transposed_at(int c, int i, int n, bool frag_major) {
+  return frag_major ? ((int64_t)(c >> 4) * (n >> 5) + (i >> 5)) * 512 + ((c & 15) + ((i >> 3) & 3) * 16) * 8 + (i & 7)
+                    : (int64_t)c * n + i;
+}
+
 // idx runs over [K][RP/4][n/2]: one thread writes entries i, i+1 of four neighbouring rows of V^T (n is even)
-__device__ __forceinline__ void image_Vt_at(const BatchDev& b, int64_t idx, uint32_t tid_v, int n, int r, int RP, bf16_t* Vt) {
+__device__ __forceinline__ void image_Vt_at(const BatchDev& b, int64_t idx, uint32_t tid_v, int n, int r, int RP, bool frag_major,
+                                            bf16_t* Vt) {
   const int quads = RP >> 2, half = n >> 1;
   const int64_t per_dir = (int64_t)half * quads;
   if (idx >= per_dir * b.K) return;
@@ -296,8 +305,21 @@ __device__ __forceinline__ void image_Vt_at(const BatchDev& b, int64_t idx, uint
     factor_quad(seed, tid_v, i, r, c0, z[0]);
     factor_quad(seed, tid_v, i + 1, r, c0, z[1]);
   }
+  bf16_t* dst = Vt + (int64_t)k * RP * n;
 #pragma unroll
-  for (int l = 0; l < 4; ++l) *reinterpret_cast<uint32_t*>(Vt + ((int64_t)k * RP + c0 + l) * n + i) = pack_bf16x2(z[0][l], z[1][l]);
+  for (int l = 0; l < 4; ++l) *reinterpret_cast<uint32_t*>(dst + transposed_at(c0 + l, i, n, frag_major)) = pack_bf16x2(z[0][l], z[1][l]);
+}
+
+// idx runs over [n/8][Rp]: one thread writes entries i .. i+7 of one row of Vb^T in operand order (neighbouring threads
+// read neighbouring columns of Vb and write neighbouring 16 bytes); columns >= R_used are zero
+__device__ __forceinline__ void image_Vb_frag_at(int64_t idx, const float* Vb, int R_cap, int R_used, int Rp, int n, bf16_t* Vbt) {
+  if (idx >= (int64_t)(n >> 3) * Rp) return;
+  const int i = (int)(idx / Rp) * 8, j = (int)(idx % Rp);
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = j < R_used ? Vb[(int64_t)(i + e) * R_cap + j] : 0.0f;
+  *reinterpret_cast<u32x4*>(Vbt + transposed_at(j, i, n, true)) =
+      u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
 }
 
 // idx runs over [m_img][RpT * 8]: one thread writes eight neighbouring entries (16 bytes) of the image [RpT][m_img][64]
@@ -367,13 +389,14 @@ hipError_t launch_probe_prep_f32(const BatchDev& b, float eps, const SeqTables& 
 
 // ---- everything a bf16 probe linear prepares before its side-down pass, in one launch ------
 // Block roles, in order: [sequence tables: 1] [token -> sequence map] [U image] [V^T image]
-// [P image] [Vb^T image: 32x32 transposing tiles].  The pieces do not depend on one another.
+// [P image] [token-side images cleared] [Vb^T image: 32x32
+// transposing tiles, or 16-byte pieces in operand order].  The pieces do not depend on one another.
 struct ProbePrepArgs {
   BatchDev b; float eps; SeqTables tabs;
   uint32_t tensor_id; int m, n, r, RP, Rp, m_img;
   const float* P; const float* Vb; int R_cap, R_used;
   bf16_t* Uimg; bf16_t* Vt; bf16_t* Pimg; bf16_t* Vbt;
-  int nb_tok, nb_U, nb_Vt, nb_P, nb_Vbt, vbt_tiles_n;
+  int nb_tok, nb_U, nb_Vt, nb_P, nb_Xs, nb_Vbt, vbt_tiles_n;
 };
 
 __global__ __launch_bounds__(1024) void k_probe_prep(ProbePrepArgs a) {
@@ -384,10 +407,16 @@ __global__ __launch_bounds__(1024) void k_probe_prep(ProbePrepArgs a) {
   blk -= a.nb_tok;
   if (blk < a.nb_U) { image_U_at(a.b, (int64_t)blk * 1024 + threadIdx.x, a.tensor_id & ~1u, a.m, a.m_img, a.r, a.tabs.SPD, a.Uimg); return; }
   blk -= a.nb_U;
-  if (blk < a.nb_Vt) { image_Vt_at(a.b, (int64_t)blk * 1024 + threadIdx.x, a.tensor_id | 1u, a.n, a.r, a.RP, a.Vt); return; }
+  if (blk < a.nb_Vt) { image_Vt_at(a.b, (int64_t)blk * 1024 + threadIdx.x, a.tensor_id | 1u, a.n, a.r, a.RP, a.tabs.Xs != nullptr, a.Vt); return; }
   blk -= a.nb_Vt;
   if (blk < a.nb_P) { image_P_at((int64_t)blk * 1024 + threadIdx.x, a.P, a.R_cap, a.R_used, a.tabs.RpT, a.m, a.m_img, a.Pimg); return; }
   blk -= a.nb_P;
+  if (blk < a.nb_Xs) {   // 1024 threads x 16 bytes: half a pool K tile
+    reinterpret_cast<u32x4*>(a.tabs.Xs)[(int64_t)blk * 1024 + threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
+    return;
+  }
+  blk -= a.nb_Xs;
+  if (a.tabs.Xs) { image_Vb_frag_at((int64_t)blk * 1024 + threadIdx.x, a.Vb, a.R_cap, a.R_used, a.Rp, a.n, a.Vbt); return; }
   // Vbt[j][i] = Vb[i][j], one 32x32 tile per block, coalesced on both sides
   __shared__ float tile[32][33];
   const int i0 = (blk % a.vbt_tiles_n) * 32, j0 = (blk / a.vbt_tiles_n) * 32;
@@ -416,9 +445,11 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   a.nb_U = blocks((int64_t)b.K * m_img * (tabs.SPD * 4));
   a.nb_Vt = blocks((int64_t)b.K * (n / 2) * (RP / 4));
   a.nb_P = Rp > 0 ? blocks((int64_t)m_img * tabs.RpT * 8) : 0;
+  static_assert(kTileN * kTileK * 2 == 2 * 1024 * 16, "two blocks clear a pool K tile");
+  a.nb_Xs = tabs.Xs ? tabs.kt_cap * 2 : 0;
   a.vbt_tiles_n = (n + 31) / 32;
-  a.nb_Vbt = Rp > 0 ? a.vbt_tiles_n * ((Rp + 31) / 32) : 0;
-  const int64_t total = 1 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Vbt;
+  a.nb_Vbt = Rp == 0 ? 0 : tabs.Xs ? blocks((int64_t)(n / 8) * Rp) : a.vbt_tiles_n * ((Rp + 31) / 32);
+  const int64_t total = 1 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Xs + a.nb_Vbt;
   hipLaunchKernelGGL(k_probe_prep, dim3((unsigned)total), dim3(1024), 0, st, a);
   return hipGetLastError();
 }

@@ -318,6 +318,104 @@ __global__ __launch_bounds__(256) void k_side_down_dirblocks(SideDownArgs a, int
     }
 }
 
+// The whole pass in one launch for small calls (side_small_call): one workgroup per (item of 16 rows, 16 columns of
+// [V | Vb]), one wave per K range.  Such a call has too few items to fill the chip one wave per (item, range): 6
+// items of a 96-row batch are 4 workgroups, each bound by the round trips of its 16 dependent steps (16 us at 4096
+// columns, then 5 us for the finishing kernel).  Here the column blocks go to workgroups of their own (X is re-read
+// from L2 once per block), a wave has the next 256 columns of its range in flight while it multiplies 256, and the
+// ranges are summed through LDS by the workgroup itself, which writes its 16 columns of the token-side images;
+// everything else in the images is cleared by the preparation launch.  Loads run along rows (row pitches are often
+// multiples of 8 KiB, which puts the same columns of all rows on the same memory channel): X comes two rows of 512
+// bytes per load, through the wave's own two stages in LDS, and V and Vb are stored in the order of the matrix
+// instruction's operands (frag_major), 1 KiB per load.
+// The products, the order within a range and over the ranges, and the rounding are those of the kernels above: a
+// row's side term has the same bits on either path.
+constexpr int kSmallCols = 256;                     // columns per batch of loads
+constexpr int kSmallStage = 16 * kSmallCols * 2;    // 16 rows: 8 KiB
+
+__global__ __launch_bounds__(512, 1) void k_side_small(SideDownArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int n_blocks = (a.RP + a.Rp) / 16, dir_blocks = a.RP / 16;
+  const int item = blockIdx.x / n_blocks, cb = blockIdx.x - item * n_blocks;
+  if (item >= a.n_items[0]) return;
+  SideItem it = a.items[item];
+  it.row0 = __builtin_amdgcn_readfirstlane(it.row0);
+  it.nrows = __builtin_amdgcn_readfirstlane(it.nrows);
+  it.kind = __builtin_amdgcn_readfirstlane(it.kind);
+  const bool dir = cb < dir_blocks;
+  if (dir && it.kind < 0) return;   // centre rows have no direction columns
+  const int split = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int steps_total = a.n / 64;
+  const int q = steps_total / a.ksplit, rem = steps_total - q * a.ksplit;
+  const int k_begin = (split * q + min(split, rem)) * 64, kchunk = (q + (split < rem ? 1 : 0)) * 64;
+  const bf16_t* v = (dir ? a.Vt + ((int64_t)it.kind * dir_blocks + cb) * 16 * a.n : a.Vbt + (int64_t)(cb - dir_blocks) * 16 * a.n) +
+                    (int64_t)k_begin * 16 + lane * 8;   // [32-column step][lane][8]
+  char* ring = lds + split * 2 * kSmallStage;
+  // load j covers rows 2j, 2j+1 of the item; chunk c of a row is stored at c ^ row.  Columns past the end of the range
+  // (or of the matrix: the window ends there) are not multiplied, rows past the item's end repeat its last row.
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(a.X + (int64_t)it.row0 * a.ldx), 0, (int)min(((int64_t)(it.nrows - 1) * a.ldx + a.n) * 2, (int64_t)0x7FFFFFFF), 0x00020000);
+  uint32_t x_off[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int row = 2 * j + (lane >> 5);
+    x_off[j] = (uint32_t)min(row, it.nrows - 1) * (uint32_t)(a.ldx * 2) + (uint32_t)(k_begin * 2) + ((lane & 31) ^ row) * 16;
+  }
+  bf16x8 fv[8];
+  auto fetch = [&](int k, int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)(ring + stage * kSmallStage + j * 1024), 16, (int)x_off[j], k * 2, 0, 0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) fv[u] = load_frag(v + (int64_t)min(k + u * 32, kchunk - 32) * 16);
+  };
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (kchunk > 0) fetch(0, 0);
+  for (int k = 0, stage = 0; k < kchunk; k += kSmallCols, stage ^= 1) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bf16x8 cv[8], cx[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      cv[u] = fv[u];
+      cx[u] = *(const bf16x8*)(ring + stage * kSmallStage + lr * (kSmallCols * 2) + (((u * 4 + lg) ^ lr) << 4));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (k + kSmallCols < kchunk) fetch(k + kSmallCols, stage ^ 1);
+    const int steps = min(kchunk - k, kSmallCols) / 32;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < steps) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cv[u], cx[u], acc, 0, 0, 0);
+  }
+  __syncthreads();   // every wave is done with its stages: their memory takes the sums of the ranges
+  f32x4* part = reinterpret_cast<f32x4*>(lds);   // [range][lane]
+  part[split * 64 + lane] = acc;
+  __syncthreads();
+  if (split != 0 || lr >= it.nrows) return;
+  f32x4 y = {0.f, 0.f, 0.f, 0.f};
+  for (int sp = 0; sp < a.ksplit; ++sp) y += part[sp * 64 + lane];
+  // where the row's 16 columns live in the images of its token tile
+  const int row = it.row0 + lr;
+  const TileHdr h = a.tile_hdr[row / kTileN];
+  int kt, col;
+  if (dir) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] *= it.scale;
+    const int block = it.kind * a.SPD + ((cb * 16) >> 5);
+    int slot = 0;
+    while (slot < h.n_slots && a.tile_slots[h.slot0 + slot] != block) ++slot;
+    if (slot == h.n_slots) return;   // cannot happen: the tile lists every direction among its rows
+    kt = h.kt0 + (slot >> 1);
+    col = (slot & 1) * 32 + ((cb * 16) & 31);
+  } else {
+    const int bcol = (cb - dir_blocks) * 16;
+    kt = h.kt0 + ((h.n_slots + 1) >> 1) + (bcol >> 6);
+    col = bcol & 63;
+  }
+  *reinterpret_cast<uint2*>(a.Xs + ((int64_t)kt * kTileN + row % kTileN) * kTileK + col + lg * 4) =
+      make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+}
+
 // Finishes the side-down pass: sums the K-range partials of every candidate row in range order, scales the
 // direction columns by sign * eps, rounds to bf16 and writes the token-side images of the GEMM's side K
 // tiles: pool K tile p = [256 rows of its token tile][64 columns].  Direction K tile j of a tile holds the
@@ -410,6 +508,16 @@ static hipError_t launch_pass_n(int nbb, const SideDownArgs& a, int cb0, hipStre
 
 hipError_t launch_side_down_bf16(const SideDownArgs& a, hipStream_t st) {
   if (a.T == 0 || a.max_items == 0) return hipSuccess;
+  if (side_small_call(a.T, a.n, a.RP + a.Rp)) {
+    static std::atomic<bool> configured[kMaxDevices];
+    const hipError_t ec = once_per_device(configured, [] {
+      return hipFuncSetAttribute((const void*)k_side_small, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 2 * kSmallStage);
+    });
+    if (ec != hipSuccess) return ec;
+    hipLaunchKernelGGL(k_side_small, dim3((unsigned)a.max_items * (unsigned)((a.RP + a.Rp) / 16)), dim3(a.ksplit * 64),
+                       a.ksplit * 2 * kSmallStage, st, a);
+    return hipGetLastError();
+  }
   const int bank_blocks = a.Rp / 16;
   // first pass: direction block 0 together with up to 8 bank blocks
   int done = bank_blocks < kSideMaxBlocks - 1 ? bank_blocks : kSideMaxBlocks - 1;

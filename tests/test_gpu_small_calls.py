@@ -115,3 +115,19 @@ def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
     out = torch.empty((T, H * dh), device=DEV, dtype=torch.bfloat16)
     zb.zo_attention(b.struct, dev[0], H * dh, dev[1], Hkv * dh, dev[2], Hkv * dh, H, Hkv, dh, scale, zb.ZO_BF16, out, H * dh)
     assert_close(to_np(out), ob.attention(q, k, v, cu, H, Hkv, dh, scale, "bf16"), 2e-2, "attention")
+
+
+# around the line between the one-launch side-down pass and the staged one (2400 waves of 16 rows, 16 columns and one K
+# range), at widths whose ranges end inside and at the end of a batch of 256 columns, with 1, 2, 4 and 8 ranges
+@pytest.mark.parametrize("n,r,R", [(64, 1, 0), (448, 48, 16), (1088, 16, 40), (2560, 8, 136), (5184, 70, 0), (20480, 4, 32)])
+def test_side_term_on_either_pass(n, r, R):
+    lens = [1, 17, 0, 40, 16, 5] + [200] * (8 if n > 10000 else 200 if n == 64 else 110)
+    w = _layer(n, lens, [i % 8 - 1 for i in range(len(lens))], 64, n, r, R, 0, False)
+    big = DeviceWorkload(w, DEV, out_dtype="f32")
+    y = big.probe_linear(0)
+    rows = np.r_[0:80, w.T - 80:w.T]
+    assert_close(to_np(y)[rows], oracle_layer(w, 0, w.layers[0].X, out_dtype="f32")[rows], 2e-2, "Y")
+    sub = wl.subset_sequences(w, np.array([5, 3, 1, 0, 2, 4]))
+    b = DeviceWorkload(sub, DEV, out_dtype="f32").probe_linear(0)
+    torch.cuda.synchronize()
+    assert torch.equal(y[torch.from_numpy(np.asarray(sub.meta["rows"])).to(DEV)], b)
