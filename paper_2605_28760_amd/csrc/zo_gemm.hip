@@ -780,6 +780,108 @@ hipError_t launch_probe_gemm_bf16(const ProbeGemmArgs& a, hipStream_t st) {
 // ---------------------------------------------------------------------------------------
 int head_vocab_tiles_bf16(int vocab) { return (vocab + BM - 1) / BM; }
 
+// The head against at most 128 tokens.  Half of a 256-token tile's matrix instructions would be padding, and the call
+// is then bound by them (147 us for 128 tokens against 50272 x 5120) instead of by the weights' way from HBM.  A tile of
+// 256 vocabulary rows x 128 tokens: a wave still owns 128 rows of its tokens, so every sum has the order (and the
+// bits) of the wide tile; the 48 KiB of a stage leave room for three, with every K tile requested two periods ahead.
+// One vocabulary tile per workgroup at a time.
+constexpr int kNarrowTokens = BN / 2;
+constexpr int kNarrowStage = kOperandStage + kNarrowTokens * BK * 2;   // 48 KiB: 256 weight rows, 128 tokens
+static_assert(3 * kNarrowStage + 4 * BN * 4 <= kGemmLds, "three stages and the exchange buffers");
+
+template <class Done>
+__device__ __forceinline__ void narrow_head(const HeadScoreArgs& p, int n_tm, int n_tok, char* lds, Done done) {
+  constexpr int kCB = 2;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int wm = wave >> 2, wn = wave & 3;
+  const int nk = p.d / BK;
+  // token rows: load j (0, 1) covers rows (2 wave + j) * 8 .. + 7 of the tile, gathered through the list
+  uint32_t offB[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int row = (wave * 2 + j) * 8 + (lane >> 3);
+    offB[j] = (uint32_t)p.rows[min(row, n_tok - 1)] * (uint32_t)(p.ldh * 2) + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+  }
+  const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)p.H, 0, (int)min(((int64_t)(p.T - 1) * p.ldh + p.d) * 2, (int64_t)0x7FFFFFFF), 0x00020000);
+  uint32_t roff[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) roff[ks] = (lane & 15) * 128 + (((ks * 4 + (lane >> 4)) ^ (((lane & 15) >> 1) & 7)) << 4);
+
+  for (int tm = blockIdx.x; tm < n_tm; tm += gridDim.x) {
+    const int m0 = tm * BM;
+    uint32_t offA[kLPW];
+#pragma unroll
+    for (int j = 0; j < kLPW; ++j) {
+      const int row = (wave * kLPW + j) * 8 + (lane >> 3);
+      offA[j] = __umul24((uint32_t)min(row, p.vocab - 1 - m0), (uint32_t)p.ldw * 2u) + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+    }
+    const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(p.Wh + (int64_t)m0 * p.ldw), 0,
+        (int)min(((int64_t)(p.vocab - m0 - 1) * p.ldw + p.d) * 2, (int64_t)0x7FFFFFFF), 0x00020000);
+    auto issue = [&](int kt, int stg) __attribute__((always_inline)) {
+      char* sb = lds + stg * kNarrowStage;
+      const int soff = min(kt, nk - 1) * (BK * 2);   // (past the last K tile: a stage nobody reads again)
+#pragma unroll
+      for (int j = 0; j < kLPW; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void*)(sb + (wave * kLPW + j) * 1024), 16, (int)offA[j], soff, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, (lds_void*)(sb + kOperandStage + (wave * 2 + j) * 1024), 16, (int)offB[j], soff, 0, 0);
+    };
+    bf16x8 fa[2][RB], fb[2][kCB];
+    auto frags = [&](int set, int stg, int ks) __attribute__((always_inline)) {
+      const char* sb = lds + stg * kNarrowStage;
+#pragma unroll
+      for (int cb = 0; cb < kCB; ++cb) fb[set][cb] = *(const bf16x8*)(sb + kOperandStage + (wn * kCB + cb) * 2048 + roff[ks]);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) fa[set][rb] = *(const bf16x8*)(sb + wm * 128 * 128 + rb * 2048 + roff[ks]);
+    };
+    f32x4 acc[RB][kCB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < kCB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mfmas = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < kCB; ++cb)
+          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[set][rb], fb[set][cb], acc[rb][cb], 0, 0, 0);
+    };
+    block_barrier();   // the exchange buffers and stages of the tile before are free
+    issue(0, 0);
+    issue(1, 1);
+    issue(2, 2);
+    static_assert(kLPW + 2 == 6, "the counts of the waits below");
+    asm volatile("s_waitcnt vmcnt(12)" ::: "memory");   // K tile 0 has landed (2 x 6 loads may be outstanding)
+    block_barrier();
+    frags(0, 0, 0);
+    int stg = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      frags(1, stg, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(0);
+      __builtin_amdgcn_sched_barrier(0);
+      // the next K tile has landed; every wave is done reading this one's stage, which takes the one three ahead
+      asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
+      block_barrier();
+      issue(kt + 3, stg);
+      const int nxt = stg == 2 ? 0 : stg + 1;
+      frags(0, nxt, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      mfmas(1);
+      __builtin_amdgcn_sched_barrier(0);
+      stg = nxt;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // drain the trailing loads
+    block_barrier();                                  // ... of every wave, and its last (unused) fragment reads
+    done(m0, 0, acc, std::integral_constant<int, kCB>{});
+  }
+}
+
 // kGather: only the scored tokens (rows p.rows[0 .. *p.n_rows - 1] of H) are multiplied; token tiles
 // and the partial outputs then run over positions in that list.
 template <bool kGather>
@@ -792,19 +894,23 @@ __global__ __launch_bounds__(kThreads, 1) void k_head_score(HeadScoreArgs p, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int wm = wave >> 2, wn = wave & 3;
-  float* s_max = (float*)(lds + kStagesLds);   // [2 wave rows][256 tokens]
-  float* s_sum = s_max + 2 * BN;                // [2 wave rows][256 tokens]
+  // [2 wave rows][256 tokens] each: behind the operand stages of the wide and of the narrow tile
+  float* s_max = (float*)(lds + 3 * kNarrowStage);
+  float* s_sum = s_max + 2 * BN;
   constexpr float kLog2e = 1.4426950408889634f;
 
-  // D block (rb, cb): vocabulary row = vbase + rb*16 + 4*g + v, token = tile_t0 + wn*64 + cb*16 + r16.
-  auto epilogue = [&](int tile_v0, int tile_t0, Acc& acc, auto) {
+  // D block (rb, cb): vocabulary row = vbase + rb*16 + 4*g + v, token = tile_t0 + wn*kCB*16 + cb*16 + r16; kCB = 16-token
+  // blocks of a wave: 4 in a 256-token tile, 2 in a narrow one of 128.
+  auto tile_done = [&](int tile_v0, int tile_t0, auto& acc, auto cb_c) __attribute__((always_inline)) {
+    constexpr int kCB = decltype(cb_c)::value;
+    constexpr int kTokens = 4 * kCB * 16;
     const int lane_t = opaque(lane), tid_t = opaque(tid);
     const int r16 = lane_t & 15, g = lane_t >> 4;
     const int tm = tile_v0 / BM;   // vocabulary tile: the index of this tile's partials
     const int vbase = tile_v0 + wm * 128;  // first vocabulary row of this wave
     if (tile_v0 + BM > p.vocab) {   // the last vocabulary tile: rows past the end count as -inf
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
+      for (int cb = 0; cb < kCB; ++cb)
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -812,8 +918,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_head_score(HeadScoreArgs p, int
             if (vbase + rb * 16 + 4 * g + v >= p.vocab) acc[rb][cb][v] = -INFINITY;
     }
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-      const int tl = wn * 64 + cb * 16 + r16;   // token within the tile
+    for (int cb = 0; cb < kCB; ++cb) {
+      const int tl = wn * (kCB * 16) + cb * 16 + r16;   // token within the tile
       const int t = tile_t0 + tl;               // its position (in the list of scored tokens, or its row)
       float mx = -INFINITY;
 #pragma unroll
@@ -851,7 +957,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_head_score(HeadScoreArgs p, int
     block_barrier();   // (not __syncthreads: the operand loads of the next tile stay in flight)
     {
       const int t = tile_t0 + tid_t;
-      if (tid_t < BN && t < n_tok) {
+      if (tid_t < kTokens && t < n_tok) {
         const float m0 = s_max[tid_t], m1 = s_max[BN + tid_t];
         const float Mx = fmaxf(m0, m1);
         const float mref = (Mx == -INFINITY) ? 0.0f : Mx;
@@ -864,6 +970,16 @@ __global__ __launch_bounds__(kThreads, 1) void k_head_score(HeadScoreArgs p, int
     // (no barrier here: the exchange buffers are written again after the next tile's K loop, whose barriers
     // every thread passes only after these reads)
   };
+
+  auto epilogue = [&](int tile_v0, int tile_t0, Acc& acc, auto) { tile_done(tile_v0, tile_t0, acc, std::integral_constant<int, CB>{}); };
+
+  // Up to 128 scored tokens (the label token of each sequence of a batch): one narrow token tile.
+  if constexpr (kGather) {
+    if (n_tok <= kNarrowTokens) {
+      narrow_head(p, n_tm, n_tok, lds, tile_done);
+      return;
+    }
+  }
 
   persistent_gemm<kGather, false, false>(p.Wh, p.ldw, p.vocab, p.H, p.ldh, n_tok, p.d, n_tm, n_tn, tn_super, 0, lds, epilogue,
                                          SideOperands{}, p.rows, p.T);

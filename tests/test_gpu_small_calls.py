@@ -131,3 +131,31 @@ def test_side_term_on_either_pass(n, r, R):
     b = DeviceWorkload(sub, DEV, out_dtype="f32").probe_linear(0)
     torch.cuda.synchronize()
     assert torch.equal(y[torch.from_numpy(np.asarray(sub.meta["rows"])).to(DEV)], b)
+
+
+@pytest.mark.parametrize("vocab,d", [(300, 64), (257, 192), (70000, 128)])
+@pytest.mark.parametrize("scored", [1, 15, 127, 128, 129])
+def test_few_scored_tokens_have_the_bits_of_a_full_call(vocab, d, scored):
+    """Up to 128 scored tokens take a narrow token tile: one to five K tiles, vocabularies that end one row into a
+    tile, inside a wave's rows and past one round of workgroups."""
+    rng = np.random.default_rng(vocab + scored)
+    T = 600
+    cu = np.array([0, 100, 100, 350, T], np.int32)
+    w = wl.Workload("few", 9, "bf16", 4, 1e-3, cu, np.array([0, 1, -1, 0], np.int32), np.zeros(2, np.int32),
+                    np.array([1, -1], np.float32), np.arange(1, dtype=np.uint64), [], True,
+                    wl.as_bf16_values(rng.standard_normal((T, d)).astype(np.float32)),
+                    wl.as_bf16_values((rng.standard_normal((vocab, d)) / np.sqrt(d)).astype(np.float32)),
+                    rng.integers(0, vocab, T).astype(np.int32), 0)
+    g = DeviceWorkload(w, DEV)
+    g.score(H=g.X)
+    full = g.tok_nll.clone()
+    keep = torch.from_numpy(np.sort(rng.choice(T, scored, replace=False))).to(DEV)
+    few = torch.full_like(g.targets, -1)
+    few[keep] = g.targets[keep]
+    g.targets = few
+    g.tok_nll.fill_(float("nan"))
+    g.score(H=g.X)
+    torch.cuda.synchronize()
+    assert torch.equal(g.tok_nll[keep], full[keep])
+    assert int((g.tok_nll != 0).sum()) <= scored and float(g.cand_cnt.sum()) <= scored
+    assert_close(to_np(full), zo.token_nll(w.X, w.head, w.targets), 1e-4, "tok_nll", atol=1e-4)
