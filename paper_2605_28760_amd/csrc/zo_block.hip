@@ -277,21 +277,23 @@ __device__ __forceinline__ bool find_query_block(const int32_t* cu, int S, int w
   for (int s0 = 0; s0 < S; s0 += kWave) {
     const int i = s0 + lane;
     const int nb = i < S ? (cu[i + 1] - cu[i] + kBQ - 1) / kBQ : 0;
+    // inclusive scan in the vector ALU: within rows of 16 lanes, then row 0 into 1, 2 into 3, then lane 31 into rows 2, 3
     int inc = nb;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int up = __shfl_up(inc, o);
-      if (lane >= o) inc += up;
-    }
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x142, 0xa, 0xf, false);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x143, 0xc, 0xf, false);
     const int excl = base + inc - nb;
     const unsigned long long hit = __ballot(w >= excl && w < excl + nb);
     if (hit) {
       const int src = __ffsll((long long)hit) - 1;
       seq = s0 + src;
-      qb = w - __shfl(excl, src);
+      qb = w - __builtin_amdgcn_readlane(excl, src);
       return true;
     }
-    base += __shfl(inc, kWave - 1);
+    base += __builtin_amdgcn_readlane(inc, kWave - 1);
   }
   return false;
 }
@@ -322,7 +324,7 @@ __device__ __forceinline__ bool find_query_block(const int32_t* cu, int S, int w
 // SIMD cover each other's latencies (32 keys per step keep a wave under 168 registers and a workgroup at
 // 48 KiB of LDS; two waves, 64 keys: 412 us).
 // 8 sequences of 2048 rows, 40 heads: 550 -> 398 us (865 TFLOP/s of causal work); 14144 ragged rows of up
-// to 512, 32 heads over 8: 134 -> 106 us, bound by the latency of a workgroup's start and its few steps.
+// to 512, 32 heads over 8: 134 -> 107 us, bound by the latency of a workgroup's start and its few steps.
 constexpr float kRaise = 1.0f;
 
 // Largest of the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes that share a query), in the vector ALU.
