@@ -159,3 +159,17 @@ def test_few_scored_tokens_have_the_bits_of_a_full_call(vocab, d, scored):
     assert torch.equal(g.tok_nll[keep], full[keep])
     assert int((g.tok_nll != 0).sum()) <= scored and float(g.cand_cnt.sum()) <= scored
     assert_close(to_np(full), zo.token_nll(w.X, w.head, w.targets), 1e-4, "tok_nll", atol=1e-4)
+
+
+@pytest.mark.parametrize("S,K", [(1025, 3), (1500, 70), (300, 70), (1024, 64)])
+def test_tables_of_many_sequences_and_directions(S, K):
+    """More than 1024 sequences (tables in global memory instead of LDS) and more than 64 directions (slot lists searched
+    instead of a mask), many of them inside one token tile."""
+    rng = np.random.default_rng(S + K)
+    lens = rng.integers(0, 4, S)
+    w = _layer(S, lens.tolist(), rng.integers(-1, 2 * K, S).tolist(), 64, 64, 4, 16, 0, False)
+    w.cand_dir = np.repeat(np.arange(K, dtype=np.int32), 2)
+    w.cand_sign = np.tile(np.array([1, -1], np.float32), K)
+    w.dir_seed = np.arange(K, dtype=np.uint64) + np.uint64(5)
+    y = DeviceWorkload(w, DEV, out_dtype="f32").probe_linear(0)
+    assert_close(to_np(y), oracle_layer(w, 0, w.layers[0].X, out_dtype="f32"), 2e-2, "Y")
