@@ -16,7 +16,7 @@
 // Vb is staged once per workgroup in LDS.  A wave's rows of X land in
 // its own two-stage ring in LDS (direct-to-LDS loads of whole 128-byte lines,
 // no registers tied up by bytes in flight): while a wave multiplies step s, the
-// lines of steps s+1 and s+2 are on their way.
+// lines of steps s+1 and s+2 are on their way.  Small calls take one launch with another split (k_side_small).
 #include <type_traits>
 
 #include "zo_device.hpp"
