@@ -508,7 +508,9 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 3) void k_attention_bf16(AttnArg
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt)
       if (__any(mx[qt] > m_run[qt] + slack)) {
-        const float m = fmaxf(column_max(mx[qt]), m_run[qt]);
+        // each query by its own scores: what the other rows of the tile hold must not move it
+        const float c = column_max(mx[qt]);
+        const float m = c > m_run[qt] + slack ? c : m_run[qt];
         const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m);
         m_run[qt] = m;
         lacc[qt] *= alpha;

@@ -206,6 +206,22 @@ def test_attention_rows_do_not_depend_on_the_rest_of_the_batch():
         np.testing.assert_array_equal(alone, packed[a:b])
 
 
+@pytest.mark.parametrize("n,keep", [(700, (1, 33, 190, 263, 385, 513, 699)), (1500, (900, 1137, 1405))])
+@pytest.mark.parametrize("scale,grow", [(128 ** -0.5, 0.0), (0.08, 0.0), (0.05, 0.01), (0.3, 0.0)])
+def test_attention_rows_do_not_depend_on_later_rows(n, keep, scale, grow):
+    """A causal row has the same bits whether its sequence ends right after it or goes on, also far into the sequence,
+    where some rows of a tile of 16 meet a new largest score by a little, some by a lot and some not at all."""
+    dh, H, Hkv = 128, 4, 2
+    g = _rng(n + int(1000 * scale))
+    q, k, v = g.normal(size=(n, H * dh)), g.normal(size=(n, Hkv * dh)), g.normal(size=(n, Hkv * dh))
+    q += grow != 0
+    k += grow * np.arange(n)[:, None]
+    whole, _ = _run_attention(q, k, v, [n], H, Hkv, dh, scale, "bf16")
+    for m in keep:
+        head, _ = _run_attention(q[:m], k[:m], v[:m], [m], H, Hkv, dh, scale, "bf16")
+        np.testing.assert_array_equal(head, whole[:m], err_msg="rows before %d" % m)
+
+
 def test_attention_empty_batches():
     batch, _ = _plain_batch([0, 0])
     dummy = torch.zeros((1, 128), device=DEV, dtype=torch.bfloat16)
