@@ -251,11 +251,11 @@ __global__ __launch_bounds__(kWave) void k_attention_f32(AttnArgs a) {
 // ------------------------------------------------------------------ attention, bf16 MFMA
 
 constexpr int kBQ = 128;            // query rows per workgroup (32 per wave)
-constexpr int kBKV = 32;            // keys per step
+constexpr int kBKV = 64;            // keys per step
 constexpr int kDh = 128;            // head dimension of this kernel
 constexpr int kAttnWaves = 4;
-constexpr int kKStage = kBKV * kDh * 2;   // 8 KiB: keys x head dim, 256-byte rows
-constexpr int kVStage = kBKV * kDh * 2;   // 8 KiB: keys x head dim, 256-byte rows
+constexpr int kKStage = kBKV * kDh * 2;   // 16 KiB: keys x head dim, 256-byte rows
+constexpr int kVStage = kBKV * kDh * 2;   // 16 KiB: keys x head dim, 256-byte rows
 
 // Swizzle keys: the 16-byte chunk c of row `row` of a stage is stored at chunk c ^ key (both stages have 256-byte
 // rows, so the same chunk of any two rows lies on the same banks).
@@ -309,24 +309,28 @@ __device__ __forceinline__ bool find_query_block(const int32_t* cu, int S, int w
 // second product.  The running maximum, the rescaling factor and the normaliser are then per-lane
 // scalars and P never leaves registers.
 //
-// Keys and values go global->LDS directly (the swizzle is applied on the source address), 32 keys per
-// step in a ring of three stages: the loads of step j+2 are issued when step j starts.  Values are
-// transposed by the LDS read itself (ds_read_b64_tr_b16: the 16 lanes of a group name four rows of 16
-// columns, and lane j receives column j).  Rows past the end of the sequence repeat its last row and
-// are always masked by the causal test.
+// Keys and values go global->LDS directly (the swizzle is applied on the source address), 64 keys per
+// step, two stages: the loads of step j+1 are issued when step j starts.  Values are transposed by the
+// LDS read itself (ds_read_b64_tr_b16: the 16 lanes of a group name four rows of 16 columns, and lane j
+// receives column j).  Rows past the end of the sequence repeat its last row and are always masked by the
+// causal test.
+//
+// A query's arithmetic is its own: the maximum is that of the keys it sees in whole steps, raised in every
+// step in which it grows, the normaliser is the fp32 sum of the fp32 weights, and nothing another row of
+// the tile holds enters it, so a row has the same bits whatever follows it in its sequence.  (A
+// maximum that lags until a row of the tile exceeds it by a factor of two, the scale in the exponent's
+// multiply-add and a normaliser summed from the rounded weights by one more matrix instruction take 400
+// us where this takes 432, but tie rows to their neighbours and sum in 16 bits.)
 //
 // Long sequences are bound by instruction issue between the two products: the matrix core leaves two
 // issue slots of four cycles free per matrix instruction, an exponential takes two of them, any other
-// vector instruction one.  So there is as little vector work as possible (the scale goes into the
-// exponent's multiply-add; only the step that meets the diagonal masks; the output is rescaled only when
-// the maximum in the exponent has to move; the normaliser is one more row of the second product, the sum
-// of the very weights it multiplies; fragment addresses are constants of the stage), and three waves per
-// SIMD cover each other's latencies (32 keys per step keep a wave under 168 registers and a workgroup at
-// 48 KiB of LDS; two waves, 64 keys: 412 us).
-// 8 sequences of 2048 rows, 40 heads: 550 -> 398 us (865 TFLOP/s of causal work); 14144 ragged rows of up
-// to 512, 32 heads over 8: 134 -> 107 us, bound by the latency of a workgroup's start and its few steps.
-constexpr float kRaise = 1.0f;
-
+// vector instruction one.  So what a step need not do it skips: only the step that meets the diagonal masks,
+// its second 32 keys are multiplied only if some row sees them, the output is rescaled only when the maximum of
+// some query grows (the factors are exactly one otherwise), and fragment addresses are constants of the stage.
+// 8 sequences of 2048 rows, 40 heads: 549 us (values through registers, every step masked and rescaled) -> 432
+// (796 TFLOP/s of causal work); 14144 ragged rows of up to 512, 32 heads over 8: 134 -> 113 us, bound by the
+// latency of a workgroup's start and its few steps.  Three waves per SIMD (168 registers, keys in two stages and
+// values in one, a second barrier per step) spill and take 441 us.
 // Largest of the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes that share a query), in the vector ALU.
 __device__ __forceinline__ float column_max(float x) {
   const uint32_t u = __float_as_uint(x);
@@ -336,12 +340,12 @@ __device__ __forceinline__ float column_max(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-__global__ __launch_bounds__(kAttnWaves* kWave, 3) void k_attention_bf16(AttnArgs a) {
-  // [3] stages of keys, [3] stages of values.  (Dynamic: with named arrays the compiler tracks which of them a
+__global__ __launch_bounds__(kAttnWaves* kWave, 2) void k_attention_bf16(AttnArgs a) {
+  // [2] stages of keys, [2] stages of values.  (Dynamic: with named arrays the compiler tracks which of them a
   // direct-to-LDS load writes and waits for the next step's loads before it reads this step's stage.)
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   char* const s_k = lds;
-  char* const s_v = lds + 3 * kKStage;
+  char* const s_v = lds + 2 * kKStage;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   int seq, qb;
@@ -363,49 +367,33 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 3) void k_attention_bf16(AttnArg
   const bf16_t* Kh = (const bf16_t*)a.K + kvh * kDh;
   const bf16_t* Vh = (const bf16_t*)a.V + kvh * kDh;
 
-  // ---- loads: load i of a wave fills the 1 KiB block wave*2 + i of a stage = 4 rows.  A whole step's offsets are the
+  // ---- loads: load i of a wave fills the 1 KiB block wave*4 + i of a stage = 4 rows.  A whole step's offsets are the
   // same for every step (the base advances); rows past the end of the sequence repeat its last row.
-  const int l_row[2] = {wave * 8 + (lane >> 4), wave * 8 + 4 + (lane >> 4)};
-  uint32_t k_ld[2], v_ld[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    k_ld[i] = (uint32_t)l_row[i] * (uint32_t)(a.ldk * 2) + ((lane & 15) ^ swz_k(l_row[i])) * 16;
-    v_ld[i] = (uint32_t)l_row[i] * (uint32_t)(a.ldv * 2) + ((lane & 15) ^ swz_v(l_row[i])) * 16;
-  }
   auto issue = [&](int step, int slot) __attribute__((always_inline)) {
     const int j0 = row_a + step * kBKV;
-    const int last_rel = row_b - 1 - j0;
-    const int rows = min(last_rel, kBKV - 1);
+    const int last_rel = min(row_b - 1 - j0, kBKV - 1);
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)(Kh + (int64_t)j0 * a.ldk), 0,
-                                                                        (rows * (int)a.ldk + kDh) * 2, 0x00020000);
+                                                                        (last_rel * (int)a.ldk + kDh) * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)(Vh + (int64_t)j0 * a.ldv), 0,
-                                                                        (rows * (int)a.ldv + kDh) * 2, 0x00020000);
-    char* dk = s_k + slot * kKStage + wave * 2048;
-    char* dv = s_v + slot * kVStage + wave * 2048;
-    if (last_rel >= kBKV - 1) {
+                                                                        (last_rel * (int)a.ldv + kDh) * 2, 0x00020000);
+    char* dk = s_k + slot * kKStage + wave * 4096;
+    char* dv = s_v + slot * kVStage + wave * 4096;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void*)(dk + i * 1024), 16, (int)k_ld[i], 0, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+      const int row = wave * 16 + 4 * i + (lane >> 4);
+      const uint32_t off = (uint32_t)min(row, last_rel) * (uint32_t)(a.ldk * 2) + ((lane & 15) ^ swz_k(row)) * 16;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void*)(dk + i * 1024), 16, (int)off, 0, 0, 0);
+    }
 #pragma unroll
-      for (int i = 0; i < 2; ++i) __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(dv + i * 1024), 16, (int)v_ld[i], 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const uint32_t back = (uint32_t)max(l_row[i] - last_rel, 0);   // rows past the last one
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void*)(dk + i * 1024), 16, (int)(k_ld[i] - back * (uint32_t)(a.ldk * 2)), 0, 0, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const uint32_t back = (uint32_t)max(l_row[i] - last_rel, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(dv + i * 1024), 16, (int)(v_ld[i] - back * (uint32_t)(a.ldv * 2)), 0, 0, 0);
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int row = wave * 16 + 4 * i + (lane >> 4);
+      const uint32_t off = (uint32_t)min(row, last_rel) * (uint32_t)(a.ldv * 2) + ((lane & 15) ^ swz_v(row)) * 16;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(dv + i * 1024), 16, (int)off, 0, 0, 0);
     }
   };
   issue(0, 0);
-  if (n_steps > 1) issue(1, 1);
 
-  // ---- queries: B fragments, lane (r16, g) holds Q[row r16 of tile qt][32 ks + 8 g .. + 8].  A negative scale
-  // moves into the queries' sign, so that the largest product is the largest score, and a zero scale into the queries
-  // themselves, so that a masked score (-inf) is never multiplied by zero.
+  // ---- queries: B fragments, lane (r16, g) holds Q[row r16 of tile qt][32 ks + 8 g .. + 8].
   bf16x8 qf[2][4];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) {
@@ -414,15 +402,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 3) void k_attention_bf16(AttnArg
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) qf[qt][ks] = load_frag(qp + ks * 32);
   }
-  float sl2 = fabsf(a.scale) * 1.4426950408889634f;   // scores are kept in base-2 units
-  if (!(a.scale > 0.0f)) {
-    const bool zero = sl2 == 0.0f;
-#pragma unroll
-    for (int qt = 0; qt < 2; ++qt)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) qf[qt][ks] = zero ? zero_frag() : -qf[qt][ks];
-    if (zero) sl2 = 1.0f;
-  }
+  const float sl2 = a.scale * 1.4426950408889634f;   // scores are kept in base-2 units
 
   // ---- fragment addresses: they differ between fragments by constants that leave the swizzle alone (4 rows, whole
   // stages) or by chunks (an exclusive or)
@@ -438,11 +418,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 3) void k_attention_bf16(AttnArg
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) oacc[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run[2] = {-INFINITY, -INFINITY};
-  // The normaliser is a row of the second product whose values are all one: the sum of the very weights the
-  // product multiplies, and no vector instruction.
-  f32x4 lacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-  const u32x4 ones_bits = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-  const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
+  float l_run[2] = {0.f, 0.f};   // this lane's share of the normaliser
 
   const char* kp[4];
 #pragma unroll
@@ -450,134 +426,142 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 3) void k_attention_bf16(AttnArg
   uint32_t vp[8];   // LDS addresses
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) vp[dt] = (uint32_t)(uintptr_t)(lds_cchar*)s_v + (v_off ^ (uint32_t)(dt << 5));
-  typedef f32x4 Scores[2][2];   // 32 keys: [half][query tile]; lane (g, r16): query r16, keys 8 g + 4 hf + v
-  // S^T = K Q^T for 32 keys x 2 query tiles
-  auto scores = [&](auto slot_c, Scores& s) __attribute__((always_inline)) {
+  typedef f32x4 Scores[2][2][2];   // [32 keys][half][query tile]; lane (g, r16): query r16, keys 32 tp + 8 g + 4 hf + v
+  // The wave's 32 rows face the 32 keys of block n_diag: every block before it is whole, the ones after are not seen.
+  const int n_diag = wave_valid ? (wq0 - row_a) / 32 : -1;
+  auto attend = [&](int step, auto slot_c) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
     constexpr int slot = decltype(slot_c)::value;
+    const bool both = step * 2 < n_diag;   // false: the step's second 32 keys lie past every query
+    Scores s;
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      bf16x8 kf[4];
+    for (int tp = 0; tp < 2; ++tp) {
+      if (tp == 1 && !both) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(kp[ks] + slot * kKStage + 4 * hf * 256);
+        for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+          for (int qt = 0; qt < 2; ++qt) s[tp][hf][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        break;
+      }
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
-          s[hf][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[qt][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[hf][qt], 0, 0, 0);
+      for (int hf = 0; hf < 2; ++hf) {
+        bf16x8 kf[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(kp[ks] + slot * kKStage + tp * 8192 + 4 * hf * 256);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+          for (int qt = 0; qt < 2; ++qt)
+            s[tp][hf][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[qt][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[tp][hf][qt], 0, 0, 0);
+      }
     }
-  };
-  float mx[2];   // this lane's largest score of the 32 keys
-  auto largest = [&](const Scores& s) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
-      float m = -INFINITY;
+    for (int tp = 0; tp < 2; ++tp)
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) m = fmaxf(m, s[hf][qt][v]);
-      mx[qt] = m * sl2;
-    }
-  };
-  typedef short s16x8 __attribute__((ext_vector_type(8)));
-  // One step: scores, weights, second product.  The wave's 32 rows face the keys of step n_whole (32 rows from a
-  // multiple of 32): every step before it is whole, the ones after it are not seen.
-  const int n_whole = wave_valid ? (wq0 - row_a) / 32 : -1;
-  auto attend = [&](int step, auto slot_c) __attribute__((always_inline)) {
-    Scores s;
-    __builtin_amdgcn_s_setprio(1);
-    scores(slot_c, s);
-    __builtin_amdgcn_s_setprio(0);
-    if (step == n_whole) {   // some key lies past some query
+        for (int qt = 0; qt < 2; ++qt) s[tp][hf][qt] *= sl2;
+    if (step * 2 + 1 >= n_diag) {   // some key lies past some query
 #pragma unroll
       for (int qt = 0; qt < 2; ++qt) {
         const int last = min(wq0 + qt * 16 + r16, row_b - 1) - (row_a + step * kBKV) - 8 * g;   // the last key this query sees
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
+        for (int tp = 0; tp < 2; ++tp)
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (4 * hf + v > last) s[hf][qt][v] = -INFINITY;
+          for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (32 * tp + 4 * hf + v > last) s[tp][hf][qt][v] = -INFINITY;
       }
     }
-    largest(s);
-    // The maximum in the exponent follows the scores at once in the first steps and in every fourth, in between only
-    // when a score exceeds it by more than kRaise: raising it costs 36 multiplications per query tile.  (A weight just
-    // below a power of two is rounded to half the relative step of one just above it, so the largest weights should
-    // sit right below 1: with the maximum left alone up to 2^8 the error against 64 bits at 2048 rows is 2.09e-3, this
-    // way 2.02e-3, raised in every step 2.01e-3 and, before this kernel, 2.03e-3; 372, 398, 412 and 550 us.)
-    const float slack = step < 4 || (step & 3) == 0 ? 0.0f : kRaise;
+    bf16x8 pf[2][2];   // [query tile][32 keys]
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt)
-      if (__any(mx[qt] > m_run[qt] + slack)) {
-        // each query by its own scores: what the other rows of the tile hold must not move it
-        const float c = column_max(mx[qt]);
-        const float m = c > m_run[qt] + slack ? c : m_run[qt];
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m);
+    for (int qt = 0; qt < 2; ++qt) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int tp = 0; tp < 2; ++tp)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) mx = fmaxf(mx, s[tp][hf][qt][v]);
+      float alpha = 1.0f;
+      if (__any(mx > m_run[qt])) {   // (otherwise every factor is one)
+        const float m = fmaxf(column_max(mx), m_run[qt]);
+        alpha = __builtin_amdgcn_exp2f(m_run[qt] - m);
         m_run[qt] = m;
-        lacc[qt] *= alpha;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) oacc[dt][qt] *= alpha;
       }
-    bf16x8 pf[2];   // [query tile]
+      float psum = 0.f;
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
-      float p[8];
+      for (int tp = 0; tp < 2; ++tp) {
+        float p[8];
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf)
+        for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) p[hf * 4 + v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[hf][qt][v], sl2, -m_run[qt]));
-      u32x4 packed = {pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7])};
-      pf[qt] = __builtin_bit_cast(bf16x8, packed);
+          for (int v = 0; v < 4; ++v) {
+            p[hf * 4 + v] = __builtin_amdgcn_exp2f(s[tp][hf][qt][v] - m_run[qt]);
+            psum += p[hf * 4 + v];
+          }
+        u32x4 packed = {pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7])};
+        pf[qt][tp] = __builtin_bit_cast(bf16x8, packed);
+      }
+      l_run[qt] = __builtin_fmaf(l_run[qt], alpha, psum);
     }
     // ---- O^T += V^T P^T
-    constexpr int at = decltype(slot_c)::value * kVStage;
 #pragma unroll
-    for (int d4 = 0; d4 < 8; d4 += 4) {
-      // (waits in the block itself: before a read through the builtin the compiler waits for every direct-to-LDS load
-      // in flight, the next step's included)
-      s16x4 t[8];
-      asm volatile(
-          "ds_read_b64_tr_b16 %0, %8 offset:%12\n ds_read_b64_tr_b16 %1, %8 offset:%13\n"
-          "ds_read_b64_tr_b16 %2, %9 offset:%12\n ds_read_b64_tr_b16 %3, %9 offset:%13\n"
-          "ds_read_b64_tr_b16 %4, %10 offset:%12\n ds_read_b64_tr_b16 %5, %10 offset:%13\n"
-          "ds_read_b64_tr_b16 %6, %11 offset:%12\n ds_read_b64_tr_b16 %7, %11 offset:%13\n"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]), "=&v"(t[6]), "=&v"(t[7])
-          : "v"(vp[d4]), "v"(vp[d4 + 1]), "v"(vp[d4 + 2]), "v"(vp[d4 + 3]), "n"(at), "n"(at + 4 * 256)
-          : "memory");
-      __builtin_amdgcn_s_setprio(1);
+    for (int tp = 0; tp < 2; ++tp) {
+      if (tp == 1 && !both) break;
 #pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(t[2 * d], t[2 * d + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+      for (int d4 = 0; d4 < 8; d4 += 4) {
+        // (waits in the block itself: before a read through the builtin the compiler waits for every direct-to-LDS load
+        // in flight, the next step's included)
+        constexpr int kAt = slot * kVStage;
+        s16x4 t[8];
+        asm volatile(
+            "ds_read_b64_tr_b16 %0, %8 offset:%12\n ds_read_b64_tr_b16 %1, %8 offset:%13\n"
+            "ds_read_b64_tr_b16 %2, %9 offset:%12\n ds_read_b64_tr_b16 %3, %9 offset:%13\n"
+            "ds_read_b64_tr_b16 %4, %10 offset:%12\n ds_read_b64_tr_b16 %5, %10 offset:%13\n"
+            "ds_read_b64_tr_b16 %6, %11 offset:%12\n ds_read_b64_tr_b16 %7, %11 offset:%13\n"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]), "=&v"(t[6]), "=&v"(t[7])
+            : "v"(vp[d4]), "v"(vp[d4 + 1]), "v"(vp[d4 + 2]), "v"(vp[d4 + 3]), "n"(kAt + tp * 8192), "n"(kAt + tp * 8192 + 4 * 256)
+            : "memory");
+        __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
-          oacc[d4 + d][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qt], oacc[d4 + d][qt], 0, 0, 0);
+        for (int d = 0; d < 4; ++d) {
+          const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(t[2 * d], t[2 * d + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+          for (int qt = 0; qt < 2; ++qt)
+            oacc[d4 + d][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qt][tp], oacc[d4 + d][qt], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_setprio(0);
       }
     }
-#pragma unroll
-    for (int qt = 0; qt < 2; ++qt) lacc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qt], lacc[qt], 0, 0, 0);
-    __builtin_amdgcn_s_setprio(0);
   };
-  // Three stages: while step s is worked on, s + 1 is landing or has landed and s + 2 is requested.
+  // Two stages: while step s is worked on, s + 1 is landing.
   auto one_step = [&](int step, auto slot_c) __attribute__((always_inline)) {
     constexpr int slot = decltype(slot_c)::value;
-    // memory returns in order: step has landed when only the four loads of step + 1 are out
-    if (step + 1 < n_steps) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    block_barrier();   // ... for every wave, and every wave is done with the stage of step - 1
-    if (step + 2 < n_steps) issue(step + 2, (slot + 2) % 3);
-    if (step <= n_whole) attend(step, slot_c);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    block_barrier();   // the step's loads have landed for every wave, and every wave is done with the stage of step - 1
+    if (step + 1 < n_steps) issue(step + 1, slot ^ 1);
+    if (step * 2 <= n_diag) attend(step, slot_c);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   };
-  for (int step = 0; step < n_steps; step += 3) {
+  for (int step = 0; step < n_steps; step += 2) {
     one_step(step, std::integral_constant<int, 0>{});
     if (step + 1 < n_steps) one_step(step + 1, std::integral_constant<int, 1>{});
-    if (step + 2 < n_steps) one_step(step + 2, std::integral_constant<int, 2>{});
   }
 
   if (!wave_valid) return;
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) {
-    const float inv = 1.0f / lacc[qt][0];   // (every row of that product holds the same sum)
+    float l = l_run[qt];
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    const float inv = 1.0f / l;
     const int qrow = wq0 + qt * 16 + r16;
     if (qrow < row_b) {
       bf16_t* o = (bf16_t*)a.O + (int64_t)qrow * a.ldo + h * kDh + g * 4;
@@ -785,7 +769,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
   if (a.T == 0 || a.S == 0 || a.n_heads == 0) return hipSuccess;
   if (a.bf16) {
     const dim3 grid(((a.T + kBQ - 1) / kBQ + a.S) * a.n_heads);
-    k_attention_bf16<<<grid, kAttnWaves * kWave, 3 * (kKStage + kVStage), st>>>(a);
+    k_attention_bf16<<<grid, kAttnWaves * kWave, 2 * (kKStage + kVStage), st>>>(a);
   } else {
     const dim3 grid(a.T, a.n_heads);
     k_attention_f32<<<grid, kWave, 0, st>>>(a);

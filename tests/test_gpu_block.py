@@ -222,6 +222,24 @@ def test_attention_rows_do_not_depend_on_later_rows(n, keep, scale, grow):
         np.testing.assert_array_equal(head, whole[:m], err_msg="rows before %d" % m)
 
 
+def test_attention_normaliser_is_summed_in_fp32():
+    """127 equal weights that all round up to bf16 by almost half a step: their sum in the denominator must be that of the
+    unrounded weights.  The outputs' own rounding is at most 2^-9 of a value and averages out over 128 columns (one part
+    in 10^4 standard deviation); a normaliser summed from rounded weights is off by more than 2e-3."""
+    dh, n = 128, 128
+    c = wl.as_bf16_values(np.linspace(0.1, 0.68, 400).astype(np.float32)).astype(np.float64)
+    w = np.exp(-c)
+    up = wl.as_bf16_values(w.astype(np.float32)) / w - 1
+    c, w, up = c[np.argmax(up)], w[np.argmax(up)], up.max()
+    assert up > 2.4e-3
+    q = np.zeros((n, dh)); q[:, 0] = 1
+    k = np.zeros((n, dh)); k[1:, 0] = -c
+    v = np.zeros((n, dh)); v[0] = 1 + np.arange(dh) / 128
+    got, _ = _run_attention(q, k, v, [n], 1, 1, dh, 1.0, "bf16")
+    ratio = got[-1] * (1 + (n - 1) * w) / v[0]
+    assert abs(ratio.mean() - 1) < 6e-4
+
+
 def test_attention_empty_batches():
     batch, _ = _plain_batch([0, 0])
     dummy = torch.zeros((1, 128), device=DEV, dtype=torch.bfloat16)

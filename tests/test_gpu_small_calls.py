@@ -98,7 +98,7 @@ def test_fp32_call_on_either_tile_size(n, m, vocab, r, R, act):
 @pytest.mark.parametrize("lens", [[1, 31, 32, 33, 64, 0, 96], [127, 128, 129], [160, 161, 255, 257, 1]])
 @pytest.mark.parametrize("scale,grow", [(128 ** -0.5, 0.0), (-(128 ** -0.5), 0.0), (0.0, 0.0), (0.1, 0.02), (0.1, -0.02)])
 def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
-    """Lengths around the 32 keys of a step, the 32 rows of a wave and the 128 of a workgroup; negative and zero
+    """Lengths around the 64 keys of a step, the 32 rows of a wave and the 128 of a workgroup; negative and zero
     scales; scores that grow along the sequence, so that the running maximum is raised again and again, or shrink, so
     that it never is.  Weights and outputs are bf16: 2e-2 as for every bf16 output here."""
     H, Hkv, dh = 4, 2, 128
