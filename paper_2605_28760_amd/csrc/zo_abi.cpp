@@ -24,13 +24,31 @@ int side_ksplit(int n) {
   return s < 1 ? 1 : s;
 }
 
-// The one-launch pass has a wave per 16 rows, 16 side columns and K range and reads X once per 16 columns; the staged
-// pass reads X once, but has a few workgroups only when the batch is small.  The line lies at 2400 waves.  Whole calls
-// on 512 output features, us, staged -> one launch: 4096 columns and 144 side columns 36 -> 24 at 38 rows, 52 -> 47 at
-// 1058 (2381 waves), 54 -> 59 at 2042 (4595); 5120 and 80: 41 -> 28 at 200, 58 -> 58 at 2042 (2553); 20480 and 80: 87 ->
-// 68 at 200, 136 -> 133 at 1058 (2645); 1024 and 48: 28 -> 22 at 1058, 43 -> 42 at 8364 (3137).
-bool side_small_call(int T, int n, int columns) {
-  return (int64_t)((T + 15) / 16) * (columns / 16) * side_ksplit(n) <= 2400;
+// The one-launch pass has a wave per item of 16 rows, 16 side columns and K range and reads X once per 16 columns; the
+// staged pass reads X once, but has a few workgroups only when the batch is small.  An item's time is its V block, which
+// it reads however few rows it has, and twice as much its rows of X when all 16 are there; the line lies at 2500 waves of
+// whole items.  With the host mirrors the items are counted as the device builds them (at least one per candidate
+// sequence, none for foreground ones); without, a sequence may add one.  Whole calls on 512 output features, us, staged ->
+// one launch, at the item counts next to the line: 4096 columns and 144 side columns, sequences of 128 rows 45 -> 39 at 60
+// items and 49 -> 47 at 80, of 16..48 46 -> 41 at 80 and 51 -> 48 at 100, of 1..4 62 -> 59 at 140 and 62 -> 64 at 200 (90
+// -> 101 at 300 of one row); 20480 and 80: 128 rows 89 -> 72 at 40 and 111 -> 113 at 60, 16..48 108 -> 105 at 60 and 110 ->
+// 114 at 80, 1..4 104 -> 94 at 100 and 108 -> 109 at 140; 5120 and 80: 128 rows 54 -> 47 at 100 and 71 -> 64 at 140, 16..48 56
+// -> 54 at 140 and 73 -> 67 at 200, 1..4 64 -> 58 at 200 and 69 -> 69 at 300; 1024 and 48: as fast at 500 items, faster below.
+// 64 rows of candidates among 6464: 74 -> 60.
+bool side_small_call(const int32_t* host_cu, const int32_t* host_seq_cand, int S, int T, int n, int columns) {
+  int64_t items = 0, rows = 0;
+  if (host_cu && host_seq_cand) {
+    for (int q = 0; q < S; ++q) {
+      if (host_seq_cand[q] < 0) continue;
+      const int len = host_cu[q + 1] - host_cu[q];
+      items += (len + 15) / 16;
+      rows += len;
+    }
+  } else {
+    items = (T + 15) / 16 + (S < T ? S : T);
+    rows = T;
+  }
+  return (items * 16 + 2 * rows) * (columns / 16) * side_ksplit(n) <= 2500 * 48;
 }
 
 // Rows per item (64, 48, 32 or 16; how rows are grouped into items does not enter any row's arithmetic).  The
@@ -146,6 +164,7 @@ zo::BatchDev to_dev(const zo_batch* b) {
 // ---- workspace plans --------------------------------------------------------------------
 struct ProbePlan {
   int RP = 0, Rp = 0, max_items = 0, item_rows = zo::kSideRows, ksplit = 1;
+  bool side_small = false;   // the side-down pass in one launch
   int SPD = 0, RpT = 0, n_tn = 0, slot_cap = 0, kt_cap = 0, m_img = 0;   // side K tiles of the bf16 GEMM
   size_t uimg_bytes = 0, pimg_bytes = 0, xs_bytes = 0;
   size_t seq_kind, seq_scale, tok_seq, n_items, items;
@@ -162,10 +181,11 @@ ProbePlan plan_probe(int T, int S, int K, int m, int n, int r, int R, zo_dtype d
   p.seq_scale = c.take((size_t)S * 4);
   p.tok_seq = c.take((size_t)T * 4);
   p.n_items = c.take(16);
-  // (the choice of the item size does not enter the layout below: a workspace query, which has no batch, and
+  // (the choice of the pass and of the item size does not enter the layout below: a workspace query, which has no batch, and
   // the call agree on every offset)
+  p.side_small = dt == ZO_BF16 && zo::side_small_call(host_cu, host_seq_cand, S, T, n, round16(r) + round16(R));
   if (dt != ZO_BF16) p.item_rows = zo::kSideRows;
-  else if (zo::side_small_call(T, n, round16(r) + round16(R))) p.item_rows = 16;
+  else if (p.side_small) p.item_rows = 16;
   else p.item_rows = zo::side_item_rows(host_cu, host_seq_cand, S, T, n, R);
   p.max_items = (T + p.item_rows - 1) / p.item_rows + S;
   // (sized for the smallest items, so that a workspace sized for a large batch also serves a smaller one)
@@ -361,7 +381,7 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
       tabs.tile_hdr = (zo::TileHdr*)(ws + plan.tile_hdr);
       tabs.tile_slots = (int32_t*)(ws + plan.tile_slots);
       tabs.kt_tile = (int32_t*)(ws + plan.kt_tile);
-      if (zo::side_small_call(T, n, plan.RP + plan.Rp)) tabs.Xs = Xs;
+      if (plan.side_small) tabs.Xs = Xs;
       ZO_HIP(zo::launch_probe_prep_bf16(bd, eps, tabs, tensor_id, m, n, r, plan.RP, plan.Rp, R > 0 ? bank->P : nullptr,
                                         R > 0 ? bank->Vb : nullptr, R > 0 ? bank->R_cap : 0, R, plan.m_img, Uimg, Vt, Pimg,
                                         Vbt, st),
@@ -373,7 +393,7 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
       sd.ksplit = plan.ksplit; sd.partial = (float*)(ws + plan.partial);
       sd.tok_seq = tabs.tok_seq; sd.seq_kind = tabs.seq_kind; sd.seq_scale = tabs.seq_scale;
       sd.tile_hdr = tabs.tile_hdr; sd.tile_slots = tabs.tile_slots; sd.kt_tile = tabs.kt_tile;
-      sd.kt_cap = plan.kt_cap; sd.SPD = plan.SPD; sd.Xs = Xs;
+      sd.kt_cap = plan.kt_cap; sd.SPD = plan.SPD; sd.Xs = Xs; sd.small = plan.side_small;
       ZO_HIP(zo::launch_side_down_bf16(sd, st), "side-down");
     }
     zo::ProbeGemmArgs g;

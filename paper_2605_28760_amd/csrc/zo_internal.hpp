@@ -124,12 +124,13 @@ struct SideDownArgs {
   const TileHdr* tile_hdr; const int32_t* tile_slots; const int32_t* kt_tile;
   int kt_cap, SPD;
   uint16_t* Xs;                     // [pool K tile][kTileN][kTileK] bf16
+  bool small;                       // the one-launch pass (side_small_call)
 };
 // K ranges of the side-down pass for an input width n: never a function of the batch, so that the
 // summation order of a row's side term does not depend on what else is in the batch.
 int side_ksplit(int n);
-// Whether a call takes the one-launch side-down pass (columns = RP + Rp).
-bool side_small_call(int T, int n, int columns);
+// Whether a call takes the one-launch side-down pass (columns = RP + Rp); no row's arithmetic depends on it.
+bool side_small_call(const int32_t* host_cu, const int32_t* host_seq_cand, int S, int T, int n, int columns);
 // Rows per side-down work item (64, 48, 32 or 16) for a batch of T rows, input width n and bank rank R; how rows
 // are grouped into items does not enter any row's arithmetic.
 int side_item_rows(const int32_t* host_cu, const int32_t* host_seq_cand, int S, int T, int n, int R);

@@ -508,7 +508,7 @@ static hipError_t launch_pass_n(int nbb, const SideDownArgs& a, int cb0, hipStre
 
 hipError_t launch_side_down_bf16(const SideDownArgs& a, hipStream_t st) {
   if (a.T == 0 || a.max_items == 0) return hipSuccess;
-  if (side_small_call(a.T, a.n, a.RP + a.Rp)) {
+  if (a.small) {
     static std::atomic<bool> configured[kMaxDevices];
     const hipError_t ec = once_per_device(configured, [] {
       return hipFuncSetAttribute((const void*)k_side_small, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 2 * kSmallStage);

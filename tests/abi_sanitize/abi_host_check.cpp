@@ -13,6 +13,7 @@
 #include "../../include/zo.h"
 
 extern int g_launches;
+extern int g_side_small;
 extern const char* g_ws_lo;
 extern const char* g_ws_hi;
 
@@ -202,6 +203,33 @@ int main() {
       }
     }
     EXPECT(zo_probe_linear_workspace_bytes(-1, 1, 1, 8, 64, 1, 0, ZO_BF16) == 0 ? 0 : 1, 0);
+  }
+  // ---- which side-down pass a batch takes: a matter of its items, not of its rows -------------------
+  {
+    struct Case { int len, n_cand, n_fg, mirrors, n, r, R, want; } cases[] = {
+        {16, 2, 0, 1, 4096, 16, 128, 1},    {16, 60, 0, 1, 4096, 16, 128, 1},   {16, 80, 0, 1, 4096, 16, 128, 0},
+        {1, 90, 0, 1, 4096, 16, 128, 1},    {1, 300, 0, 1, 4096, 16, 128, 0},   {1, 1000, 0, 1, 4096, 16, 128, 0},
+        {4, 100, 0, 1, 4096, 16, 128, 1},   {4, 200, 0, 1, 4096, 16, 128, 0},   {2, 140, 0, 1, 20480, 8, 64, 1},   {2, 170, 0, 1, 20480, 8, 64, 0},
+        {128, 8, 0, 1, 4096, 16, 128, 1},   {128, 16, 0, 1, 4096, 16, 128, 0},  {16, 4, 2000, 1, 4096, 16, 128, 1},
+        {300, 2, 60, 1, 4096, 16, 128, 1},  {0, 500, 0, 1, 4096, 16, 128, 1},   {1, 300, 0, 0, 4096, 16, 128, 0},
+        {48, 2, 0, 0, 4096, 16, 128, 1},    {16, 4, 2000, 0, 4096, 16, 128, 0}};
+    for (const Case& c : cases) {
+      const int S = c.n_cand + c.n_fg, T = c.len * S + 1;   // (one foreground row at the end: T > 0)
+      std::vector<int32_t> cu(S + 2), sc(S + 1);
+      for (int s = 0; s <= S; ++s) cu[s] = c.len * s;
+      cu[S + 1] = T;
+      for (int s = 0; s <= S; ++s) sc[s] = s < c.n_cand ? s % 2 : -1;
+      HostBatch h = make_batch(T, cu, sc, {0, 0}, 1);
+      if (c.mirrors) mirror(h);
+      const size_t wsb = zo_probe_linear_workspace_bytes(T, S + 1, 1, 512, c.n, c.r, c.R, ZO_BF16);
+      g_ws_lo = (const char*)FAKE; g_ws_hi = g_ws_lo + wsb;
+      zo_bank bank = {c.R, c.R, (float*)FAKE, (float*)FAKE};
+      g_side_small = -1;
+      EXPECT(zo_probe_linear(&h.b, FAKE, c.n, FAKE, c.n, nullptr, 512, c.n, ZO_BF16, c.r, 1e-3f, 4, &bank, 0, FAKE, 512, ZO_BF16,
+                             FAKE, wsb, nullptr), ZO_OK);
+      EXPECT(g_side_small, c.want);
+      g_ws_lo = g_ws_hi = nullptr;
+    }
   }
   char msg[64];
   zo_last_error(msg, sizeof msg);   // short buffer: truncation path

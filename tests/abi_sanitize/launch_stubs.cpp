@@ -9,6 +9,7 @@
 #include "zo_internal.hpp"
 
 int g_launches = 0;
+int g_side_small = -1;   // pass of the last side-down launch: 1 one launch, 0 staged
 const char* g_ws_lo = nullptr;
 const char* g_ws_hi = nullptr;
 
@@ -27,6 +28,8 @@ const char* hipGetErrorString(hipError_t) { return "stub"; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 }
+
+static int g_prep_small = -1;
 
 namespace zo {
 
@@ -75,13 +78,17 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   inside(Pimg, (size_t)t.RpT * m_img * 128, "Pimg");
   inside(Vt, (size_t)b.K * RP * n * 2, "Vt");
   inside(Vbt, (size_t)Rp * n * 2, "Vbt");
+  g_prep_small = t.Xs ? 1 : 0;
   return hipSuccess;
 }
 
 hipError_t launch_side_down_bf16(const SideDownArgs& a, hipStream_t) {
   ++g_launches;
+  if ((a.small ? 1 : 0) != g_prep_small) abort();   // the operand layout that the preparation was told to write
   inside(a.partial, (size_t)a.ksplit * a.T * (a.RP + a.Rp) * 4, "partial");
   inside(a.Xs, (size_t)a.kt_cap * kTileN * kTileK * 2, "Xs");
+  g_side_small = a.small ? 1 : 0;
+  if (a.small && a.item_rows != 16) abort();
   if (a.ksplit < 1 || a.ksplit > 8 || (a.item_rows != 16 && a.item_rows != 32 && a.item_rows != 48 && a.item_rows != 64)) abort();
   return hipSuccess;
 }

@@ -117,8 +117,7 @@ def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
     assert_close(to_np(out), ob.attention(q, k, v, cu, H, Hkv, dh, scale, "bf16"), 2e-2, "attention")
 
 
-# around the line between the one-launch side-down pass and the staged one (2400 waves of 16 rows, 16 columns and one K
-# range), at widths whose ranges end inside and at the end of a batch of 256 columns, with 1, 2, 4 and 8 ranges
+# on both sides of the line between the one-launch side-down pass and the staged one, at widths whose ranges end inside and at the end of a batch of 256 columns, with 1, 2, 4 and 8 ranges
 @pytest.mark.parametrize("n,r,R", [(64, 1, 0), (448, 48, 16), (1088, 16, 40), (2560, 8, 136), (5184, 70, 0), (20480, 4, 32)])
 def test_side_term_on_either_pass(n, r, R):
     lens = [1, 17, 0, 40, 16, 5] + [200] * (8 if n > 10000 else 200 if n == 64 else 110)
@@ -173,3 +172,18 @@ def test_tables_of_many_sequences_and_directions(S, K):
     w.dir_seed = np.arange(K, dtype=np.uint64) + np.uint64(5)
     y = DeviceWorkload(w, DEV, out_dtype="f32").probe_linear(0)
     assert_close(to_np(y), oracle_layer(w, 0, w.layers[0].X, out_dtype="f32"), 2e-2, "Y")
+
+
+@pytest.mark.parametrize("n,R", [(64, 0), (2560, 40)])
+def test_side_term_of_a_batch_changed_on_the_device(n, R):
+    """The host's copies of the tables decide which side-down pass a call takes, never its result: a handle whose device tables were changed (one candidate sequence becomes 40) gives what a new handle gives."""
+    lens = [5, 40, 1, 16, 17] * 8
+    few = _layer(n, lens, [0] + [-1] * 39, 64, n, 20, R, 0, False)
+    many = _layer(n, lens, [i % 7 for i in range(40)], 64, n, 20, R, 0, False)
+    g = DeviceWorkload(few, DEV, out_dtype="f32")
+    g.batch.seq_cand.copy_(torch.from_numpy(many.seq_cand))
+    y = g.probe_linear(0)
+    want = DeviceWorkload(many, DEV, out_dtype="f32").probe_linear(0)
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+    assert_close(to_np(y), oracle_layer(many, 0, many.layers[0].X, out_dtype="f32"), 2e-2, "Y")
