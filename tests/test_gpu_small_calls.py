@@ -187,3 +187,14 @@ def test_side_term_of_a_batch_changed_on_the_device(n, R):
     torch.cuda.synchronize()
     assert torch.equal(y, want)
     assert_close(to_np(y), oracle_layer(many, 0, many.layers[0].X, out_dtype="f32"), 2e-2, "Y")
+
+
+@pytest.mark.parametrize("n,r,K,lens", [(448, 512, 24, [1] * 48), (128, 40, 80, [3, 0, 5] * 60), (64, 100, 3, [250, 12, 16, 1])])
+def test_side_slots_of_high_ranks_and_many_directions(n, r, K, lens):
+    """Slot lists of several hundred entries, more than 64 directions in a token tile, and items that lie in two tiles."""
+    w = _layer(n + r, lens, [i % (2 * K) for i in range(len(lens))], 64, n, r, 16, 0, False)
+    w.cand_dir = np.repeat(np.arange(K, dtype=np.int32), 2)
+    w.cand_sign = np.tile(np.array([1, -1], np.float32), K)
+    w.dir_seed = np.arange(K, dtype=np.uint64) + np.uint64(5)
+    y = DeviceWorkload(w, DEV, out_dtype="f32").probe_linear(0)
+    assert_close(to_np(y), oracle_layer(w, 0, w.layers[0].X, out_dtype="f32"), 2e-2, "Y")
