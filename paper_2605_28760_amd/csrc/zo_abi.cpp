@@ -34,8 +34,10 @@ int side_ksplit(int n) {
 // -> 101 at 300 of one row); 20480 and 80: 128 rows 89 -> 72 at 40 and 111 -> 113 at 60, 16..48 108 -> 105 at 60 and 110 ->
 // 114 at 80, 1..4 104 -> 94 at 100 and 108 -> 109 at 140; 5120 and 80: 128 rows 54 -> 47 at 100 and 71 -> 64 at 140, 16..48 56
 // -> 54 at 140 and 73 -> 67 at 200, 1..4 64 -> 58 at 200 and 69 -> 69 at 300; 1024 and 48: as fast at 500 items, faster below.
-// 64 rows of candidates among 6464: 74 -> 60.
+// 64 rows of candidates among 6464: 72 -> 58.  (The launch is sized for items of every row and sequence; beyond 32768
+// workgroups those that find none cost what the pass gains: 4 candidates among 4000 foreground sequences 270 -> 275.)
 bool side_small_call(const int32_t* host_cu, const int32_t* host_seq_cand, int S, int T, int n, int columns) {
+  if (((int64_t)(T + 15) / 16 + S) * (columns / 16) > 32768) return false;
   int64_t items = 0, rows = 0;
   if (host_cu && host_seq_cand) {
     for (int q = 0; q < S; ++q) {
@@ -361,7 +363,7 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
   tabs.item_rows = plan.item_rows;
   tabs.tile_hdr = nullptr; tabs.tile_slots = nullptr; tabs.kt_tile = nullptr;
   tabs.n_tn = plan.n_tn; tabs.slot_cap = plan.slot_cap; tabs.kt_cap = plan.kt_cap; tabs.SPD = plan.SPD; tabs.RpT = plan.RpT;
-  tabs.Xs = nullptr;
+  tabs.frag_major = plan.side_small;
   // a batch without candidates (or probes and bank both absent) is a plain GEMM
   const bool has_side = batch->n_cands > 0;
 
@@ -381,7 +383,6 @@ int32_t zo_probe_linear(const zo_batch* batch, const void* X, int64_t ldx, const
       tabs.tile_hdr = (zo::TileHdr*)(ws + plan.tile_hdr);
       tabs.tile_slots = (int32_t*)(ws + plan.tile_slots);
       tabs.kt_tile = (int32_t*)(ws + plan.kt_tile);
-      if (plan.side_small) tabs.Xs = Xs;
       ZO_HIP(zo::launch_probe_prep_bf16(bd, eps, tabs, tensor_id, m, n, r, plan.RP, plan.Rp, R > 0 ? bank->P : nullptr,
                                         R > 0 ? bank->Vb : nullptr, R > 0 ? bank->R_cap : 0, R, plan.m_img, Uimg, Vt, Pimg,
                                         Vbt, st),

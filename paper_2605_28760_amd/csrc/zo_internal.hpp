@@ -69,8 +69,7 @@ struct SeqTables {
   int32_t n_tn, slot_cap, kt_cap;
   int32_t SPD;         // 32-column blocks per direction
   int32_t RpT;         // bank K tiles of a tile with candidates
-  uint16_t* Xs;        // non-null for the one-launch side-down pass: the preparation clears the token-side images and
-                       // writes Vt and Vbt in the order of the matrix instruction's operands
+  bool frag_major;     // Vt and Vbt in the order of the matrix instruction's operands (for the one-launch side-down pass)
 };
 
 // number of compute units of the current device (256 on MI355X; cached per device)
@@ -107,7 +106,7 @@ hipError_t launch_probe_prep_f32(const BatchDev& b, float eps, const SeqTables& 
 // bf16 operand images.  For the GEMM's side K tiles: Uimg [K * SPD][m_img][32] (32-column blocks of U,
 // 64-byte rows), Pimg [RpT][m_img][64] (64-column blocks of P, 128-byte rows); rows >= m and columns
 // beyond the rank are zero.  For the side-down pass: Vt [K][RP][n] (V transposed), Vbt [Rp][n] (or
-// both in operand order, see SeqTables::Xs).
+// both in operand order, see SeqTables::frag_major).
 
 // ---- zo_side.hip --------------------------------------------------------------
 struct SideDownArgs {

@@ -389,14 +389,13 @@ hipError_t launch_probe_prep_f32(const BatchDev& b, float eps, const SeqTables& 
 
 // ---- everything a bf16 probe linear prepares before its side-down pass, in one launch ------
 // Block roles, in order: [sequence tables: 1] [token -> sequence map] [U image] [V^T image]
-// [P image] [token-side images cleared] [Vb^T image: 32x32
-// transposing tiles, or 16-byte pieces in operand order].  The pieces do not depend on one another.
+// [P image] [Vb^T image: 32x32 transposing tiles, or 16-byte pieces in operand order].  The pieces do not depend on one another.
 struct ProbePrepArgs {
   BatchDev b; float eps; SeqTables tabs;
   uint32_t tensor_id; int m, n, r, RP, Rp, m_img;
   const float* P; const float* Vb; int R_cap, R_used;
   bf16_t* Uimg; bf16_t* Vt; bf16_t* Pimg; bf16_t* Vbt;
-  int nb_tok, nb_U, nb_Vt, nb_P, nb_Xs, nb_Vbt, vbt_tiles_n;
+  int nb_tok, nb_U, nb_Vt, nb_P, nb_Vbt, vbt_tiles_n;
 };
 
 __global__ __launch_bounds__(1024) void k_probe_prep(ProbePrepArgs a) {
@@ -407,16 +406,11 @@ __global__ __launch_bounds__(1024) void k_probe_prep(ProbePrepArgs a) {
   blk -= a.nb_tok;
   if (blk < a.nb_U) { image_U_at(a.b, (int64_t)blk * 1024 + threadIdx.x, a.tensor_id & ~1u, a.m, a.m_img, a.r, a.tabs.SPD, a.Uimg); return; }
   blk -= a.nb_U;
-  if (blk < a.nb_Vt) { image_Vt_at(a.b, (int64_t)blk * 1024 + threadIdx.x, a.tensor_id | 1u, a.n, a.r, a.RP, a.tabs.Xs != nullptr, a.Vt); return; }
+  if (blk < a.nb_Vt) { image_Vt_at(a.b, (int64_t)blk * 1024 + threadIdx.x, a.tensor_id | 1u, a.n, a.r, a.RP, a.tabs.frag_major, a.Vt); return; }
   blk -= a.nb_Vt;
   if (blk < a.nb_P) { image_P_at((int64_t)blk * 1024 + threadIdx.x, a.P, a.R_cap, a.R_used, a.tabs.RpT, a.m, a.m_img, a.Pimg); return; }
   blk -= a.nb_P;
-  if (blk < a.nb_Xs) {   // 1024 threads x 16 bytes: half a pool K tile
-    reinterpret_cast<u32x4*>(a.tabs.Xs)[(int64_t)blk * 1024 + threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
-    return;
-  }
-  blk -= a.nb_Xs;
-  if (a.tabs.Xs) { image_Vb_frag_at((int64_t)blk * 1024 + threadIdx.x, a.Vb, a.R_cap, a.R_used, a.Rp, a.n, a.Vbt); return; }
+  if (a.tabs.frag_major) { image_Vb_frag_at((int64_t)blk * 1024 + threadIdx.x, a.Vb, a.R_cap, a.R_used, a.Rp, a.n, a.Vbt); return; }
   // Vbt[j][i] = Vb[i][j], one 32x32 tile per block, coalesced on both sides
   __shared__ float tile[32][33];
   const int i0 = (blk % a.vbt_tiles_n) * 32, j0 = (blk / a.vbt_tiles_n) * 32;
@@ -445,11 +439,9 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   a.nb_U = blocks((int64_t)b.K * m_img * (tabs.SPD * 4));
   a.nb_Vt = blocks((int64_t)b.K * (n / 2) * (RP / 4));
   a.nb_P = Rp > 0 ? blocks((int64_t)m_img * tabs.RpT * 8) : 0;
-  static_assert(kTileN * kTileK * 2 == 2 * 1024 * 16, "two blocks clear a pool K tile");
-  a.nb_Xs = tabs.Xs ? tabs.kt_cap * 2 : 0;
   a.vbt_tiles_n = (n + 31) / 32;
-  a.nb_Vbt = Rp == 0 ? 0 : tabs.Xs ? blocks((int64_t)(n / 8) * Rp) : a.vbt_tiles_n * ((Rp + 31) / 32);
-  const int64_t total = 1 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Xs + a.nb_Vbt;
+  a.nb_Vbt = Rp == 0 ? 0 : tabs.frag_major ? blocks((int64_t)(n / 8) * Rp) : a.vbt_tiles_n * ((Rp + 31) / 32);
+  const int64_t total = 1 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Vbt;
   hipLaunchKernelGGL(k_probe_prep, dim3((unsigned)total), dim3(1024), 0, st, a);
   return hipGetLastError();
 }

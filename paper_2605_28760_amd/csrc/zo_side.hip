@@ -318,13 +318,36 @@ __global__ __launch_bounds__(256) void k_side_down_dirblocks(SideDownArgs a, int
     }
 }
 
+// The eight columns 8c .. 8c+7 of a row in pool K tile p, which belongs to token tile tn: the first of the columns of
+// [V | Vb] behind them, with the row's scale of them, or -1 where the image is zero (another direction's slot, columns
+// beyond the ranks, foreground rows, rows past the end of the batch).
+__device__ __forceinline__ int image_columns(const SideDownArgs& a, int p, int tn, int row, int c, float& scale) {
+  scale = 1.0f;
+  if (row >= a.T) return -1;
+  const TileHdr h = a.tile_hdr[tn];
+  const int j = p - h.kt0, n_dir_kt = (h.n_slots + 1) >> 1;
+  const int s = a.tok_seq[row];
+  const int kind = a.seq_kind[s];
+  if (j < n_dir_kt) {
+    const int slot = 2 * j + (c >> 2);
+    if (kind < 0 || slot >= h.n_slots) return -1;
+    const int e = a.tile_slots[h.slot0 + slot];
+    const int col = (e % a.SPD) * 32 + (c & 3) * 8;
+    if (e / a.SPD != kind || col >= a.RP) return -1;
+    scale = a.seq_scale[s];
+    return col;
+  }
+  const int bcol = (j - n_dir_kt) * 64 + c * 8;
+  return kind >= kKindCentre && bcol < a.Rp ? a.RP + bcol : -1;
+}
+
 // The whole pass in one launch for small calls (side_small_call): one workgroup per (item of 16 rows, 16 columns of
 // [V | Vb]), one wave per K range.  Such a call has too few items to fill the chip one wave per (item, range): 6
 // items of a 96-row batch are 4 workgroups, each bound by the round trips of its 16 dependent steps (16 us at 4096
 // columns, then 5 us for the finishing kernel).  Here the column blocks go to workgroups of their own (X is re-read
 // from L2 once per block), a wave has the next 256 columns of its range in flight while it multiplies 256, and the
 // ranges are summed through LDS by the workgroup itself, which writes its 16 columns of the token-side images;
-// everything else in the images is cleared by the preparation launch.  Loads run along rows (row pitches are often
+// the rest of a K tile in use is cleared by the launch's workgroups without an item.  Loads run along rows (row pitches are often
 // multiples of 8 KiB, which puts the same columns of all rows on the same memory channel): X comes two rows of 512
 // bytes per load, through the wave's own two stages in LDS, and V and Vb are stored in the order of the matrix
 // instruction's operands (frag_major), 1 KiB per load.
@@ -337,7 +360,20 @@ __global__ __launch_bounds__(512, 1) void k_side_small(SideDownArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int n_blocks = (a.RP + a.Rp) / 16, dir_blocks = a.RP / 16;
   const int item = blockIdx.x / n_blocks, cb = blockIdx.x - item * n_blocks;
-  if (item >= a.n_items[0]) return;
+  const int n_work = a.n_items[0] * n_blocks;
+  if ((int)blockIdx.x >= n_work) {
+    // workgroups without an item (the grid is a bound) clear the K tiles, a quarter at a time, where no item writes
+    for (int piece = blockIdx.x - n_work; piece < a.n_items[1] * 4; piece += gridDim.x - n_work) {
+      const int p = piece >> 2, tn = a.kt_tile[p];
+      for (int e = threadIdx.x; e < kTileN / 4 * 8; e += blockDim.x) {
+        const int rr = (piece & 3) * (kTileN / 4) + (e >> 3), c = e & 7;
+        float scale;
+        if (image_columns(a, p, tn, tn * kTileN + rr, c, scale) < 0)
+          *reinterpret_cast<u32x4*>(a.Xs + ((int64_t)p * kTileN + rr) * kTileK + c * 8) = u32x4{0u, 0u, 0u, 0u};
+      }
+    }
+    return;
+  }
   SideItem it = a.items[item];
   it.row0 = __builtin_amdgcn_readfirstlane(it.row0);
   it.nrows = __builtin_amdgcn_readfirstlane(it.nrows);
@@ -441,43 +477,21 @@ __global__ __launch_bounds__(256) void k_side_finish(SideDownArgs a) {
   const int p = blockIdx.x >> 3;
   if (p >= a.n_items[1]) return;
   const int tn = a.kt_tile[p];
-  const TileHdr h = a.tile_hdr[tn];
-  const int j = p - h.kt0;
   const int rr = (blockIdx.x & 7) * 32 + (threadIdx.x >> 3), c = threadIdx.x & 7;
   const int row = tn * kTileN + rr;
   const int NC = a.RP + a.Rp;
-  const int n_dir_kt = (h.n_slots + 1) >> 1;
   float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (row < a.T) {
-    const int s = a.tok_seq[row];
-    const int kind = a.seq_kind[s];
-    int col = -1, ncol = 0;   // first partial column behind this thread's 8 values, how many of them exist
-    float scale = 1.0f;
-    if (j < n_dir_kt) {
-      const int slot = 2 * j + (c >> 2);
-      if (kind >= 0 && slot < h.n_slots) {
-        const int e = a.tile_slots[h.slot0 + slot];
-        if (e / a.SPD == kind) {
-          col = (e % a.SPD) * 32 + (c & 3) * 8;
-          ncol = min(8, a.RP - col);
-          scale = a.seq_scale[s];
-        }
-      }
-    } else if (kind >= kKindCentre) {
-      const int bcol = (j - n_dir_kt) * 64 + c * 8;
-      col = a.RP + bcol;
-      ncol = min(8, a.Rp - bcol);
+  float scale;
+  const int col = image_columns(a, p, tn, row, c, scale);
+  if (col >= 0) {
+    for (int sp = 0; sp < a.ksplit; ++sp) {
+      const float4* src = reinterpret_cast<const float4*>(a.partial + ((int64_t)sp * a.T + row) * NC + col);
+      const float4 u = src[0], w = src[1];   // RP and Rp are multiples of 16: all 8 exist
+      y[0] += u.x; y[1] += u.y; y[2] += u.z; y[3] += u.w;
+      y[4] += w.x; y[5] += w.y; y[6] += w.z; y[7] += w.w;
     }
-    if (ncol > 0) {
-      for (int sp = 0; sp < a.ksplit; ++sp) {
-        const float4* src = reinterpret_cast<const float4*>(a.partial + ((int64_t)sp * a.T + row) * NC + col);
-        const float4 u = src[0], w = src[1];   // RP and Rp are multiples of 16: all 8 exist
-        y[0] += u.x; y[1] += u.y; y[2] += u.z; y[3] += u.w;
-        y[4] += w.x; y[5] += w.y; y[6] += w.z; y[7] += w.w;
-      }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] *= scale;
-    }
+    for (int e = 0; e < 8; ++e) y[e] *= scale;
   }
   u32x4 out = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7])};
   *reinterpret_cast<u32x4*>(a.Xs + ((int64_t)p * kTileN + rr) * kTileK + c * 8) = out;
@@ -529,7 +543,9 @@ hipError_t launch_side_down_bf16(const SideDownArgs& a, hipStream_t st) {
       return hipFuncSetAttribute((const void*)k_side_small, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 2 * kSmallStage);
     });
     if (ec != hipSuccess) return ec;
-    hipLaunchKernelGGL(k_side_small, dim3((unsigned)a.max_items * (unsigned)((a.RP + a.Rp) / 16)), dim3(a.ksplit * 64),
+    // a workgroup per item and 16 columns, and up to 128 more: with fewer the clearing would wait for one of those to end
+    const unsigned extra = a.kt_cap * 4 < 128 ? a.kt_cap * 4 : 128;
+    hipLaunchKernelGGL(k_side_small, dim3((unsigned)a.max_items * (unsigned)((a.RP + a.Rp) / 16) + extra), dim3(a.ksplit * 64),
                        a.ksplit * 2 * kSmallStage, st, a);
     return hipGetLastError();
   }

@@ -210,9 +210,9 @@ int main() {
         {16, 2, 0, 1, 4096, 16, 128, 1},    {16, 60, 0, 1, 4096, 16, 128, 1},   {16, 80, 0, 1, 4096, 16, 128, 0},
         {1, 90, 0, 1, 4096, 16, 128, 1},    {1, 300, 0, 1, 4096, 16, 128, 0},   {1, 1000, 0, 1, 4096, 16, 128, 0},
         {4, 100, 0, 1, 4096, 16, 128, 1},   {4, 200, 0, 1, 4096, 16, 128, 0},   {2, 140, 0, 1, 20480, 8, 64, 1},   {2, 170, 0, 1, 20480, 8, 64, 0},
-        {128, 8, 0, 1, 4096, 16, 128, 1},   {128, 16, 0, 1, 4096, 16, 128, 0},  {16, 4, 2000, 1, 4096, 16, 128, 1},
+        {128, 8, 0, 1, 4096, 16, 128, 1},   {128, 16, 0, 1, 4096, 16, 128, 0},  {16, 4, 1000, 1, 4096, 16, 128, 1},
         {300, 2, 60, 1, 4096, 16, 128, 1},  {0, 500, 0, 1, 4096, 16, 128, 1},   {1, 300, 0, 0, 4096, 16, 128, 0},
-        {48, 2, 0, 0, 4096, 16, 128, 1},    {16, 4, 2000, 0, 4096, 16, 128, 0}};
+        {16, 4, 4000, 1, 4096, 16, 128, 0}, {48, 2, 0, 0, 4096, 16, 128, 1},    {16, 4, 2000, 0, 4096, 16, 128, 0}};
     for (const Case& c : cases) {
       const int S = c.n_cand + c.n_fg, T = c.len * S + 1;   // (one foreground row at the end: T > 0)
       std::vector<int32_t> cu(S + 2), sc(S + 1);

@@ -78,7 +78,7 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   inside(Pimg, (size_t)t.RpT * m_img * 128, "Pimg");
   inside(Vt, (size_t)b.K * RP * n * 2, "Vt");
   inside(Vbt, (size_t)Rp * n * 2, "Vbt");
-  g_prep_small = t.Xs ? 1 : 0;
+  g_prep_small = t.frag_major ? 1 : 0;
   return hipSuccess;
 }
 

@@ -198,3 +198,25 @@ def test_side_slots_of_high_ranks_and_many_directions(n, r, K, lens):
     w.dir_seed = np.arange(K, dtype=np.uint64) + np.uint64(5)
     y = DeviceWorkload(w, DEV, out_dtype="f32").probe_linear(0)
     assert_close(to_np(y), oracle_layer(w, 0, w.layers[0].X, out_dtype="f32"), 2e-2, "Y")
+
+
+@pytest.mark.parametrize("n,r,R,lens,K", [(64, 4, 0, [4] * 400, 64), (448, 20, 72, [5, 0, 61, 190, 40], 2), (64, 40, 9, [1] * 90, 30),
+                                          (5184, 16, 16, [255, 2, 300, 17], 2)])
+def test_side_images_are_cleared_where_they_are_used(n, r, R, lens, K):
+    """A workspace full of NaN changes no result (every K tile in use is written whole), and the K tiles that the batch could
+    have needed but does not use are left alone: with 400 sequences sorted by 64 directions, 42 of 207 are in use."""
+    S = len(lens)
+    w = _layer(n + r, lens, [i * 2 * K // S if i % 5 else -1 for i in range(S)], 64, n, r, R, 0, False)
+    w.cand_dir = np.repeat(np.arange(K, dtype=np.int32), 2)
+    w.cand_sign = np.tile(np.array([1, -1], np.float32), K)
+    w.dir_seed = np.arange(K, dtype=np.uint64) + np.uint64(5)
+    g = DeviceWorkload(w, DEV, out_dtype="f32")
+    g.ws.zero_()
+    want = g.probe_linear(0).clone()
+    g.ws.fill_(255)
+    got = g.probe_linear(0)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert_close(to_np(got), oracle_layer(w, 0, w.layers[0].X, out_dtype="f32"), 2e-2, "Y")
+    if S == 400:
+        assert int((g.ws == 255).sum()) > 160 * 256 * 64 * 2
