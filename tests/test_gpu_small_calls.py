@@ -32,8 +32,8 @@ def _layer(seed, lens, seq_cand, m, n, r, R, act, bias):
                        np.arange(3, dtype=np.uint64) + np.uint64(77 + seed), [layer], False)
 
 
-# (weight rows, row count of the small call): each pair takes another tile, from 32x32 to 128x128, at the edges of
-# the tile and of the weight rows; the full batch takes the 256x256 kernel
+# (weight rows, row count of the small call): most of the tiles from 32x32 to 128x128, at the edges of the tile and of the
+# weight rows, few K stages; the full batch takes the 256x256 kernel
 @pytest.mark.parametrize("m,rows,full", [(520, 1, 16500), (520, 33, 16500), (512, 500, 16500), (504, 1000, 16500),
                                          (16384, 20, 700), (520, 1999, 16500), (512, 4000, 16500), (32768, 31, 400),
                                          (512, 8001, 16500)])
@@ -63,6 +63,32 @@ def test_small_call_has_the_bits_of_a_large_one(m, rows, full, n, r, R, act, bia
     b = small.probe_linear(0)
     torch.cuda.synchronize()
     assert sub.T == rows and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,r,R,act,bias,out", [(2112, 33, 72, 1, True, "bf16"), (1088, 16, 0, 0, False, "f32"),
+                                                (2368, 8, 130, 2, False, "bf16")])
+def test_every_tile_has_the_bits_of_the_large_one(n, r, R, act, bias, out):
+    """Each of the seven tiles, on widths that take every ring of stages round at least twice and end inside a stage of 256
+    columns.  The row counts hold for 256 compute units: which tile each takes is asserted."""
+    m, rows = 4112, [31, 64, 95, 161, 300, 447, 890]
+    tile_of = zb.lib()["_ZN2zo15small_gemm_tileEii"]   # zo::small_gemm_tile(rows, weight rows)
+    assert [tile_of(x, m) for x in rows] == list(range(7)) and tile_of(sum(rows), m) == -1
+    lens, group = [], []
+    for i, x in enumerate(rows):
+        a = min(x // 2, 200)
+        lens += [a, 0, x - a - 7, 7]
+        group += [i] * 4
+    w = _layer(n, lens, [i % 8 - 1 for i in range(len(lens))], m, n, r, R, act, bias)
+    y = DeviceWorkload(w, DEV, out_dtype=out).probe_linear(0)
+    for i, x in enumerate(rows):
+        sub = wl.subset_sequences(w, np.flatnonzero(np.array(group) == i)[::-1].copy())
+        got = DeviceWorkload(sub, DEV, out_dtype=out).probe_linear(0)
+        torch.cuda.synchronize()
+        assert sub.T == x and torch.equal(y[torch.from_numpy(np.asarray(sub.meta["rows"])).to(DEV)], got), "tile %d" % i
+    some = np.r_[0:40, w.T - 40:w.T]
+    want = oracle_layer(w, 0, w.layers[0].X, rows=some, out_dtype=out)
+    # (a gated output is the product of two sums, each within 2e-2: d(ab)/ab = da/a + db/b)
+    assert_close(to_np(y)[some], want, 4e-2 if act == 2 else 2e-2, "Y")
 
 
 # widths with and without whole groups of four columns, K slabs that end early, tiles of 32 and of 64 (the second row
@@ -120,7 +146,7 @@ def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
 # on both sides of the line between the one-launch side-down pass and the staged one, at widths whose ranges end inside and at the end of a batch of 256 columns, with 1, 2, 4 and 8 ranges
 @pytest.mark.parametrize("n,r,R", [(64, 1, 0), (448, 48, 16), (1088, 16, 40), (2560, 8, 136), (5184, 70, 0), (20480, 4, 32)])
 def test_side_term_on_either_pass(n, r, R):
-    lens = [1, 17, 0, 40, 16, 5] + [200] * (8 if n > 10000 else 200 if n == 64 else 110)
+    lens = [1, 17, 0, 40, 16, 5] + [200] * (12 if n > 10000 else 260 if n == 64 else 110)
     w = _layer(n, lens, [i % 8 - 1 for i in range(len(lens))], 64, n, r, R, 0, False)
     big = DeviceWorkload(w, DEV, out_dtype="f32")
     y = big.probe_linear(0)
@@ -132,11 +158,13 @@ def test_side_term_on_either_pass(n, r, R):
     assert torch.equal(y[torch.from_numpy(np.asarray(sub.meta["rows"])).to(DEV)], b)
 
 
-@pytest.mark.parametrize("vocab,d", [(300, 64), (257, 192), (70000, 128)])
+@pytest.mark.parametrize("vocab,d,pitch", [(300, 64, 64), (257, 192, 192), (70000, 128, 128), (600, 256, 256), (513, 320, 328),
+                                           (257, 1024, 1024), (66000, 448, 2048)])
 @pytest.mark.parametrize("scored", [1, 15, 127, 128, 129])
-def test_few_scored_tokens_have_the_bits_of_a_full_call(vocab, d, scored):
-    """Up to 128 scored tokens take a narrow token tile: one to five K tiles, vocabularies that end one row into a
-    tile, inside a wave's rows and past one round of workgroups."""
+def test_few_scored_tokens_have_the_bits_of_a_full_call(vocab, d, pitch, scored):
+    """Up to 128 scored tokens take a narrow token tile: 1 to 16 K tiles (its ring of three stages goes round up to
+    five times), vocabularies that end one row into a tile, inside a wave's rows and past one round of workgroups; the last
+    head spans more than 256 MB and is read by the streaming variant."""
     rng = np.random.default_rng(vocab + scored)
     T = 600
     cu = np.array([0, 100, 100, 350, T], np.int32)
@@ -146,6 +174,10 @@ def test_few_scored_tokens_have_the_bits_of_a_full_call(vocab, d, scored):
                     wl.as_bf16_values((rng.standard_normal((vocab, d)) / np.sqrt(d)).astype(np.float32)),
                     rng.integers(0, vocab, T).astype(np.int32), 0)
     g = DeviceWorkload(w, DEV)
+    if pitch != d:
+        wide = torch.zeros((vocab, pitch), device=DEV, dtype=torch.bfloat16)
+        wide[:, :d] = g.head
+        g.head = wide[:, :d]
     g.score(H=g.X)
     full = g.tok_nll.clone()
     keep = torch.from_numpy(np.sort(rng.choice(T, scored, replace=False))).to(DEV)
