@@ -261,11 +261,13 @@ constexpr int kVStage = kBKV * kDh * 2;   // 16 KiB: keys x head dim, 256-byte r
 // rows, so the same chunk of any two rows lies on the same banks).
 // Keys are read 16 rows at a time, {8*(i/4) + i%4 : i < 16} plus a multiple of 4 and of 32: sixteen different keys.
 __device__ __forceinline__ int swz_k(int row) { return (row & 3) | (((row >> 3) & 3) << 2); }
-// Values are read transposed, 32 bytes (two chunks) of each of eight rows at a time, {0..3, 8..11} plus a multiple
-// of 4 and of 16: eight different pairs of chunks.
-__device__ __forceinline__ int swz_v(int row) { return ((row & 3) | (((row >> 3) & 1) << 2)) << 1; }
+// Values are read transposed, 8 bytes of each of four neighbouring chunks (the lower half of the even ones, the upper of
+// the odd ones, or the other way round) of eight rows at a time, {0..3, 8..11} plus a multiple of 4 and of 16: with bit 1 of
+// the key zero no two of the 32 pieces share a bank.
+__device__ __forceinline__ int swz_v(int row) { return (row & 1) | (((row >> 1) & 1) << 2) | (((row >> 3) & 1) << 3); }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) const char lds_cchar;
 
@@ -312,25 +314,29 @@ __device__ __forceinline__ bool find_query_block(const int32_t* cu, int S, int w
 // Keys and values go global->LDS directly (the swizzle is applied on the source address), 64 keys per
 // step, two stages: the loads of step j+1 are issued when step j starts.  Values are transposed by the
 // LDS read itself (ds_read_b64_tr_b16: the 16 lanes of a group name four rows of 16 columns, and lane j
-// receives column j).  Rows past the end of the sequence repeat its last row and are always masked by the
+// receives column j); which columns a tile holds is chosen so that over a pair of tiles a lane ends up with
+// eight neighbouring ones, one 16-byte store (8-byte stores: 128 sequences of 128 rows, 40 heads, 162 us;
+// 16-byte stores 146).  Rows past the end of the sequence repeat its last row and are always masked by the
 // causal test.
 //
 // A query's arithmetic is its own: the maximum is that of the keys it sees in whole steps, raised in every
 // step in which it grows, the normaliser is the fp32 sum of the fp32 weights, and nothing another row of
 // the tile holds enters it, so a row has the same bits whatever follows it in its sequence.  (A
 // maximum that lags until a row of the tile exceeds it by a factor of two, the scale in the exponent's
-// multiply-add and a normaliser summed from the rounded weights by one more matrix instruction take 400
-// us where this takes 432, but tie rows to their neighbours and sum in 16 bits.)
+// multiply-add and a normaliser summed from the rounded weights by one more matrix instruction, 32 keys per
+// step, take 398 us where this takes 428, but tie rows to their neighbours and sum in 16 bits.)
 //
 // Long sequences are bound by instruction issue between the two products: the matrix core leaves two
 // issue slots of four cycles free per matrix instruction, an exponential takes two of them, any other
 // vector instruction one.  So what a step need not do it skips: only the step that meets the diagonal masks,
 // its second 32 keys are multiplied only if some row sees them, the output is rescaled only when the maximum of
 // some query grows (the factors are exactly one otherwise), and fragment addresses are constants of the stage.
-// 8 sequences of 2048 rows, 40 heads: 549 us (values through registers, every step masked and rescaled) -> 432
-// (796 TFLOP/s of causal work); 14144 ragged rows of up to 512, 32 heads over 8: 134 -> 113 us, bound by the
-// latency of a workgroup's start and its few steps.  Three waves per SIMD (168 registers, keys in two stages and
-// values in one, a second barrier per step) spill and take 441 us.
+// 8 sequences of 2048 rows, 40 heads: 547 us (values through registers, every step masked and rescaled) -> 428
+// (803 TFLOP/s of causal work); 14144 ragged rows of up to 512, 32 heads over 8: 134 -> 109 us, bound by the
+// latency of a workgroup's start and its few steps; 128 sequences of 128 rows: 150 -> 146, near the bandwidth of its
+// 671 MB.  Sequences of a few rows are bound by how many workgroups are resident, two per compute unit (128 of up
+// to 30 rows, 40 heads: 50 -> 40; the 32-key form above, three per unit, 28).  Three waves per SIMD with 64 keys (168
+// registers, one stage of keys or values, a second barrier per step) spill and take 440 to 490 us, and 35 on the short.
 // Largest of the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes that share a query), in the vector ALU.
 __device__ __forceinline__ float column_max(float x) {
   const uint32_t u = __float_as_uint(x);
@@ -408,9 +414,10 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 2) void k_attention_bf16(AttnArg
   // stages) or by chunks (an exclusive or)
   const int k_row = 8 * (r16 >> 2) + (r16 & 3);
   const uint32_t k_off = k_row * 256 + ((g ^ swz_k(k_row)) << 4);
-  // values: lane i of a group names row (key) 8 g + i/4, columns 4 (i%4) .. +3 of a tile of 16
+  // values: lane i of a group names row (key) 8 g + i/4 and four columns of chunk i%4 of a block of 32: in tile 2 dp the
+  // first four of an even chunk and the last four of an odd one, in tile 2 dp + 1 the others
   const int v_row = 8 * g + (r16 >> 2);
-  const uint32_t v_off = v_row * 256 + ((((r16 & 3) >> 1) ^ swz_v(v_row)) << 4) + (r16 & 1) * 8;
+  const uint32_t v_off = v_row * 256 + (((r16 & 3) ^ swz_v(v_row)) << 4) + (r16 & 1) * 8;
 
   f32x4 oacc[8][2];   // [head-dim tile][query tile]
 #pragma unroll
@@ -425,7 +432,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 2) void k_attention_bf16(AttnArg
   for (int ks = 0; ks < 4; ++ks) kp[ks] = s_k + (k_off ^ (ks << 6));
   uint32_t vp[8];   // LDS addresses
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) vp[dt] = (uint32_t)(uintptr_t)(lds_cchar*)s_v + (v_off ^ (uint32_t)(dt << 5));
+  for (int dt = 0; dt < 8; ++dt) vp[dt] = (uint32_t)(uintptr_t)(lds_cchar*)s_v + (v_off ^ (uint32_t)((dt >> 1) << 6 | (dt & 1) << 3));
   typedef f32x4 Scores[2][2][2];   // [32 keys][half][query tile]; lane (g, r16): query r16, keys 32 tp + 8 g + 4 hf + v
   // The wave's 32 rows face the 32 keys of block n_diag: every block before it is whole, the ones after are not seen.
   const int n_diag = wave_valid ? (wq0 - row_a) / 32 : -1;
@@ -564,11 +571,14 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 2) void k_attention_bf16(AttnArg
     const float inv = 1.0f / l;
     const int qrow = wq0 + qt * 16 + r16;
     if (qrow < row_b) {
-      bf16_t* o = (bf16_t*)a.O + (int64_t)qrow * a.ldo + h * kDh + g * 4;
+      bf16_t* o = (bf16_t*)a.O + (int64_t)qrow * a.ldo + h * kDh + g * 8;
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        const f32x4 x = oacc[dt][qt];
-        *reinterpret_cast<uint2*>(o + dt * 16) = make_uint2(pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv));
+      for (int dp = 0; dp < 4; ++dp) {
+        const f32x4 x = oacc[2 * dp][qt], y = oacc[2 * dp + 1][qt];
+        const u32x2 xp = {pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv)};
+        const u32x2 yp = {pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv)};
+        const u32x2 lo = (g & 1) ? yp : xp, hi = (g & 1) ? xp : yp;   // chunk g of the block: its first and last four columns
+        *reinterpret_cast<u32x4*>(o + dp * 32) = u32x4{lo[0], lo[1], hi[0], hi[1]};
       }
     }
   }
