@@ -70,7 +70,8 @@ typedef enum zo_dtype { ZO_F32 = 0, ZO_BF16 = 1 } zo_dtype;
  *   cand_sign  [C]    +1, -1 or 0 (0 = centre)
  *   dir_seed   [K]    64-bit seed of each direction; U uses the stream
  *                     (seed, tensor_id & ~1), V the stream (seed, tensor_id | 1)
- *   host_*            optional host copies used only for validation; may be NULL
+ *   host_*            optional host copies, used to validate a call and to choose how its work is
+ *                     launched, never for its results; may be NULL
  *   dir_seed_v [K]    optional (NULL: V is drawn from dir_seed too): separate seeds
  *                     for V, so that one V_k can be reused over an interval of steps
  *                     while U_t is drawn afresh (Sec. 3.2)
@@ -150,8 +151,8 @@ int32_t zo_batch_index(const zo_batch* batch, int32_t* tok_seq, int32_t* tok_can
  * bit-identical to an all-foreground call.
  *
  *   X [T x n] ld ldx, W [m x n] ld ldw, Y [T x m] ld ldy  (elements; row-major)
- *   in_dtype  type of X and W and of the factors U, V (ZO_F32: everything fp32
- *             on the vector ALU; ZO_BF16: bf16 operands, fp32 accumulation on
+ *   in_dtype  type of X and W and of the factors U, V (ZO_F32: fp32 operands,
+ *             products and sums, on the fp32 matrix instruction; ZO_BF16: bf16 operands, fp32 accumulation on
  *             the matrix cores, U and V rounded to bf16)
  *   out_dtype type of Y: equal to in_dtype, or ZO_F32 with ZO_BF16 inputs
  *   bias      fp32 [m] or NULL;  act 0 = none, 1 = ReLU, 2 = gated SiLU (the gated MLP of the

@@ -4,8 +4,8 @@
 // fp32 calls are small (the 256-wide configuration at 768 rows is typical), so a call is bound by the latency of
 // its launches and of the loads inside them: one preparation launch, one for the side columns, one for the
 // products; operands are requested a whole K slab (64 or 128 columns) at a time, and the tiles shrink until the
-// chip has work.  At 768 x 256 x 256 (r = 4) and a 512-row head, on the vector ALU before -> now: side columns
-// 28 -> 5 us, products 42 -> 6, head 42 -> 7, preparation four launches -> one.
+// chip has work.  At 768 x 256 x 256 (r = 4) and a 512-row head, on the vector ALU before -> now (kernel trace): side
+// columns 28 -> 7 us, products 42 -> 7, head 42 -> 8, preparation four launches -> one; linear and scoring 134 -> 31.
 //
 // An output element is summed in an order that depends on the input width alone, so its bits do not depend on
 // the batch, the tile size or the load width.
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(C::kThreads) void k_head_f32(HeadScoreF32Args p) {
   constexpr int WR = 4;   // one wave per 16 vocabulary rows, whatever the tile: a token's sums are merged in one order
   __shared__ __attribute__((aligned(16))) float lds[C::kLdsFloats];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
-  const int v0 = blockIdx.x * kSimtTile, t0 = blockIdx.y * TN;
+  const int v0 = blockIdx.x * kHeadTileF32, t0 = blockIdx.y * TN;
   f32x4 acc[C::RB][C::CB];
   C::template multiply<kVec>(p.Wh, p.ldw, p.vocab, v0, p.H, p.ldh, p.T, t0, p.d, lds, acc);
   __syncthreads();   // the operand slabs are done with: their memory holds the exchange between wave rows now
@@ -297,12 +297,12 @@ hipError_t launch_probe_f32(const ProbeF32Args& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-int head_vocab_tiles_f32(int vocab) { return (vocab + kSimtTile - 1) / kSimtTile; }
+int head_vocab_tiles_f32(int vocab) { return (vocab + kHeadTileF32 - 1) / kHeadTileF32; }
 
 hipError_t launch_head_score_f32(const HeadScoreF32Args& a, hipStream_t st) {
   if (a.T == 0) return hipSuccess;
   const bool vec = whole_quads(a.H, a.ldh, a.Wh, a.ldw, a.d);
-  static_assert(kSimtTile == 64, "vocabulary rows per workgroup");
+  static_assert(kHeadTileF32 == 64, "vocabulary rows per workgroup");
   if (tiles(a.vocab, 64, a.T, 64) >= compute_units()) {
     using C = TileF32<64, 64, 4, 1, 64>;
     const dim3 grid((a.vocab + 63) / 64, (a.T + 63) / 64);

@@ -23,7 +23,7 @@ constexpr int side_lds_bytes(int nbb, int rb, int w) { return w * (2 * rb * 2048
 // (64-row items next to eight bank blocks).
 constexpr int side_waves_of(int nbb, int rb) { return side_lds_bytes(nbb, rb, kSideWaves) <= 160 * 1024 ? kSideWaves : kSideWaves - 1; }
 constexpr int kSideMaxBlocks = 9; // 16-column blocks a side-down wave accumulates at once
-constexpr int kSimtTile = 64;     // vocabulary rows per tile of the fp32 head kernel
+constexpr int kHeadTileF32 = 64;  // vocabulary rows per tile of the fp32 head kernel
 
 struct BatchDev {
   int T, S, C, K;

@@ -35,7 +35,7 @@ namespace zo {
 
 int compute_units() { return 256; }
 int head_vocab_tiles_bf16(int vocab) { return (vocab + kTileM - 1) / kTileM; }
-int head_vocab_tiles_f32(int vocab) { return (vocab + kSimtTile - 1) / kSimtTile; }
+int head_vocab_tiles_f32(int vocab) { return (vocab + kHeadTileF32 - 1) / kHeadTileF32; }
 int attention_f32_max_head_dim() { return 256; }
 int attention_bf16_head_dim() { return 128; }
 
@@ -43,8 +43,6 @@ int attention_bf16_head_dim() { return 128; }
 STUB(launch_philox_words(uint64_t, uint32_t, uint64_t, int64_t, uint32_t*, hipStream_t))
 STUB(launch_factor_fill(uint64_t, uint32_t, int64_t, int, int, void*, hipStream_t))
 STUB(launch_tok_index(const BatchDev&, int32_t*, int32_t*, hipStream_t))
-STUB(launch_factors_f32(const BatchDev&, uint32_t, int, int, int, float*, float*, hipStream_t))
-STUB(launch_probe_f32(const ProbeF32Args&, hipStream_t))
 STUB(launch_head_score_f32(const HeadScoreF32Args&, hipStream_t))
 STUB(launch_active_rows(const int32_t*, int, int32_t*, int32_t*, int32_t*, hipStream_t))
 STUB(launch_estimate(const BatchDev&, const float*, const int32_t*, float, int, float*, float*, hipStream_t))
@@ -57,20 +55,19 @@ STUB(launch_add_norm(const NormArgs&, hipStream_t))
 STUB(launch_qk_norm_rope(const QkRopeArgs&, hipStream_t))
 STUB(launch_attention(const AttnArgs&, hipStream_t))
 
-hipError_t launch_seq_tables(const BatchDev& b, float, const SeqTables& t, hipStream_t) {
-  ++g_launches;
+static void check_tables(const BatchDev& b, const SeqTables& t) {
   inside(t.seq_kind, (size_t)b.S * 4, "seq_kind");
   inside(t.seq_scale, (size_t)b.S * 4, "seq_scale");
   inside(t.tok_seq, (size_t)b.T * 4, "tok_seq");
   inside(t.items, (size_t)t.max_items * sizeof(SideItem), "items");
   inside(t.n_items, 8, "n_items");
-  return hipSuccess;
 }
 
-hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables& t, uint32_t, int, int n, int, int RP,
+hipError_t launch_probe_prep_bf16(const BatchDev& b, float, const SeqTables& t, uint32_t, int, int n, int, int RP,
                                   int Rp, const float*, const float*, int, int, int m_img, uint16_t* Uimg, uint16_t* Vt,
-                                  uint16_t* Pimg, uint16_t* Vbt, hipStream_t st) {
-  launch_seq_tables(b, eps, t, st);
+                                  uint16_t* Pimg, uint16_t* Vbt, hipStream_t) {
+  ++g_launches;
+  check_tables(b, t);
   inside(t.tile_hdr, (size_t)t.n_tn * sizeof(TileHdr), "tile_hdr");
   inside(t.tile_slots, (size_t)t.slot_cap * 4, "tile_slots");
   inside(t.kt_tile, (size_t)t.kt_cap * 4, "kt_tile");
@@ -79,6 +76,17 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   inside(Vt, (size_t)b.K * RP * n * 2, "Vt");
   inside(Vbt, (size_t)Rp * n * 2, "Vbt");
   g_prep_small = t.frag_major ? 1 : 0;
+  return hipSuccess;
+}
+
+hipError_t launch_probe_f32(const ProbeF32Args& a, hipStream_t) {
+  ++g_launches;
+  if (a.has_side) {
+    check_tables(a.batch, a.tabs);
+    inside(a.Uf, (size_t)a.batch.K * a.m * a.r * 4, "Uf");
+    inside(a.Vf, (size_t)a.batch.K * a.n * a.r * 4, "Vf");
+    inside(a.Tside, (size_t)a.T * (a.r + a.R) * 4, "Tside");
+  }
   return hipSuccess;
 }
 
