@@ -362,15 +362,14 @@ __global__ __launch_bounds__(512, 1) void k_side_small(SideDownArgs a) {
   const int item = blockIdx.x / n_blocks, cb = blockIdx.x - item * n_blocks;
   const int n_work = a.n_items[0] * n_blocks;
   if ((int)blockIdx.x >= n_work) {
-    // workgroups without an item (the grid is a bound) clear the K tiles, a quarter at a time, where no item writes
-    for (int piece = blockIdx.x - n_work; piece < a.n_items[1] * 4; piece += gridDim.x - n_work) {
-      const int p = piece >> 2, tn = a.kt_tile[p];
-      for (int e = threadIdx.x; e < kTileN / 4 * 8; e += blockDim.x) {
-        const int rr = (piece & 3) * (kTileN / 4) + (e >> 3), c = e & 7;
-        float scale;
-        if (image_columns(a, p, tn, tn * kTileN + rr, c, scale) < 0)
-          *reinterpret_cast<u32x4*>(a.Xs + ((int64_t)p * kTileN + rr) * kTileK + c * 8) = u32x4{0u, 0u, 0u, 0u};
-      }
+    // Workgroups without an item (the grid is a bound) clear the K tiles where no item writes, 8 columns of a row per
+    // thread: each look-up is a chain of loads, and one after another they outlast the items of a narrow layer.
+    const int64_t total = (int64_t)a.n_items[1] * (kTileN * 8), stride = (int64_t)(gridDim.x - n_work) * blockDim.x;
+    for (int64_t e = (int64_t)(blockIdx.x - n_work) * blockDim.x + threadIdx.x; e < total; e += stride) {
+      const int p = (int)(e / (kTileN * 8)), rr = (int)(e >> 3) % kTileN, c = (int)e & 7, tn = a.kt_tile[p];
+      float scale;
+      if (image_columns(a, p, tn, tn * kTileN + rr, c, scale) < 0)
+        *reinterpret_cast<u32x4*>(a.Xs + ((int64_t)p * kTileN + rr) * kTileK + c * 8) = u32x4{0u, 0u, 0u, 0u};
     }
     return;
   }
@@ -543,8 +542,9 @@ hipError_t launch_side_down_bf16(const SideDownArgs& a, hipStream_t st) {
       return hipFuncSetAttribute((const void*)k_side_small, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 2 * kSmallStage);
     });
     if (ec != hipSuccess) return ec;
-    // a workgroup per item and 16 columns, and up to 128 more: with fewer the clearing would wait for one of those to end
-    const unsigned extra = a.kt_cap * 4 < 128 ? a.kt_cap * 4 : 128;
+    // a workgroup per item and 16 columns, and up to 256 more for the clearing when every one of those has an item
+    const int64_t clear = ((int64_t)a.kt_cap * (kTileN * 8) + a.ksplit * 64 - 1) / (a.ksplit * 64);
+    const unsigned extra = clear < 256 ? (unsigned)clear : 256u;
     hipLaunchKernelGGL(k_side_small, dim3((unsigned)a.max_items * (unsigned)((a.RP + a.Rp) / 16) + extra), dim3(a.ksplit * 64),
                        a.ksplit * 2 * kSmallStage, st, a);
     return hipGetLastError();
