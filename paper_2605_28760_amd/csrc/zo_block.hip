@@ -337,6 +337,7 @@ __device__ __forceinline__ bool find_query_block(const int32_t* cu, int S, int w
 // 671 MB.  Sequences of a few rows are bound by how many workgroups are resident, two per compute unit (128 of up
 // to 30 rows, 40 heads: 50 -> 40; the 32-key form above, three per unit, 28).  Three waves per SIMD with 64 keys (168
 // registers, one stage of keys or values, a second barrier per step) spill and take 440 to 490 us, and 35 on the short.
+
 // Largest of the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the lanes that share a query), in the vector ALU.
 __device__ __forceinline__ float column_max(float x) {
   const uint32_t u = __float_as_uint(x);
@@ -437,6 +438,7 @@ __global__ __launch_bounds__(kAttnWaves* kWave, 2) void k_attention_bf16(AttnArg
   // The wave's 32 rows face the 32 keys of block n_diag: every block before it is whole, the ones after are not seen.
   const int n_diag = wave_valid ? (wq0 - row_a) / 32 : -1;
   auto attend = [&](int step, auto slot_c) __attribute__((always_inline)) {
+    // (a score is rounded before the maximum is taken off: contracted or not must not be the compiler's choice)
 #pragma clang fp contract(off)
     constexpr int slot = decltype(slot_c)::value;
     const bool both = step * 2 < n_diag;   // false: the step's second 32 keys lie past every query

@@ -347,10 +347,10 @@ __device__ __forceinline__ int image_columns(const SideDownArgs& a, int p, int t
 // columns, then 5 us for the finishing kernel).  Here the column blocks go to workgroups of their own (X is re-read
 // from L2 once per block), a wave has the next 256 columns of its range in flight while it multiplies 256, and the
 // ranges are summed through LDS by the workgroup itself, which writes its 16 columns of the token-side images;
-// the rest of a K tile in use is cleared by the launch's workgroups without an item.  Loads run along rows (row pitches are often
-// multiples of 8 KiB, which puts the same columns of all rows on the same memory channel): X comes two rows of 512
-// bytes per load, through the wave's own two stages in LDS, and V and Vb are stored in the order of the matrix
-// instruction's operands (frag_major), 1 KiB per load.
+// the rest of a K tile in use is cleared by the launch's workgroups without an item.  Loads run along rows (row
+// pitches are often multiples of 8 KiB, which puts the same columns of all rows on the same memory channel): X comes
+// two rows of 512 bytes per load, through the wave's own two stages in LDS, and V and Vb are stored in the order of
+// the matrix instruction's operands (frag_major), 1 KiB per load.
 // The products, the order within a range and over the ranges, and the rounding are those of the kernels above: a
 // row's side term has the same bits on either path.
 constexpr int kSmallCols = 256;                     // columns per batch of loads
