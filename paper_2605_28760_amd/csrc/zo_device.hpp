@@ -20,6 +20,18 @@ constexpr int kWave = 64;
 constexpr int kKindForeground = -2;  // candidate id -1: base weights only
 constexpr int kKindCentre = -1;      // candidate without a probe: bank only
 
+// kind and probe scale (sign * eps) of a sequence of candidate c
+__device__ __forceinline__ void candidate_kind(int c, int n_cands, int n_dirs, float eps, const int32_t* cand_dir,
+                                               const float* cand_sign, int& kind, float& scale) {
+  kind = kKindForeground;
+  scale = 0.0f;
+  if (c < 0 || c >= n_cands) return;
+  const int d = cand_dir[c];
+  const float sg = cand_sign[c];
+  if (d >= 0 && d < n_dirs && sg != 0.0f) { kind = d; scale = sg * eps; }
+  else kind = kKindCentre;
+}
+
 // ---- Philox4x32-10 ----------------------------------------------------------
 __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
   constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;

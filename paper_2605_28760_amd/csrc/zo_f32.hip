@@ -2,10 +2,10 @@
 // instruction (v_mfma_f32_16x16x4_f32: fp32 products and sums throughout).
 //
 // fp32 calls are small (the 256-wide configuration at 768 rows is typical), so a call is bound by the latency of
-// its launches and of the loads inside them: one preparation launch, one for the side columns, one for the
-// products; operands are requested a whole K slab (64 or 128 columns) at a time, and the tiles shrink until the
-// chip has work.  At 768 x 256 x 256 (r = 4) and a 512-row head, on the vector ALU before -> now (kernel trace): side
-// columns 28 -> 7 us, products 42 -> 7, head 42 -> 8, preparation four launches -> one; linear and scoring 134 -> 31.
+// its launches and of the loads inside them: the side columns ride along with the products in one launch where they are few,
+// and have a preparation launch and one of their own otherwise; operands are requested a whole K slab (64 or 128 columns) at
+// a time, and the tiles shrink until the chip has work.  At 768 x 256 x 256 (r = 4) and a 512-row head: probe linear 16.4 us in
+// three launches (3, 7 and 7) -> 11 in one, linear and scoring 31 -> 26 (kernel trace; on the vector ALU 134).
 //
 // An output element is summed in an order that depends on the input width alone, so its bits do not depend on
 // the batch, the tile size or the load width.
@@ -30,10 +30,12 @@ struct TileF32 {
   static constexpr int kQuads = (TM + TN) * (KC / 4) / kThreads;   // 16-byte pieces of a slab per thread
   static_assert((TM + TN) * (KC / 4) % kThreads == 0, "whole pieces per thread");
 
-  template <bool kVec>
+  // side: what further waves of the workgroup multiply with the rows of B in the same walk over K (SideF32 below, or NoSide:
+  // there are none).
+  template <bool kVec, class Side>
   __device__ static __forceinline__ void multiply(const float* __restrict__ A, int64_t lda, int M, int m0,
                                                   const float* __restrict__ B, int64_t ldb, int N, int n0, int K,
-                                                  float* lds, f32x4 (&acc)[RB][CB]) {
+                                                  float* lds, f32x4 (&acc)[RB][CB], Side& side) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave / WC, wc = wave % WC;
     f32x4 piece[kQuads];
@@ -64,7 +66,14 @@ struct TileF32 {
       for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* fragA = lds + (wr * (TM / WR) + (lane & 15)) * kPitch + (lane >> 4) * 4;
     const float* fragB = lds + (TM + wc * (TN / WC) + (lane & 15)) * kPitch + (lane >> 4) * 4;
+    if constexpr (Side::kWaves > 0) {
+      if (wave >= WR * WC) {   // the side waves: a walk of their own through the same barriers
+        side.walk(K, lds + TM * kPitch);
+        return;
+      }
+    }
     load(0);
+    if constexpr (Side::kWaves > 0) __syncthreads();   // (their tables)
     for (int k0 = 0; k0 < K; k0 += KC) {
       if (k0 > 0) __syncthreads();   // every wave is done with the previous slab
 #pragma unroll
@@ -94,67 +103,288 @@ struct TileF32 {
   }
 };
 
+struct NoSide {
+  static constexpr int kWaves = 0;
+};
+
+// The side columns of a tile's tokens, computed by four more waves of the tile's own workgroup: rows of [V_0 | V_1 | .. | Vb]^T,
+// 16 to a block, meet the slabs of X that the products use.  V is drawn from its seeds slab by slab (a Philox block holds four
+// neighbouring entries of V), Vb is read; a block of the result is X [V or Vb] of the tile's tokens, and a token takes
+// the block of its own direction.  The waves of the products are waiting for their operands most of the time (one wave per
+// SIMD), so what these waves add is hidden but for their start: done by the same waves it took 12.4 us instead of 11.
+constexpr int kFusedBlocks = 3;      // 16-column blocks at most
+constexpr int kFusedColumns = 16 * kFusedBlocks;
+constexpr int kFusedTable = 1024;    // sequences and candidates at most (their tables sit in LDS)
+
+// LDS of a fused tile, in words: the operand slabs, the side operand's slab, U of the tile's features, the side columns of
+// its tokens, the tokens' kinds, the seeds, and the batch's tables.
+template <class C, int TM, int TN>
+struct FusedLds {
+  int rows, u, cols, kinds, seeds, cu, cand, dir, sign, end;
+  __host__ __device__ explicit FusedLds(const ProbeF32Args& p) {
+    const int K = p.batch.K, blocks = K * ((p.r + 15) / 16) + (p.R + 15) / 16;
+    rows = C::kLdsFloats;
+    u = rows + blocks * 16 * C::kPitch;
+    cols = u + K * TM * p.r;
+    kinds = cols + TN * (p.r + p.R);
+    seeds = (kinds + TN + 1) & ~1;   // 64-bit: [K] of U, [K] of V
+    cu = seeds + 4 * K;
+    cand = cu + p.batch.S + 1;
+    dir = cand + p.batch.S;
+    sign = dir + p.batch.C;
+    end = sign + p.batch.C;
+  }
+};
+
+template <class C, int TM, int TN, int KC>
+struct SideF32 {
+  static constexpr int kWaves = 4, kThreads = kWaves * 64;
+  static constexpr int kItems = (kFusedBlocks * (TN / 16) + kWaves - 1) / kWaves;   // (block of columns, 16 tokens) pairs of a wave
+  const ProbeF32Args& p;
+  const int m0, t0;
+  const FusedLds<C, TM, TN> at;
+  float* const lds;
+  float* const rows;             // [blocks * 16][kPitch]
+  const int rb, n_blocks;        // blocks of a direction, of all directions and the bank
+
+  __device__ __forceinline__ SideF32(const ProbeF32Args& args, float* mem, int first_m, int first_t)
+      : p(args), m0(first_m), t0(first_t), at(args), lds(mem), rows(mem + at.rows), rb((args.r + 15) / 16),
+        n_blocks(args.batch.K * ((args.r + 15) / 16) + (args.R + 15) / 16) {}
+
+  // four neighbouring entries of a factor stream
+  __device__ __forceinline__ f32x4 draw(uint64_t seed, uint32_t stream, uint64_t block) const {
+    const uint4 w = factor_block(seed, stream, block);
+    float z0, z1, z2, z3;
+    box_muller(w.x, w.y, z0, z1);
+    box_muller(w.z, w.w, z2, z3);
+    return f32x4{z0, z1, z2, z3};
+  }
+
+  // columns k0 .. k0 + KC of the side operand; with the first, U of the tile's features
+  __device__ __forceinline__ void fill(int tid, int k0) {
+    const int K = p.batch.K, n_here = min(KC, p.n - k0);
+    const uint64_t* seeds = reinterpret_cast<const uint64_t*>(lds + at.seeds);
+    float* bank = rows + K * rb * 16 * C::kPitch;
+    constexpr int U = 8;   // values of Vb asked for together
+    for (int e0 = tid; e0 < KC * p.R; e0 += kThreads * U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * kThreads, i = e / p.R, j = e - i * p.R;
+        v[u] = i < n_here ? p.Vb[(int64_t)(k0 + i) * p.R_cap + j] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * kThreads, i = e / p.R, j = e - i * p.R;
+        if (i < KC) bank[j * C::kPitch + i] = v[u];
+      }
+    }
+    const int v_dir = KC * p.r / 4, u_dir = TM * p.r / 4;   // Philox blocks: k0 r and m0 r are multiples of 4
+    const int n_v = v_dir * K, total = n_v + (k0 == 0 ? u_dir * K : 0);
+    for (int q = tid; q < total; q += kThreads) {
+      const bool is_v = q < n_v;
+      const int q0 = is_v ? q : q - n_v, per_dir = is_v ? v_dir : u_dir;
+      const int d = q0 / per_dir, blk = q0 - d * per_dir;
+      const f32x4 z = draw(seeds[is_v ? K + d : d], is_v ? p.tensor_id | 1u : p.tensor_id & ~1u, (uint64_t)(is_v ? k0 : m0) * p.r / 4 + blk);
+      if (is_v) {
+        int i = blk * 4 / p.r, j = blk * 4 - i * p.r;
+        float* dst = rows + d * rb * 16 * C::kPitch;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+          dst[j * C::kPitch + i] = i < n_here ? z[l] : 0.f;
+          if (++j == p.r) { j = 0; ++i; }
+        }
+      } else {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) lds[at.u + q0 * 4 + l] = z[l];
+      }
+    }
+  }
+
+  // The side waves' part of TileF32::multiply (slab_x: the slab's rows of X); leaves the tokens' columns and kinds in LDS.
+  __device__ __forceinline__ void walk(int n, const float* slab_x) {
+    const BatchDev& b = p.batch;
+    const int tid = threadIdx.x - C::kThreads, lane = tid & 63, wave = tid >> 6;
+    int* words = reinterpret_cast<int*>(lds);
+    {   // every table in one round trip
+      uint64_t* seeds = reinterpret_cast<uint64_t*>(lds + at.seeds);
+      for (int e = tid; e <= b.S; e += kThreads) {
+        words[at.cu + e] = b.cu[e];
+        if (e < b.S) words[at.cand + e] = b.seq_cand[e];
+      }
+      for (int e = tid; e < b.C; e += kThreads) {
+        words[at.dir + e] = b.cand_dir[e];
+        lds[at.sign + e] = b.cand_sign[e];
+      }
+      if (tid < b.K) {
+        seeds[tid] = b.seed[tid];
+        seeds[b.K + tid] = b.seed_v ? b.seed_v[tid] : b.seed[tid];
+      }
+      // rows that pad a block stay zero
+      for (int row = wave; row < n_blocks * 16; row += kWaves) {
+        const bool bank = row >= b.K * rb * 16;
+        if (bank ? row - b.K * rb * 16 >= p.R : row % (rb * 16) >= p.r)
+          for (int k = lane; k < KC; k += 64) rows[row * C::kPitch + k] = 0.f;
+      }
+    }
+    __syncthreads();
+    f32x4 acc[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < n; k0 += KC) {
+      if (k0 > 0) __syncthreads();
+      fill(tid, k0);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        const int item = i * kWaves + wave, blk = item / (TN / 16), cb = item % (TN / 16);
+        if (blk >= n_blocks) break;
+        const float* fa = rows + (blk * 16 + (lane & 15)) * C::kPitch + (lane >> 4) * 4;
+        const float* fb = slab_x + (cb * 16 + (lane & 15)) * C::kPitch + (lane >> 4) * 4;
+#pragma unroll
+        for (int kb = 0; kb < KC / 16; ++kb) {
+          if (k0 + kb * 16 >= n) break;
+          const f32x4 a = *reinterpret_cast<const f32x4*>(fa + kb * 16), x = *reinterpret_cast<const f32x4*>(fb + kb * 16);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], x[k], acc[i], 0, 0, 0);
+        }
+      }
+    }
+    // a token's kind and scale, then its columns
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int item = i * kWaves + wave, blk = item / (TN / 16), cb = item % (TN / 16);
+      const int tl = cb * 16 + (lane & 15), t = t0 + tl;
+      int kind = kKindForeground;
+      float scale = 0.f;
+      if (t < p.T) {
+        int lo = 0, hi = b.S;   // the last sequence that starts at or before the row
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (words[at.cu + mid] <= t) lo = mid; else hi = mid;
+        }
+        candidate_kind(words[at.cand + lo], b.C, b.K, p.eps, words + at.dir, lds + at.sign, kind, scale);
+      }
+      if (blk == 0) words[at.kinds + tl] = kind;
+      if (blk >= n_blocks) break;
+      const int d = blk / rb;   // direction of the block, or past them the bank
+      const bool bank = d >= b.K;
+      const int j0 = (bank ? blk - b.K * rb : blk - d * rb) * 16 + 4 * (lane >> 4);
+      if (bank ? kind < kKindCentre : kind != d) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (j0 + e < (bank ? p.R : p.r)) lds[at.cols + tl * (p.r + p.R) + (bank ? p.r : 0) + j0 + e] = bank ? acc[i][e] : acc[i][e] * scale;
+    }
+  }
+};
+
 bool whole_quads(const void* a, int64_t lda, const void* b, int64_t ldb, int K) {
   return (((uintptr_t)a | (uintptr_t)b) & 15u) == 0 && lda % 4 == 0 && ldb % 4 == 0 && K % 4 == 0;
 }
 
-// Tside[t, :] = [ s_t eps X[t,:] V_{k_t} | X[t,:] Vb ]; zero where the row has no such term.  One wave per (row,
-// 8 columns): the lanes share the input columns, then the eight sums are folded across the wave.
-__global__ __launch_bounds__(256) void k_side_f32(ProbeF32Args p) {
-  const int NC = p.r + p.R;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int j0 = blockIdx.y * 8;
-  if (t >= p.T) return;
-  const int s = p.tok_seq[t];
-  const int kind = p.seq_kind[s];
-  const float* x = p.X + (int64_t)t * p.ldx;
-  float acc[8] = {};
-  // a group of eight may hold direction columns, bank columns, or both
-  const float* src[8];
-  int64_t pitch[8];
+// Tside[t, :] = [ s_t eps X[t,:] V_{k_t} | X[t,:] Vb ] where the row has such a term, for the calls whose side columns do not
+// ride along with the products (fused_f32).  A wave per 16 rows, 16 columns and direction among the rows (the first
+// kSideDirs; further ones follow in turn), operands straight from memory, 256 columns of X asked for together: such a call is
+// a chain of round trips.  Linear and scoring, a wave per row and 8 columns on the vector ALU -> this: 3671 rows, 632 wide, 8 + 33
+// columns 225 -> 128 us; 2010 rows, 258 wide, four directions, 1 + 33 columns 80 -> 67; 252 rows, 366 wide, 8 + 33 46 -> 42.5.
+// The chain of products is that of SideF32: the same bits.
+constexpr int kSideDirs = 4;
+
+template <bool kVec>
+__global__ __launch_bounds__(64) void k_side_f32(ProbeF32Args p) {
+  constexpr int U = 16;                  // blocks of 16 columns of X per trip
+  const int NC = p.r + p.R, rb = (p.r + 15) / 16;
+  const int lane = threadIdx.x, g = lane >> 4, col = lane & 15;
+  const int t = blockIdx.x * 16 + col;   // this lane's row of X, and column of the result
+  const bool dir = (int)blockIdx.y < rb;
+  const int j0 = dir ? blockIdx.y * 16 : ((int)blockIdx.y - rb) * 16;
+  const int j = j0 + col;                // this lane's column of V or Vb
+  const int s = p.tok_seq[min(t, p.T - 1)];
+  const int kind = t < p.T ? p.seq_kind[s] : kKindForeground;
+  const float* x = p.X + (int64_t)min(t, p.T - 1) * p.ldx;
+  uint64_t left = __ballot(dir ? kind >= 0 : kind >= kKindCentre);
+  for (int nth = 0; left; ++nth) {
+    int k = 0;
+    uint64_t mine = left;
+    if (dir) {   // the rows of one direction
+      k = __builtin_amdgcn_readlane(kind, __ffsll((unsigned long long)left) - 1);
+      mine = __ballot(kind == k);
+    }
+    left &= ~mine;
+    if (nth % kSideDirs != (int)blockIdx.z) continue;
+    const float* v = dir ? p.Vf + (int64_t)k * p.n * p.r + min(j, p.r - 1) : p.Vb + min(j, p.R - 1);
+    const int64_t pitch = dir ? p.r : p.R_cap;
+    const bool real = j < (dir ? p.r : p.R);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < p.n; k0 += 16 * U) {
+      f32x4 a[U], b[U];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int j = j0 + e;
-    src[e] = nullptr;
-    pitch[e] = 0;
-    if (j < p.r) {
-      if (kind >= 0) { src[e] = p.Vf + (int64_t)kind * p.n * p.r + j; pitch[e] = p.r; }
-    } else if (j < NC && kind >= kKindCentre) {
-      src[e] = p.Vb + (j - p.r);
-      pitch[e] = p.R_cap;
+      for (int u = 0; u < U; ++u) {
+        const int at = k0 + u * 16 + g * 4;
+        if constexpr (kVec) {
+          b[u] = *reinterpret_cast<const f32x4*>(x + min(at, p.n - 4));
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) b[u][i] = x[min(at + i, p.n - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[u][i] = v[min(at + i, p.n - 1) * pitch];
+      }
+      // (the loads all go out before the first product: left alone they are moved behind the ends of the row they may be past)
+#pragma unroll
+      for (int u = 0; u < U; ++u) asm volatile("" : "+v"(a[u]), "+v"(b[u]));
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (k0 + u * 16 >= p.n) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool in = k0 + u * 16 + g * 4 + i < p.n;
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in && real ? a[u][i] : 0.f, in ? b[u][i] : 0.f, acc, 0, 0, 0);
+        }
+      }
+    }
+    if ((mine >> lane) & 1) {
+      const float scale = dir ? p.seq_scale[s] : 1.0f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int jj = j0 + 4 * g + e;
+        if (jj < (dir ? p.r : p.R)) p.Tside[(int64_t)t * NC + (dir ? jj : p.r + jj)] = acc[e] * scale;
+      }
     }
   }
-  for (int i = lane; i < p.n; i += 64) {
-    const float xi = x[i];
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (src[e]) acc[e] = fmaf(xi, src[e][(int64_t)i * pitch[e]], acc[e]);
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) acc[e] += __shfl_xor(acc[e], o);
-  }
-  const float scale = kind >= 0 ? p.seq_scale[s] : 0.0f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    if (lane == e && j0 + e < NC) p.Tside[(int64_t)t * NC + j0 + e] = j0 + e < p.r ? acc[e] * scale : acc[e];
 }
 
-template <class C, int TM, int TN, int WC, bool kVec>
-__global__ __launch_bounds__(C::kThreads) void k_probe_f32(ProbeF32Args p) {
-  __shared__ __attribute__((aligned(16))) float lds[C::kLdsFloats];
+// kFused: the call's one launch.  Four more waves look up the tile's tokens' sequences, draw the factors it needs and
+// compute its tokens' side columns along with the products; otherwise these come from memory (k_probe_prep_f32, k_side_f32).
+template <class C, int TM, int TN, int WC, int KC, bool kVec, bool kFused>
+__global__ __launch_bounds__(C::kThreads + (kFused ? 256 : 0)) void k_probe_f32(ProbeF32Args p) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m0 = blockIdx.x * TM, t0 = blockIdx.y * TN;
-  f32x4 acc[C::RB][C::CB];
-  C::template multiply<kVec>(p.W, p.ldw, p.m, m0, p.X, p.ldx, p.T, t0, p.n, lds, acc);
   const int NC = p.r + p.R;
+  f32x4 acc[C::RB][C::CB];
+  const float* s_u = nullptr;      // [direction][TM][r]
+  const float* s_side = nullptr;   // [TN][NC]
+  const int* s_kind = nullptr;
+  if constexpr (kFused) {
+    SideF32<C, TM, TN, KC> side(p, lds, m0, t0);
+    C::template multiply<kVec>(p.W, p.ldw, p.m, m0, p.X, p.ldx, p.T, t0, p.n, lds, acc, side);
+    __syncthreads();
+    if (wave >= C::kThreads / 64) return;
+    s_u = lds + side.at.u;
+    s_side = lds + side.at.cols;
+    s_kind = reinterpret_cast<const int*>(lds + side.at.kinds);
+  } else {
+    NoSide none;
+    C::template multiply<kVec>(p.W, p.ldw, p.m, m0, p.X, p.ldx, p.T, t0, p.n, lds, acc, none);
+  }
 #pragma unroll
   for (int cb = 0; cb < C::CB; ++cb) {
-    const int t = t0 + (wave % WC) * (C::CB * 16) + cb * 16 + (lane & 15);
+    const int tl = (wave % WC) * (C::CB * 16) + cb * 16 + (lane & 15), t = t0 + tl;
     if (t >= p.T) continue;
     int kind = kKindForeground;
-    if (p.has_side) kind = p.seq_kind[p.tok_seq[t]];
+    if constexpr (kFused) kind = s_kind[tl];
+    else if (p.has_side) kind = p.seq_kind[p.tok_seq[t]];
 #pragma unroll
     for (int rb = 0; rb < C::RB; ++rb) {
       const int o = m0 + (wave / WC) * (C::RB * 16) + rb * 16 + 4 * (lane >> 4);   // four neighbouring features
@@ -163,7 +393,7 @@ __global__ __launch_bounds__(C::kThreads) void k_probe_f32(ProbeF32Args p) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) y[e] = acc[rb][cb][e];
       if (kind >= kKindCentre) {   // foreground rows skip the side state entirely
-        const float* ts = p.Tside + (int64_t)t * NC;
+        const float* ts = kFused ? s_side + tl * NC : p.Tside + (int64_t)t * NC;
         float side[4] = {0.f, 0.f, 0.f, 0.f};
         int64_t at[4];   // rows past the end repeat the last one (not stored)
 #pragma unroll
@@ -175,12 +405,12 @@ __global__ __launch_bounds__(C::kThreads) void k_probe_f32(ProbeF32Args p) {
           for (int e = 0; e < 4; ++e) side[e] = fmaf(x, p.P[at[e] * p.R_cap + jj], side[e]);
         }
         if (kind >= 0) {
-          const float* u = p.Uf + (int64_t)kind * p.m * p.r;
+          const float* u = kFused ? s_u + ((int64_t)kind * TM + (o - m0)) * p.r : p.Uf + (int64_t)kind * p.m * p.r;
 #pragma unroll 4
           for (int jj = 0; jj < p.r; ++jj) {
             const float x = ts[jj];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) side[e] = fmaf(x, u[at[e] * p.r + jj], side[e]);
+            for (int e = 0; e < 4; ++e) side[e] = fmaf(x, u[(kFused ? e : at[e]) * p.r + jj], side[e]);
           }
         }
 #pragma unroll
@@ -213,7 +443,8 @@ __global__ __launch_bounds__(C::kThreads) void k_head_f32(HeadScoreF32Args p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
   const int v0 = blockIdx.x * kHeadTileF32, t0 = blockIdx.y * TN;
   f32x4 acc[C::RB][C::CB];
-  C::template multiply<kVec>(p.Wh, p.ldw, p.vocab, v0, p.H, p.ldh, p.T, t0, p.d, lds, acc);
+  NoSide none;
+  C::template multiply<kVec>(p.Wh, p.ldw, p.vocab, v0, p.H, p.ldh, p.T, t0, p.d, lds, acc, none);
   __syncthreads();   // the operand slabs are done with: their memory holds the exchange between wave rows now
   float* s_max = lds;              // [WR][TN]
   float* s_sum = lds + WR * TN;    // [WR][TN]
@@ -274,27 +505,55 @@ int64_t tiles(int rows, int tm, int cols, int tn) { return (int64_t)((rows + tm 
 
 }  // namespace
 
+// Whether a call's side columns ride along with its products, in one launch.  (No result depends on it.)  A tile draws and
+// multiplies the columns of all directions, whichever its tokens have, so the line lies at three blocks of 16; linear and
+// scoring of a layer, us, three launches -> one: one block, 768 rows, 256 wide 31 -> 26; two, 450 rows, 432 wide 39 -> 33; three,
+// 1080 rows, 209 wide 44.8 -> 42.0, 540 rows, 510 wide 79.4 -> 78.4; four, 872 rows, 344 wide 57.7 -> 66.8, 4650 rows, 392 wide 70 -> 78.
+// Tiles of 32x32 have to be resident all at once (two or three per compute unit, by their LDS): in a second round the start of a
+// tile's side waves shows (1998 rows, 343 wide, three blocks 75 -> 80; 1466 rows, 560 wide, one block 67.7 -> 69.2).
+static bool fused_f32(const ProbeF32Args& a, bool large_tiles) {
+  const int64_t blocks = (int64_t)a.batch.K * ((a.r + 15) / 16) + (a.R + 15) / 16;
+  if (!a.has_side || blocks > kFusedBlocks || a.r + a.R > kFusedColumns || a.batch.S > kFusedTable || a.batch.C > kFusedTable) return false;
+  if (large_tiles) return true;
+  const int64_t lds = sizeof(float) * (int64_t)FusedLds<TileF32<32, 32, 2, 2, 128>, 32, 32>(a).end;
+  return tiles(a.m, 32, a.T, 32) <= compute_units() * (160 * 1024 / lds);
+}
+
+template <int TM, int TN, int KC, bool kVec, bool kFused>
+static hipError_t launch_probe_f32_tile(const ProbeF32Args& a, hipStream_t st) {
+  using C = TileF32<TM, TN, 2, 2, KC>;
+  size_t lds = sizeof(float) * C::kLdsFloats;
+  if constexpr (kFused) {
+    lds = sizeof(float) * FusedLds<C, TM, TN>(a).end;
+    static std::atomic<bool> configured[kMaxDevices];
+    const hipError_t ec = once_per_device(configured, [] {
+      return hipFuncSetAttribute((const void*)k_probe_f32<C, TM, TN, 2, KC, kVec, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    });
+    if (ec != hipSuccess) return ec;
+  }
+  hipLaunchKernelGGL((k_probe_f32<C, TM, TN, 2, KC, kVec, kFused>), dim3((a.m + TM - 1) / TM, (a.T + TN - 1) / TN), dim3(C::kThreads + (kFused ? 256 : 0)), (unsigned)lds, st, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_probe_f32(const ProbeF32Args& a, hipStream_t st) {
   if (a.T == 0 || a.m == 0) return hipSuccess;
-  if (a.has_side) {
+  // 64x64 tiles when they give every compute unit one, 32x32 (a longer K slab, four times the workgroups) otherwise
+  const bool large = tiles(a.m, 64, a.T, 64) >= compute_units();
+  const bool fused = fused_f32(a, large);
+  const bool vec = whole_quads(a.X, a.ldx, a.W, a.ldw, a.n);
+  if (a.has_side && !fused) {
     const hipError_t e = launch_probe_prep_f32(a.batch, a.eps, a.tabs, a.tensor_id, a.m, a.n, a.r, a.Uf, a.Vf, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_side_f32, dim3((a.T + 3) / 4, (a.r + a.R + 7) / 8), dim3(256), 0, st, a);
+    const dim3 grid((a.T + 15) / 16, (a.r + 15) / 16 + (a.R + 15) / 16, a.batch.K < 1 ? 1 : a.batch.K < kSideDirs ? a.batch.K : kSideDirs);
+    if (vec && a.n > 0) hipLaunchKernelGGL(k_side_f32<true>, grid, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL(k_side_f32<false>, grid, dim3(64), 0, st, a);
   }
-  const bool vec = whole_quads(a.X, a.ldx, a.W, a.ldw, a.n);
-  // 64x64 tiles when they give every compute unit one, 32x32 (a longer K slab, four times the workgroups) otherwise
-  if (tiles(a.m, 64, a.T, 64) >= compute_units()) {
-    using C = TileF32<64, 64, 2, 2, 64>;
-    const dim3 grid((a.m + 63) / 64, (a.T + 63) / 64);
-    if (vec) hipLaunchKernelGGL((k_probe_f32<C, 64, 64, 2, true>), grid, dim3(C::kThreads), 0, st, a);
-    else hipLaunchKernelGGL((k_probe_f32<C, 64, 64, 2, false>), grid, dim3(C::kThreads), 0, st, a);
-  } else {
-    using C = TileF32<32, 32, 2, 2, 128>;
-    const dim3 grid((a.m + 31) / 32, (a.T + 31) / 32);
-    if (vec) hipLaunchKernelGGL((k_probe_f32<C, 32, 32, 2, true>), grid, dim3(C::kThreads), 0, st, a);
-    else hipLaunchKernelGGL((k_probe_f32<C, 32, 32, 2, false>), grid, dim3(C::kThreads), 0, st, a);
+  if (large) {
+    if (fused) return vec ? launch_probe_f32_tile<64, 64, 64, true, true>(a, st) : launch_probe_f32_tile<64, 64, 64, false, true>(a, st);
+    return vec ? launch_probe_f32_tile<64, 64, 64, true, false>(a, st) : launch_probe_f32_tile<64, 64, 64, false, false>(a, st);
   }
-  return hipGetLastError();
+  if (fused) return vec ? launch_probe_f32_tile<32, 32, 128, true, true>(a, st) : launch_probe_f32_tile<32, 32, 128, false, true>(a, st);
+  return vec ? launch_probe_f32_tile<32, 32, 128, true, false>(a, st) : launch_probe_f32_tile<32, 32, 128, false, false>(a, st);
 }
 
 int head_vocab_tiles_f32(int vocab) { return (vocab + kHeadTileF32 - 1) / kHeadTileF32; }

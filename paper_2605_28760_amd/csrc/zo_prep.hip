@@ -127,12 +127,7 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
       const int next = b.cu[s + 1];
       const int c = b.seq_cand[s];
       len = max(next - row0, 0);
-      if (c >= 0 && c < b.C) {
-        const int d = b.cand_dir[c];
-        const float sg = b.cand_sign[c];
-        if (d >= 0 && d < b.K && sg != 0.0f) { kind = d; scale = sg * eps; }
-        else kind = kKindCentre;
-      }
+      candidate_kind(c, b.C, b.K, eps, b.cand_dir, b.cand_sign, kind, scale);
       t.seq_kind[s] = kind;
       t.seq_scale[s] = scale;
       if (cached) {

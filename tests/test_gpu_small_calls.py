@@ -121,6 +121,29 @@ def test_fp32_call_on_either_tile_size(n, m, vocab, r, R, act):
     assert torch.equal(big.seq_nll[:5], small.seq_nll)
 
 
+# one and two directions, ranks below, at and above a block of 16 columns, with and without a bank, input widths that end inside
+# a group of four, a block of 16 and a K slab, both tile sizes
+@pytest.mark.parametrize("n,m,dirs,r,R", [(256, 256, 1, 4, 0), (130, 200, 2, 3, 0), (63, 96, 1, 16, 9), (300, 40, 1, 17, 0), (64, 64, 0, 1, 32),
+                                          (5, 33, 1, 1, 1), (641, 52, 2, 16, 0)])
+@pytest.mark.parametrize("long", [False, True])
+def test_fp32_side_columns_have_the_same_bits_on_either_way(n, m, dirs, r, R, long):
+    """Side columns computed along with the products, or by launches of their own: the latter are taken beyond 1024
+    sequences, here empty ones among the others."""
+    lens = [1, 33, 0, 70, 16, 2, 2, 2, 2] + ([250] * 80 if long else [])
+    w = _layer(n * m, lens, [i % (2 * dirs + 2) - 1 for i in range(len(lens))], m, n, r, R, 0, True)
+    w.dtype, w.eps, w.dir_seed = "f32", 1e-2, w.dir_seed[:dirs]
+    w.cand_dir = np.append(np.repeat(np.arange(dirs, dtype=np.int32), 2), np.int32(-1))   # (+, -) of every direction, centre
+    w.cand_sign = np.append(np.tile(np.array([1, -1], np.float32), dirs), np.float32(0))
+    a = DeviceWorkload(w, DEV).probe_linear(0)
+    empty = 1100
+    w.cu_seqlens = np.concatenate([np.zeros(empty, np.int32), w.cu_seqlens])
+    w.seq_cand = np.concatenate([np.arange(empty, dtype=np.int32) % (2 * dirs + 2) - 1, w.seq_cand]).astype(np.int32)
+    b = DeviceWorkload(w, DEV).probe_linear(0)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    assert_close(to_np(b), oracle_layer(w, 0, w.layers[0].X), 1e-5, "Y")
+
+
 @pytest.mark.parametrize("lens", [[1, 31, 32, 33, 64, 0, 96], [127, 128, 129], [160, 161, 255, 257, 1]])
 @pytest.mark.parametrize("scale,grow", [(128 ** -0.5, 0.0), (-(128 ** -0.5), 0.0), (0.0, 0.0), (0.1, 0.02), (0.1, -0.02)])
 def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
