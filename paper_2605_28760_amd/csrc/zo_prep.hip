@@ -80,14 +80,19 @@ hipError_t launch_tok_index(const BatchDev& b, int32_t* tok_seq, int32_t* tok_ca
   return hipGetLastError();
 }
 
-// Exclusive prefix sum of one value per thread over a block of 1024 threads; *total = the block's sum.
-__device__ __forceinline__ int block_scan_1024(int v, int* s_wave, int* total) {
+// Exclusive prefix sum of one value per thread over a block of 1024 threads, of which only the first n have one (n is the same
+// in every thread); *total = the sum.  Up to 64 values are the first wave's own affair (0.4 us less); the other waves get 0.
+__device__ __forceinline__ int block_scan_1024(int v, int n, int* s_wave, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int incl = v;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const int u = __shfl_up(incl, off);
     if (lane >= off) incl += u;
+  }
+  if (n <= 64) {
+    *total = __shfl(incl, 63);
+    return incl - v;
   }
   __syncthreads();   // the previous scan's totals have been read
   if (lane == 63) s_wave[wave] = incl;
@@ -103,20 +108,14 @@ __device__ __forceinline__ int block_scan_1024(int v, int* s_wave, int* total) {
   return before + incl - v;
 }
 
-// Per-sequence kind / scale, the list of side-down work items (chunks of at
-// most item_rows rows of one sequence) and, for the bf16 GEMM, the side K tiles of
-// every token tile.  One workgroup; sequences and tiles are scanned in blocks of
-// 1024 so the item order follows the row order.
-//
-// This workgroup is the longest chain of a preparation launch, so what it looks up repeatedly (bounds and kinds of
-// the first 1024 sequences) sits in LDS, and the directions a tile has met in one 64-bit mask: 34 sequences on 6 tiles
-// took 12 us with every look-up in global memory and tree scans of 20 barriers, whatever else the launch did.
+// Per-sequence kind / scale and the list of side-down work items (chunks of at most item_rows rows of one sequence).
+// One workgroup; sequences are scanned in blocks of 1024 so the item order follows the row order.  This workgroup and the
+// one of the token tiles below are the longest chains of a preparation launch of a small batch (the images are there after 2
+// to 3 us), so they run side by side, each reading the batch's tables for itself: one after the other, with a thread per
+// tile, they took 5.2 us of a prompt pair, 7.4 of 34 sequences on 6 tiles.
 __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, const SeqTables& t) {
-  constexpr int kCached = 1024;
   __shared__ int s_wave[16];
-  __shared__ int s_cu[kCached + 1], s_kind[kCached];
   const int tid = threadIdx.x;
-  const bool cached = b.S <= kCached;
   int carry = 0;
   for (int base = 0; base < b.S; base += 1024) {
     const int s = base + tid;
@@ -130,16 +129,11 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
       candidate_kind(c, b.C, b.K, eps, b.cand_dir, b.cand_sign, kind, scale);
       t.seq_kind[s] = kind;
       t.seq_scale[s] = scale;
-      if (cached) {
-        s_cu[s] = row0;
-        s_cu[s + 1] = next;   // (the neighbour writes the same value)
-        s_kind[s] = kind;
-      }
       // (a foreground sequence has no side term: no items, none of its rows is read by the side-down pass)
       nchunk = kind == kKindForeground ? 0 : (len + t.item_rows - 1) / t.item_rows;
     }
     int total;
-    const int first = carry + block_scan_1024(nchunk, s_wave, &total);
+    const int first = carry + block_scan_1024(nchunk, min(b.S - base, 1024), s_wave, &total);
     for (int j = 0; j < nchunk; ++j) {
       if (first + j < t.max_items) {
         SideItem it;
@@ -153,62 +147,91 @@ __device__ __forceinline__ void seq_tables_block(const BatchDev& b, float eps, c
     carry += total;
   }
   if (tid == 0) t.n_items[0] = min(carry, t.max_items);
-  if (!t.tile_hdr) return;
+}
 
-  // Token tiles.  A tile's slot list names the distinct directions of the sequences that intersect it, in
-  // order of first appearance, SPD slots each; it lives in a region of the list sized by the number of
-  // those sequences (the sum over the tiles is at most the tiles plus the sequences).  Kinds written by
-  // other threads of this workgroup above are visible after the barriers of the scans.
+// Largest s in [0, S) with cu[s] <= t, found by a wave: a 64th of the range per step.
+__device__ __forceinline__ int wave_seq_of_row(const int32_t* cu, int S, int t, int lane) {
+  int base = 0, n = S;
+  while (n > 1) {
+    const int step = (n + 63) >> 6, at = lane * step;
+    const int k = max(__popcll(__ballot(at < n && cu[base + min(at, n - 1)] <= t)) - 1, 0);
+    base += k * step;
+    n = min(step, n - k * step);
+  }
+  return base;
+}
+
+// The side K tiles of every token tile of the bf16 GEMM.  A tile's slot list names the distinct directions of the
+// sequences that intersect it, in order of first appearance, SPD slots each.  One workgroup, a wave per tile: its lanes look
+// at 64 of the tile's sequences at a time and take the directions off one by one.  Where a tile's slots lie needs no
+// knowledge of the tiles before it: with s the first sequence of tile i, at most s + i (tile, sequence) intersections do.
+__device__ __forceinline__ void tile_tables_block(const BatchDev& b, const SeqTables& t) {
+  constexpr int kCached = 1024;   // sequences whose bounds and kinds are kept in LDS
+  __shared__ int s_wave[16], s_cu[kCached + 1], s_kind[kCached];
+  __shared__ int s_tile[1024], s_slot0[1024];   // directions of a tile (bit 31: it holds a candidate's row), its first slot
+  __shared__ int s_dirs[16][kTileN];    // a wave's tile: the directions met so far
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool cached = b.S <= kCached;
+  auto kind_of = [&](int s) {
+    int kind;
+    float scale;
+    candidate_kind(b.seq_cand[s], b.C, b.K, 1.0f, b.cand_dir, b.cand_sign, kind, scale);
+    return kind;
+  };
+  if (cached && tid < b.S) {
+    s_cu[tid] = b.cu[tid];
+    if (tid == b.S - 1) s_cu[b.S] = b.cu[b.S];
+    s_kind[tid] = kind_of(tid);
+  }
   __syncthreads();
   const int32_t* cu = cached ? s_cu : b.cu;
-  const int32_t* kinds = cached ? s_kind : t.seq_kind;
-  int slot_carry = 0, kt_carry = 0;
+  const int per_tile = min(b.K, kTileN);
+  const bool by_sequence = (int64_t)t.n_tn + b.S <= (int64_t)t.n_tn * per_tile;   // (which of the two bounds slot_cap is)
+  int kt_carry = 0;
   for (int base = 0; base < t.n_tn; base += 1024) {
-    const int tn = base + tid;
-    int t0 = 0, t1 = 0, s_first = 0, s_last = -1, bound = 0;
-    if (tn < t.n_tn) {
-      t0 = tn * kTileN;
-      t1 = min(b.T, t0 + kTileN);
-      s_first = seq_of_row(cu, b.S, t0);
-      s_last = seq_of_row(cu, b.S, t1 - 1);
-      bound = min(min(s_last - s_first + 1, b.K), kTileN) * t.SPD;   // a tile meets at most kTileN non-empty sequences
-    }
-    int total;
-    const int slot0 = slot_carry + block_scan_1024(bound, s_wave, &total);
-    slot_carry += total;
-    int q = 0, n_kt = 0, n_bank = 0;
-    if (tn < t.n_tn) {
+    const int n_here = min(t.n_tn - base, 1024);
+    for (int i = wave; i < n_here; i += 16) {
+      const int tn = base + i, t0 = tn * kTileN, t1 = min(b.T, t0 + kTileN);
+      const int s_first = wave_seq_of_row(cu, b.S, t0, lane), s_last = wave_seq_of_row(cu, b.S, t1 - 1, lane);
+      const int slot0 = (by_sequence ? s_first + tn : tn * per_tile) * t.SPD;
+      int q = 0;
       bool any = false;
-      uint64_t met = 0;   // directions met so far, when there are at most 64
-      for (int s = s_first; s <= s_last; ++s) {
-        if (min(cu[s + 1], t1) <= max(cu[s], t0)) continue;   // no row of s in this tile
-        const int kind = kinds[s];
-        if (kind >= kKindCentre) any = true;
-        if (kind < 0) continue;
-        bool seen = false;
-        if (b.K <= 64) {
-          seen = (met >> kind) & 1;
-          met |= 1ull << kind;
-        } else {
-          for (int j = 0; j < q && !seen; ++j) seen = t.tile_slots[slot0 + j * t.SPD] == kind * t.SPD;
-        }
-        if (!seen && slot0 + (q + 1) * t.SPD <= t.slot_cap) {
-          for (int blk = 0; blk < t.SPD; ++blk) t.tile_slots[slot0 + q * t.SPD + blk] = kind * t.SPD + blk;
-          ++q;
+      for (int s0 = s_first; s0 <= s_last; s0 += 64) {
+        const int s = min(s0 + lane, s_last);
+        const bool rows = s0 + lane <= s_last && min(cu[s + 1], t1) > max(cu[s], t0);
+        const int kind = rows ? (cached ? s_kind[s] : kind_of(s)) : kKindForeground;
+        any |= __ballot(kind >= kKindCentre) != 0;
+        uint64_t left = __ballot(kind >= 0);
+        for (int j = 0; j < (s0 > s_first ? q : 0); ++j) left &= ~__ballot(kind == s_dirs[wave][j]);
+        while (left) {
+          const int k = __builtin_amdgcn_readlane(kind, __ffsll((unsigned long long)left) - 1);
+          left &= ~__ballot(kind == k);
+          if (slot0 + (q + 1) * t.SPD > t.slot_cap) break;   // cannot happen: the cap is a bound
+          if (lane < t.SPD) t.tile_slots[slot0 + q * t.SPD + lane] = k * t.SPD + lane;
+          s_dirs[wave][q++] = k;   // (every lane the same value)
         }
       }
-      n_bank = any ? t.RpT : 0;
-      n_kt = (q * t.SPD + 1) / 2 + n_bank;
+      if (lane == 0) {
+        s_tile[i] = q | (any ? 1 << 31 : 0);
+        s_slot0[i] = slot0;
+      }
     }
-    const int kt0 = kt_carry + block_scan_1024(n_kt, s_wave, &total);
+    __syncthreads();
+    const int tn = base + tid, met = tid < n_here ? s_tile[tid] : 0;   // (n_here <= 64: only the first wave's scan counts)
+    const int n_slots = (met & 0x7FFFFFFF) * t.SPD, n_bank = met < 0 ? t.RpT : 0;
+    const int n_kt = tid < n_here ? (n_slots + 1) / 2 + n_bank : 0;
+    int total;
+    const int kt0 = kt_carry + block_scan_1024(n_kt, n_here, s_wave, &total);
     kt_carry += total;
-    if (tn < t.n_tn) {
+    if (tid < n_here) {
       TileHdr h;
-      h.kt0 = kt0; h.n_slots = q * t.SPD; h.n_bank_kt = n_bank; h.slot0 = slot0;
-      if (kt0 + n_kt > t.kt_cap) { h.n_slots = 0; h.n_bank_kt = 0; n_kt = 0; }   // cannot happen: the caps are bounds
+      h.kt0 = kt0; h.n_slots = n_slots; h.n_bank_kt = n_bank; h.slot0 = s_slot0[tid];
+      const bool fits = kt0 + n_kt <= t.kt_cap;
+      if (!fits) { h.n_slots = 0; h.n_bank_kt = 0; }   // cannot happen: the caps are bounds
       t.tile_hdr[tn] = h;
-      for (int j = 0; j < n_kt; ++j) t.kt_tile[kt0 + j] = tn;
+      for (int j = 0; fits && j < n_kt; ++j) t.kt_tile[kt0 + j] = tn;
     }
+    __syncthreads();   // s_tile is written again
   }
   if (tid == 0) t.n_items[1] = min(kt_carry, t.kt_cap);
 }
@@ -383,7 +406,7 @@ hipError_t launch_probe_prep_f32(const BatchDev& b, float eps, const SeqTables& 
 }
 
 // ---- everything a bf16 probe linear prepares before its side-down pass, in one launch ------
-// Block roles, in order: [sequence tables: 1] [token -> sequence map] [U image] [V^T image]
+// Block roles, in order: [sequence tables: 1] [token tiles: 1] [token -> sequence map] [U image] [V^T image]
 // [P image] [Vb^T image: 32x32 transposing tiles, or 16-byte pieces in operand order].  The pieces do not depend on one another.
 struct ProbePrepArgs {
   BatchDev b; float eps; SeqTables tabs;
@@ -396,7 +419,8 @@ struct ProbePrepArgs {
 __global__ __launch_bounds__(1024) void k_probe_prep(ProbePrepArgs a) {
   int blk = blockIdx.x;
   if (blk == 0) { seq_tables_block(a.b, a.eps, a.tabs); return; }
-  blk -= 1;
+  if (blk == 1) { tile_tables_block(a.b, a.tabs); return; }
+  blk -= 2;
   if (blk < a.nb_tok) { tok_index_at(a.b, blk * 1024 + threadIdx.x, a.tabs.tok_seq, nullptr); return; }
   blk -= a.nb_tok;
   if (blk < a.nb_U) { image_U_at(a.b, (int64_t)blk * 1024 + threadIdx.x, a.tensor_id & ~1u, a.m, a.m_img, a.r, a.tabs.SPD, a.Uimg); return; }
@@ -436,7 +460,7 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   a.nb_P = Rp > 0 ? blocks((int64_t)m_img * tabs.RpT * 8) : 0;
   a.vbt_tiles_n = (n + 31) / 32;
   a.nb_Vbt = Rp == 0 ? 0 : tabs.frag_major ? blocks((int64_t)(n / 8) * Rp) : a.vbt_tiles_n * ((Rp + 31) / 32);
-  const int64_t total = 1 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Vbt;
+  const int64_t total = 2 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Vbt;
   hipLaunchKernelGGL(k_probe_prep, dim3((unsigned)total), dim3(1024), 0, st, a);
   return hipGetLastError();
 }
