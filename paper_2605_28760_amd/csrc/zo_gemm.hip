@@ -767,7 +767,7 @@ static hipError_t launch_probe_bias(const ProbeGemmArgs& a, hipStream_t st) {
 
 hipError_t launch_probe_gemm_bf16(const ProbeGemmArgs& a, hipStream_t st) {
   if (a.T == 0 || a.m == 0) return hipSuccess;
-  const int tile = small_gemm_tile(a.T, a.m);
+  const int tile = gemm_tile(a.T, a.m);
   if (tile >= 0) return launch_probe_gemm_small(a, tile, st);
   if (a.has_side) return a.out_bf16 ? launch_probe_bias<true, true>(a, st) : launch_probe_bias<true, false>(a, st);
   return a.out_bf16 ? launch_probe_bias<false, true>(a, st) : launch_probe_bias<false, false>(a, st);

@@ -1,5 +1,5 @@
 // The probe linear (Sec. 3.2) for batches that leave most of the chip idle when cut into 256x256 tiles: the
-// same arithmetic on smaller output tiles, one tile per workgroup.
+// same arithmetic on smaller output tiles, from 32x32 to 160x256, one tile per workgroup.
 //
 // Such a call is bound by how fast the operands reach the compute units, not by the matrix cores: the weight
 // matrix comes once from HBM and every workgroup pulls its rows of both operands from L2.  The kernel
@@ -35,11 +35,14 @@ struct SmallTile {
   static constexpr int CPR = KC / 8;                          // 16-byte chunks per row
   static constexpr int kRowBytes = KC * 2;
   static constexpr int kStage = (TM + TN) * kRowBytes;
-  static constexpr int kLoads = kStage / 1024 / kWaves;       // direct-to-LDS loads of a wave per stage
-  static constexpr int kLoadsA = TM * kRowBytes / 1024 / kWaves;
+  // direct-to-LDS loads of 1 KiB, neighbouring blocks of the A part, then of the B part, of a stage; where the A part does not
+  // come out even over the waves, they are dealt in turn and the last waves repeat the last block
+  static constexpr int kBlocksA = TM * kRowBytes / 1024, kBlocksB = TN * kRowBytes / 1024;
+  static constexpr int kLoadsA = (kBlocksA + kWaves - 1) / kWaves, kLoadsB = kBlocksB / kWaves;
+  static constexpr int kLoads = kLoadsA + kLoadsB;            // of a wave per stage
   static constexpr int kLds = S * kStage;
   static constexpr int kSideTiles = KC / kTileK;              // side K tiles per stage
-  static_assert(TM * kRowBytes % (1024 * kWaves) == 0 && TN * kRowBytes % (1024 * kWaves) == 0, "whole loads per wave");
+  static_assert(TM * kRowBytes % 1024 == 0 && TN * kRowBytes % (1024 * kWaves) == 0, "whole loads");
   static_assert((S - 1) * kLoads <= 63, "the load counter holds 6 bits");
   static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
   static_assert(kTileN % TN == 0, "a token tile of this kernel lies inside one tile of the side tables");
@@ -77,17 +80,19 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
   const int n_side_st = (n_side + C::kSideTiles - 1) / C::kSideTiles;
   const int n_st = n_side_st + (p.n + C::KC - 1) / C::KC;
 
-  // Load j of a wave fills 1 KiB block (wave * kLoadsA + j) of the A part, then of the B part, of a stage; lane
-  // i lands at byte 16 i of it.  Rows past the end of a matrix repeat its last row (never stored), columns past
+  // Load j of a wave fills a 1 KiB block of the A part, then of the B part, of a stage; lane i lands at byte 16 i of it.  Rows past the end of a matrix repeat its last row (never stored), columns past
   // the end of a row in its last stage are whatever follows (never multiplied; the windows bound every access).
   constexpr int kRowsPerLoad = 64 / C::CPR;
   const int lrow = lane / C::CPR, lchunk = lane % C::CPR;
+  auto block_of = [&](int j) {
+    if (j >= C::kLoadsA) return wave * C::kLoadsB + j - C::kLoadsA;
+    return C::kBlocksA % C::kWaves == 0 ? wave * C::kLoadsA + j : min(j * C::kWaves + wave, C::kBlocksA - 1);
+  };
   uint32_t off[C::kLoads];
 #pragma unroll
   for (int j = 0; j < C::kLoads; ++j) {
     const bool isA = j < C::kLoadsA;
-    const int blk = isA ? wave * C::kLoadsA + j : wave * (C::kLoads - C::kLoadsA) + j - C::kLoadsA;
-    const int row = blk * kRowsPerLoad + lrow;
+    const int row = block_of(j) * kRowsPerLoad + lrow;
     const int ch = lchunk ^ C::key(row);
     const int r = isA ? min(row, p.m - 1 - m0) : min(row, p.T - 1 - t0);
     off[j] = __umul24((uint32_t)r, (uint32_t)(isA ? p.ldw : p.ldx) * 2u) + ch * 16;
@@ -100,8 +105,7 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
                                                                       (int)min(bytesB, (int64_t)0x7FFFFFFF), 0x00020000);
   auto dst_of = [&](int slot, int j) {
     const bool isA = j < C::kLoadsA;
-    return lds + slot * C::kStage + (isA ? (wave * C::kLoadsA + j) * 1024
-                                         : C::TM * C::kRowBytes + (wave * (C::kLoads - C::kLoadsA) + j - C::kLoadsA) * 1024);
+    return lds + slot * C::kStage + (isA ? 0 : C::TM * C::kRowBytes) + block_of(j) * 1024;
   };
   auto issue_base = [&](int st, int slot) {
     const int soff = st * C::kRowBytes;
@@ -123,7 +127,7 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
     if (n_dir_kt > 0) {
 #pragma unroll
       for (int j = 0; j < C::kLoadsA; ++j) {
-        const int ch = lchunk ^ C::key((wave * C::kLoadsA + j) * kRowsPerLoad + lrow);
+        const int ch = lchunk ^ C::key(block_of(j) * kRowsPerLoad + lrow);
         e[j] = p.tile_slots[h.slot0 + min(2 * (st * C::kSideTiles + (ch >> 3)) + ((ch >> 2) & 1), h.n_slots - 1)];
       }
     } else {
@@ -133,8 +137,7 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
 #pragma unroll
     for (int j = 0; j < C::kLoads; ++j) {
       const bool isA = j < C::kLoadsA;
-      const int blk = isA ? wave * C::kLoadsA + j : wave * (C::kLoads - C::kLoadsA) + j - C::kLoadsA;
-      const int row = blk * kRowsPerLoad + lrow;
+      const int row = block_of(j) * kRowsPerLoad + lrow;
       const int ch = lchunk ^ C::key(row);
       const int q = min(st * C::kSideTiles + (ch >> 3), n_side - 1);
       if (!isA) {
@@ -196,8 +199,43 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   load_frags(0, lds, 0);
-  int slot = 0;
-  for (int st = 0; st < n_st; ++st) {
+  int slot = 0, st = 0;
+  if constexpr (C::KC == 64) {
+    // Stages of two k-steps whose successor S ahead is one of base columns: loads and fragment reads are spread through the
+    // products, one after each group of them: a wave that issues its loads in one burst stands at the memory pipeline's queue
+    // (5120 x 20480 at 1560 tokens on 160x256 tiles 387 -> 350 us, on 128x128 565 -> 493).
+    auto spread = [&](auto n_loads_c) __attribute__((always_inline)) {
+      constexpr int n_loads = decltype(n_loads_c)::value, n = C::RB * C::CB, n_reads = C::RB + C::CB;
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
+#pragma unroll
+        for (int e = n_reads * i / n; e < n_reads * (i + 1) / n; ++e) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+#pragma unroll
+        for (int e = n_loads * i / n; e < n_loads * (i + 1) / n; ++e) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // load
+      }
+    };
+    for (; st + C::S < n_st && (!kSide || st + C::S >= n_side_st); ++st) {
+      const int next = slot == C::S - 1 ? 0 : slot + 1;
+      __builtin_amdgcn_sched_barrier(0);
+      load_frags(1, lds + slot * C::kStage, 1);
+      mfmas(0);
+      spread(std::integral_constant<int, 0>{});
+      __builtin_amdgcn_sched_barrier(0);
+      wait_loads(std::integral_constant<int, (C::S - 2) * C::kLoads>{});
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      issue_base(st + C::S - n_side_st, slot);
+      load_frags(0, lds + next * C::kStage, 0);
+      mfmas(1);
+      spread(std::integral_constant<int, C::kLoads>{});
+      __builtin_amdgcn_sched_barrier(0);
+      slot = next;
+    }
+  }
+  for (; st < n_st; ++st) {
     const char* s = lds + slot * C::kStage;
     const int next = slot == C::S - 1 ? 0 : slot + 1;
     const int cols = (kSide && st < n_side_st) ? (n_side - st * C::kSideTiles) * kTileK : p.n - (st - n_side_st) * C::KC;
@@ -310,10 +348,18 @@ hipError_t launch_tile(const ProbeGemmArgs& a, hipStream_t st) {
 // 10 ns, measured on a 4096-row layer at 4096 and 12288 columns and on a 5120 x 20480 layer (16 .. 1536
 // tokens, weights from HBM; a 256x256 tile of the large kernel: 163, half of one: 82).  The more of a tile's
 // operands are shared, the less time per element; the smaller the tile, the more compute units have one.
-enum { kT32x32, kT32x64, kT64x32, kT64x64, kT64x128, kT128x64, kT128x128, kTiles };
-constexpr struct { int tm, tn, cost; } kTileCost[kTiles] = {
-    {32, 32, 17}, {32, 64, 20}, {64, 32, 23}, {64, 64, 28}, {64, 128, 43}, {128, 64, 43}, {128, 128, 57}};
+enum { kT32x32, kT32x64, kT64x32, kT64x64, kT64x128, kT128x64, kT128x128, kTiles, kT160x128 = kTiles, kT160x256, kAllTiles };
+constexpr struct { int tm, tn, cost; } kTileCost[kAllTiles] = {
+    {32, 32, 17}, {32, 64, 20}, {64, 32, 23}, {64, 64, 28}, {64, 128, 43}, {128, 64, 43}, {128, 128, 57}, {160, 128, 66}, {160, 256, 110}};
 constexpr int kCostWhole = 163, kCostHalf = 82;
+
+int64_t up(int64_t a, int64_t b) { return (a + b - 1) / b; }
+int64_t tile_cost(int T, int m, int tile) {   // tile -1: the 256x256 kernel
+  const int64_t cus = compute_units();
+  if (tile >= 0) return up(up(m, kTileCost[tile].tm) * up(T, kTileCost[tile].tn), cus) * kTileCost[tile].cost;
+  const int64_t whole = up(m, kTileM) * up(T, kTileN), rem = whole % cus;
+  return whole / cus * kCostWhole + (rem == 0 ? 0 : (rem <= cus / 2 ? kCostHalf : kCostWhole));
+}
 
 }  // namespace
 
@@ -322,15 +368,22 @@ constexpr int kCostWhole = 163, kCostHalf = 82;
 // 45 -> 14, at 384 45 -> 24, at 768 45 -> 34; 5120 x 20480 at 32 tokens 207 -> 56, at 512 259 -> 193;
 // 1024 x 3072 at 1475 tokens 36 -> 19; from about 1500 tokens at 4096 rows up the large kernel is the faster one.
 int small_gemm_tile(int T, int m) {
-  const int64_t cus = compute_units();
-  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-  const int64_t whole = up(m, kTileM) * up(T, kTileN), rem = whole % cus;
-  int64_t best_cost = whole / cus * kCostWhole + (rem == 0 ? 0 : (rem <= cus / 2 ? kCostHalf : kCostWhole));
   int best = -1;
-  for (int i = 0; i < kTiles; ++i) {
-    const int64_t cost = up(up(m, kTileCost[i].tm) * up(T, kTileCost[i].tn), cus) * kTileCost[i].cost;
-    if (cost < best_cost) { best = i; best_cost = cost; }
-  }
+  for (int i = 0; i < kTiles; ++i)
+    if (tile_cost(T, m, i) < tile_cost(T, m, best)) best = i;
+  return best;
+}
+
+// The same with the two tiles of 160 weight rows, for calls of some hundred to some thousand rows whose 256x256 tiles leave part of
+// the chip idle in their only round, or most of it in the second.  Their time per round depends more than that of the others
+// on how full the round is, so they have to be 5 % ahead.  Whole calls, us, 256x256 -> 160x256: 5120 x 20480 at 1560 tokens
+// 497 -> 350, at 1980 538 -> 389; 5120 x 5120 at 1740 128 -> 106; 4096 x 4096 at 2300 116 -> 92; 6144 x 4096 at 3300 180 -> 172
+// (two rounds each); 20480 x 5120 at 1300 279 -> 299 (three for two: not taken).  160x128: 5120 x 5120 at 900 81 -> 71.
+int gemm_tile(int T, int m) {
+  int best = small_gemm_tile(T, m);
+  const int64_t cost = tile_cost(T, m, best);
+  for (int i = kTiles; i < kAllTiles; ++i)
+    if (tile_cost(T, m, i) * 20 < cost * 19 && (best < kTiles || tile_cost(T, m, i) < tile_cost(T, m, best))) best = i;
   return best;
 }
 
@@ -342,6 +395,8 @@ hipError_t launch_probe_gemm_small(const ProbeGemmArgs& a, int tile, hipStream_t
     case kT64x64: return launch_tile<SmallTile<64, 64, 4, 2, 128, 4>>(a, st);
     case kT64x128: return launch_tile<SmallTile<64, 128, 2, 4, 64, 3>>(a, st);
     case kT128x64: return launch_tile<SmallTile<128, 64, 4, 2, 128, 3>>(a, st);
+    case kT160x128: return launch_tile<SmallTile<160, 128, 2, 4, 64, 4>>(a, st);
+    case kT160x256: return launch_tile<SmallTile<160, 256, 2, 4, 64, 3>>(a, st);
     default: return launch_tile<SmallTile<128, 128, 2, 4, 64, 4>>(a, st);
   }
 }

@@ -160,7 +160,8 @@ struct ProbeGemmArgs {
 };
 hipError_t launch_probe_gemm_bf16(const ProbeGemmArgs& a, hipStream_t st);
 // ---- zo_gemm_small.hip: the same products on smaller tiles, for calls with few rows --------------
-int small_gemm_tile(int T, int m);   // which of its tiles suits the call; -1: the 256x256 kernel
+int small_gemm_tile(int T, int m);   // which of its tiles up to 128x128 suits the call; -1: the 256x256 kernel
+int gemm_tile(int T, int m);         // which of all its tiles
 hipError_t launch_probe_gemm_small(const ProbeGemmArgs& a, int tile, hipStream_t st);
 
 struct HeadScoreArgs {

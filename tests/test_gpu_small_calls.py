@@ -91,6 +91,34 @@ def test_every_tile_has_the_bits_of_the_large_one(n, r, R, act, bias, out):
     assert_close(to_np(y)[some], want, 4e-2 if act == 2 else 2e-2, "Y")
 
 
+@pytest.mark.parametrize("n,r,R,act,bias,out", [(704, 33, 72, 1, True, "bf16"), (192, 16, 0, 0, False, "f32"),
+                                                (64, 4, 0, 0, True, "bf16"), (1088, 8, 200, 2, False, "bf16")])
+def test_tiles_of_160_weight_rows_have_the_bits_of_the_large_one(n, r, R, act, bias, out):
+    """Both tiles of 160 weight rows (the waves' loads of their weights do not come out even there), the last one of fewer rows,
+    on widths of fewer K stages than their rings hold, and with side state of more and of fewer than that.  The row counts hold
+    for 256 compute units: which tile each takes is asserted."""
+    m, rows = 5072, [897, 1990, 2113]
+    tile_of = zb.lib()["_ZN2zo9gemm_tileEii"]   # zo::gemm_tile(rows, weight rows)
+    assert [tile_of(x, m) for x in rows[:2]] == [7, 8] and tile_of(sum(rows), m) == -1
+    lens, group = [], []
+    for i, x in enumerate(rows):
+        while x > 0:
+            lens.append(min(x, 333))
+            group.append(i)
+            x -= lens[-1]
+    w = _layer(n, lens, [i % 8 - 1 for i in range(len(lens))], m, n, r, R, act, bias)
+    y = DeviceWorkload(w, DEV, out_dtype=out).probe_linear(0)
+    for i in (0, 1):
+        sub = wl.subset_sequences(w, np.flatnonzero(np.array(group) == i)[::-1].copy())
+        got = DeviceWorkload(sub, DEV, out_dtype=out).probe_linear(0)
+        torch.cuda.synchronize()
+        assert sub.T == rows[i] and torch.equal(y[torch.from_numpy(np.asarray(sub.meta["rows"])).to(DEV)], got), "tile %d" % i
+    some = np.r_[0:20, 880:910, w.T - 20:w.T]
+    want = oracle_layer(w, 0, w.layers[0].X, rows=some, out_dtype=out)
+    # (a gated output is the product of two sums, each within 2e-2: d(ab)/ab = da/a + db/b)
+    assert_close(to_np(y)[some], want, 4e-2 if act == 2 else 2e-2, "Y")
+
+
 # widths with and without whole groups of four columns, K slabs that end early, tiles of 32 and of 64 (the second row
 # count of a pair takes the larger tile), a vocabulary that ends inside a tile and inside a wave's rows
 @pytest.mark.parametrize("n,m,vocab,r,R,act", [(256, 256, 512, 4, 0, 0), (130, 200, 77, 3, 9, 1), (63, 96, 1000, 10, 0, 2),
