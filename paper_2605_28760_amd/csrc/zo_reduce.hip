@@ -274,8 +274,8 @@ struct BankCols { int32_t first_dir; int32_t n; int32_t col0[kBankBatch]; };
 // Four consecutive entries 4q .. 4q+3 of a [rows x r] factor stream scaled into `dst` (a row-major matrix
 // of pitch R_cap, the factor's block starting at column col0): dst = beta * f (set) or dst += beta * f.
 // One Philox block yields the four normals.  When the rank is a multiple of 4 the four entries are
-// neighbours in one row, and if the block is 16-byte aligned they move as one float4.
-template <bool kAccumulate>
+// neighbours in one row (kWhole), and if the block is 16-byte aligned they move as one float4.
+template <bool kAccumulate, bool kWhole>
 __device__ __forceinline__ void bank_quad(float* M, int R_cap, int col0, int rows, int r, uint64_t seed, uint32_t tid,
                                           int64_t q, float beta, bool bf16) {
   const int64_t e0 = q * 4, total = (int64_t)rows * r;
@@ -293,25 +293,56 @@ __device__ __forceinline__ void bank_quad(float* M, int R_cap, int col0, int row
   const int i = total < (1ll << 31) ? (int)((uint32_t)e0 / (uint32_t)r) : (int)(e0 / r);
   const int j = (int)(e0 - (int64_t)i * r);
   float* dst = M + (int64_t)i * R_cap + col0 + j;
-  if ((r & 3) == 0 && (((uintptr_t)dst) & 15u) == 0) {
+  if constexpr (kWhole) {
     float4 v = make_float4(z[0], z[1], z[2], z[3]);
-    if (kAccumulate) {
-      const float4 old = *reinterpret_cast<const float4*>(dst);
-      v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
+    if ((((uintptr_t)dst) & 15u) == 0) {
+      if (kAccumulate) {
+        const float4 old = *reinterpret_cast<const float4*>(dst);
+        v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
+      }
+      *reinterpret_cast<float4*>(dst) = v;
+    } else {
+#pragma unroll
+      for (int l = 0; l < 4; ++l) dst[l] = kAccumulate ? dst[l] + z[l] : z[l];
     }
-    *reinterpret_cast<float4*>(dst) = v;
     return;
   }
+  // Other ranks: the four entries may lie in two rows or more.  Their places follow from the first one's step by step (a 64-bit
+  // division per entry took longer than everything else: rank 6, 28 layers of 8304 rows, 4 directions 82 us -> 47), and
+  // what they are added to is read before the first one is written.  An even rank moves pairs of neighbours.
+  float* at[4];
+  int row = i, col = j;
 #pragma unroll
   for (int l = 0; l < 4; ++l) {
-    const int64_t e = e0 + l;
-    if (e >= total) break;
-    float* d1 = M + (e / r) * R_cap + col0 + (int)(e % r);
-    *d1 = kAccumulate ? *d1 + z[l] : z[l];
+    at[l] = M + (int64_t)row * R_cap + col0 + col;
+    if (++col == r) { col = 0; ++row; }
   }
+  if ((r & 1) == 0 && (((uintptr_t)at[0] | (uintptr_t)at[2]) & 7u) == 0) {   // (total is even then: pairs are whole)
+    const bool second = e0 + 2 < total;
+    float2 a = make_float2(z[0], z[1]), b = make_float2(z[2], z[3]);
+    if (kAccumulate) {
+      const float2 old_a = *reinterpret_cast<const float2*>(at[0]);
+      const float2 old_b = second ? *reinterpret_cast<const float2*>(at[2]) : old_a;
+      a.x += old_a.x; a.y += old_a.y; b.x += old_b.x; b.y += old_b.y;
+    }
+    *reinterpret_cast<float2*>(at[0]) = a;
+    if (second) *reinterpret_cast<float2*>(at[2]) = b;
+    return;
+  }
+  if (kAccumulate) {
+    float old[4];
+#pragma unroll
+    for (int l = 0; l < 4; ++l) old[l] = *at[e0 + l < total ? l : 0];
+#pragma unroll
+    for (int l = 0; l < 4; ++l) z[l] += old[l];
+  }
+#pragma unroll
+  for (int l = 0; l < 4; ++l)
+    if (e0 + l < total) *at[l] = z[l];
 }
 
 // Quad q of direction kb (within the batch `cols`) of one layer's update.
+template <bool kWhole>
 __device__ __forceinline__ void bank_update_entry(const BankUpdateArgs& a, const BankCols& cols, int kb, int64_t q) {
   const int k = cols.first_dir + kb;
   // block and mode: from the host (by value) or from the device-resident schedule
@@ -321,24 +352,26 @@ __device__ __forceinline__ void bank_update_entry(const BankUpdateArgs& a, const
   const float w = a.dir_weight ? a.dir_weight[k] : a.default_weight;
   const float beta = -a.lr * a.proj_grad[k] * w;
   if (append) {
-    bank_quad<false>(a.P, a.R_cap, col0, a.m, a.r, a.seed[k], a.tensor_id & ~1u, q, beta, a.bf16);
-    bank_quad<false>(a.Vb, a.R_cap, col0, a.n, a.r, a.seed_v ? a.seed_v[k] : a.seed[k], a.tensor_id | 1u, q, 1.0f, a.bf16);
+    bank_quad<false, kWhole>(a.P, a.R_cap, col0, a.m, a.r, a.seed[k], a.tensor_id & ~1u, q, beta, a.bf16);
+    bank_quad<false, kWhole>(a.Vb, a.R_cap, col0, a.n, a.r, a.seed_v ? a.seed_v[k] : a.seed[k], a.tensor_id | 1u, q, 1.0f, a.bf16);
   } else {
-    bank_quad<true>(a.P, a.R_cap, col0, a.m, a.r, a.seed[k], a.tensor_id & ~1u, q, beta, a.bf16);
+    bank_quad<true, kWhole>(a.P, a.R_cap, col0, a.m, a.r, a.seed[k], a.tensor_id & ~1u, q, beta, a.bf16);
   }
 }
 
 // grid.y = direction within the batch; grid.x covers the quads of max(m, n) * r entries.
+template <bool kWhole>
 __global__ void k_bank_update(BankUpdateArgs a, BankCols cols) {
-  bank_update_entry(a, cols, blockIdx.y, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  bank_update_entry<kWhole>(a, cols, blockIdx.y, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // The same update for many layers in one launch (grid.z = layer): at the paper's sizes one layer's
 // update is a few hundred KB and its launch costs more than its traffic.
+template <bool kWhole>
 __global__ void k_bank_update_multi(BankUpdateArgs a, BankCols cols, BankLayerSet layers) {
   const BankLayer& l = layers.l[blockIdx.z];
   a.P = l.P; a.Vb = l.Vb; a.R_cap = l.R_cap; a.m = l.m; a.n = l.n; a.tensor_id = l.tensor_id;
-  bank_update_entry(a, cols, blockIdx.y, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  bank_update_entry<kWhole>(a, cols, blockIdx.y, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 hipError_t launch_bank_update(const BankUpdateArgs& a, int n_dirs, const int32_t* col0, hipStream_t st) {
@@ -350,7 +383,9 @@ hipError_t launch_bank_update(const BankUpdateArgs& a, int n_dirs, const int32_t
     cols.first_dir = first;
     cols.n = n_dirs - first < kBankBatch ? n_dirs - first : kBankBatch;
     for (int i = 0; i < kBankBatch; ++i) cols.col0[i] = (col0 && i < cols.n) ? col0[first + i] : 0;
-    hipLaunchKernelGGL(k_bank_update, dim3((unsigned)((total + 255) / 256), cols.n), dim3(256), 0, st, a, cols);
+    const dim3 grid((unsigned)((total + 255) / 256), cols.n);
+    if (a.r % 4 == 0) hipLaunchKernelGGL(k_bank_update<true>, grid, dim3(256), 0, st, a, cols);
+    else hipLaunchKernelGGL(k_bank_update<false>, grid, dim3(256), 0, st, a, cols);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -375,8 +410,9 @@ hipError_t launch_bank_update_multi(const BankUpdateArgs& common, const BankLaye
       cols.first_dir = first;
       cols.n = n_dirs - first < kBankBatch ? n_dirs - first : kBankBatch;
       for (int i = 0; i < kBankBatch; ++i) cols.col0[i] = i < cols.n ? col0[first + i] : 0;
-      hipLaunchKernelGGL(k_bank_update_multi, dim3((unsigned)((total + 255) / 256), cols.n, nl), dim3(256), 0, st, common,
-                         cols, set);
+      const dim3 grid((unsigned)((total + 255) / 256), cols.n, nl);
+      if (common.r % 4 == 0) hipLaunchKernelGGL(k_bank_update_multi<true>, grid, dim3(256), 0, st, common, cols, set);
+      else hipLaunchKernelGGL(k_bank_update_multi<false>, grid, dim3(256), 0, st, common, cols, set);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

@@ -318,6 +318,34 @@ def test_bank_update_at_rank_128():
     assert np.all(np.abs(gotV - want.Vb) <= 2.0 ** -7 * np.abs(want.Vb) + 1e-6)
 
 
+@pytest.mark.parametrize("r,R_cap,col0", [(1, 5, [1, 4]), (2, 8, [6, 0]), (3, 9, [0, 5]), (6, 16, [0, 10]), (6, 17, [3, 9]), (10, 21, [11, 0])])
+def test_bank_update_at_ranks_that_are_no_multiple_of_four(r, R_cap, col0):
+    """Philox blocks that straddle rows: even ranks on columns that are and are not 8-byte aligned, odd ones, a last block of fewer
+    than four entries; accumulate and append, columns outside the blocks untouched."""
+    m, n, K = 67, 35, 2
+    rng = np.random.default_rng(r * 100 + R_cap)
+    P, Vb = (rng.standard_normal((x, R_cap)).astype(np.float32) * np.float32(0.01) for x in (m, n))
+    seeds = np.array([31, 32], np.uint64)
+    b = zo.Batch(np.array([0, 1], np.int32), np.array([0], np.int32), np.array([0], np.int32), np.array([1.0], np.float32), seeds)
+    grads = np.array([0.75, -1.5], np.float32)
+    Pd, Vd = torch.from_numpy(P).to(DEV), torch.from_numpy(Vb).to(DEV)
+    bank = zb.make_bank(R_cap, R_cap, Pd, Vd)
+    g, sd = torch.from_numpy(grads).to(DEV), torch.from_numpy(seeds.view(np.int64)).to(DEV)
+    zb.zo_bank_update(bank, m, n, r, K, sd, 4, g, 0.1, None, np.array(col0, np.int32), 0, zb.ZO_F32); _sync()
+    want = zo.bank_update(zo.Bank(P, Vb, R_cap), b, m, n, r, 4, grads, 0.1, col0, factor_dtype="f32")
+    assert_close(Pd.cpu().numpy(), want.P, 1e-5, "P accumulate")
+    assert torch.equal(Vd.cpu(), torch.from_numpy(Vb))
+    untouched = [c for c in range(R_cap) if not any(c0 <= c < c0 + r for c0 in col0)]
+    assert torch.equal(Pd.cpu()[:, untouched], torch.from_numpy(P)[:, untouched])
+    bank = zb.make_bank(R_cap, 0, Pd, Vd)
+    zb.zo_bank_update(bank, m, n, r, K, sd, 4, g, 0.1, None, np.array(col0, np.int32), 1, zb.ZO_F32); _sync()
+    U = [px.factor_matrix(int(s), 4, m, r, "f32") for s in seeds]
+    V = [px.factor_matrix(int(s), 5, n, r, "f32") for s in seeds]
+    for k, c in enumerate(col0):
+        assert_close(Pd.cpu().numpy()[:, c:c + r], -0.1 * grads[k] / K * U[k], 1e-5, "P append", atol=1e-7)
+        assert_close(Vd.cpu().numpy()[:, c:c + r], V[k], 1e-5, "Vb append", atol=1e-6)
+
+
 def test_bank_update_of_many_layers_in_one_call_equals_the_per_layer_updates():
     """zo_bank_update_multi over 50 layers of mixed shapes (more than one launch holds), accumulate and
     append, against zo_bank_update layer by layer: bit for bit, including the columns left alone."""
