@@ -784,13 +784,32 @@ int head_vocab_tiles_bf16(int vocab) { return (vocab + BM - 1) / BM; }
 // is then bound by them (147 us for 128 tokens against 50272 x 5120) instead of by the weights' way from HBM.  A tile of
 // 256 vocabulary rows x 128 tokens: a wave still owns 128 rows of its tokens, so every sum has the order (and the
 // bits) of the wide tile; the 48 KiB of a stage leave room for three, with every K tile requested two periods ahead.
-// One vocabulary tile per workgroup at a time.  Weights that do not fit the Infinity Cache are read with the
+// One tile per workgroup at a time.  Weights that do not fit the Infinity Cache are read with the
 // non-temporal hint (151936 x 4096: 336 -> 322 us; with it, 32000 x 1024, which stays there from call to call, 38.5 -> 40).
 constexpr int kNarrowTokens = BN / 2;
 constexpr int kNonTemporalLoad = 2;              // cache-policy operand of a buffer load: the nt bit
 constexpr int64_t kInfinityCache = 256ll << 20;
 constexpr int kNarrowStage = kOperandStage + kNarrowTokens * BK * 2;   // 48 KiB: 256 weight rows, 128 tokens
 static_assert(3 * kNarrowStage + 4 * BN * 4 <= kGemmLds, "three stages and the exchange buffers");
+
+//
+// Several narrow tiles are taken for a few hundred tokens whose wide tiles would fill their rounds badly: by rounds and time per
+// round and K tile (10 ns), 5 % ahead and up to eight rounds (beyond, the chip's power and not the last round counts: 6188
+// tokens against 32000 x 4096 1210 us wide, 1413 narrow).  Whole calls, us, wide -> narrow: 151936 x 4096 at 333 tokens 531 -> 466,
+// 32000 x 4096 at 224 124 -> 93, at 544 203 -> 181, 27246 x 1152 at 1066 94 -> 85; 50272 x 5120 at 1125 530 -> 553 (not taken).
+constexpr int kCostNarrow = 92, kCostWide = 163, kNarrowRounds = 8;
+
+// Bit k: k narrow tiles of tokens are taken.  (Worked out on the host for every number of them: the tokens to score are only known
+// on the device, and the divisions there cost a call 0.9 us.)
+static uint64_t narrow_counts(int n_tm, int workgroups) {
+  uint64_t mask = 2;
+  for (int k = 2; k < 64; ++k) {
+    const int64_t narrow = ((int64_t)n_tm * k + workgroups - 1) / workgroups;
+    const int64_t wide = ((int64_t)n_tm * ((k + 1) / 2) + workgroups - 1) / workgroups;
+    if (narrow <= kNarrowRounds && narrow * kCostNarrow * 20 < wide * kCostWide * 19) mask |= 1ull << k;
+  }
+  return mask;
+}
 
 template <bool kStream, class Done>
 __device__ __forceinline__ void narrow_head(const HeadScoreArgs& p, int n_tm, int n_tok, char* lds, Done done) {
@@ -800,21 +819,28 @@ __device__ __forceinline__ void narrow_head(const HeadScoreArgs& p, int n_tm, in
   const int lane = tid & 63;
   const int wm = wave >> 2, wn = wave & 3;
   const int nk = p.d / BK;
-  // token rows: load j (0, 1) covers rows (2 wave + j) * 8 .. + 7 of the tile, gathered through the list
-  uint32_t offB[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = (wave * 2 + j) * 8 + (lane >> 3);
-    offB[j] = (uint32_t)p.rows[min(row, n_tok - 1)] * (uint32_t)(p.ldh * 2) + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
-  }
+  const int n_tt = (n_tok + kNarrowTokens - 1) / kNarrowTokens;
   const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc(
       (void*)p.H, 0, (int)min(((int64_t)(p.T - 1) * p.ldh + p.d) * 2, (int64_t)0x7FFFFFFF), 0x00020000);
   uint32_t roff[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) roff[ks] = (lane & 15) * 128 + (((ks * 4 + (lane >> 4)) ^ (((lane & 15) >> 1) & 7)) << 4);
 
-  for (int tm = blockIdx.x; tm < n_tm; tm += gridDim.x) {
+  // Consecutive workgroup ids land on consecutive XCDs.  With several token tiles an XCD takes neighbouring items, the token tiles
+  // of a vocabulary tile next to each other, so that its weights are read into one L2 once; with one there is nothing to
+  // share, and neighbouring vocabulary tiles go to different XCDs (32000 x 4096: 80 us instead of 89).
+  const int slots = gridDim.x / kXcds;
+  const int first = n_tt == 1 ? (int)blockIdx.x : (blockIdx.x % kXcds) * slots + blockIdx.x / kXcds;
+  for (int item = first; item < n_tm * n_tt; item += gridDim.x) {
+    const int tm = item / n_tt, t0 = (item - tm * n_tt) * kNarrowTokens;
     const int m0 = tm * BM;
+    // token rows: load j (0, 1) covers rows (2 wave + j) * 8 .. + 7 of the tile, gathered through the list
+    uint32_t offB[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int row = (wave * 2 + j) * 8 + (lane >> 3);
+      offB[j] = (uint32_t)p.rows[min(t0 + row, n_tok - 1)] * (uint32_t)(p.ldh * 2) + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+    }
     uint32_t offA[kLPW];
 #pragma unroll
     for (int j = 0; j < kLPW; ++j) {
@@ -854,6 +880,18 @@ __device__ __forceinline__ void narrow_head(const HeadScoreArgs& p, int n_tm, in
         for (int cb = 0; cb < kCB; ++cb)
           acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[set][rb], fb[set][cb], acc[rb][cb], 0, 0, 0);
     };
+    // loads and fragment reads spread through the products, one after each group of them
+    auto spread = [&](auto n_loads_c) __attribute__((always_inline)) {
+      constexpr int n_loads = decltype(n_loads_c)::value, n = RB * kCB, n_reads = RB + kCB;
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
+#pragma unroll
+        for (int e = n_reads * i / n; e < n_reads * (i + 1) / n; ++e) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+#pragma unroll
+        for (int e = n_loads * i / n; e < n_loads * (i + 1) / n; ++e) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // load
+      }
+    };
     block_barrier();   // the exchange buffers and stages of the tile before are free
     issue(0, 0);
     issue(1, 1);
@@ -864,31 +902,33 @@ __device__ __forceinline__ void narrow_head(const HeadScoreArgs& p, int n_tm, in
     frags(0, 0, 0);
     int stg = 0;
     for (int kt = 0; kt < nk; ++kt) {
-      frags(1, stg, 1);
       __builtin_amdgcn_sched_barrier(0);
+      frags(1, stg, 1);
       mfmas(0);
+      spread(std::integral_constant<int, 0>{});
       __builtin_amdgcn_sched_barrier(0);
       // the next K tile has landed; every wave is done reading this one's stage, which takes the one three ahead
       asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
       block_barrier();
+      __builtin_amdgcn_sched_barrier(0);
       issue(kt + 3, stg);
       const int nxt = stg == 2 ? 0 : stg + 1;
       frags(0, nxt, 0);
-      __builtin_amdgcn_sched_barrier(0);
       mfmas(1);
+      spread(std::integral_constant<int, kLPW + 2>{});
       __builtin_amdgcn_sched_barrier(0);
       stg = nxt;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // drain the trailing loads
     block_barrier();                                  // ... of every wave, and its last (unused) fragment reads
-    done(m0, 0, acc, std::integral_constant<int, kCB>{});
+    done(m0, t0, acc, std::integral_constant<int, kCB>{});
   }
 }
 
 // kGather: only the scored tokens (rows p.rows[0 .. *p.n_rows - 1] of H) are multiplied; token tiles
 // and the partial outputs then run over positions in that list.
 template <bool kGather>
-__global__ __launch_bounds__(kThreads, 1) void k_head_score(HeadScoreArgs p, int n_tm, int tn_super) {
+__global__ __launch_bounds__(kThreads, 1) void k_head_score(HeadScoreArgs p, int n_tm, int tn_super, uint64_t narrow) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int n_tok = kGather ? __builtin_amdgcn_readfirstlane(*p.n_rows) : p.T;   // tokens to score
   if (n_tok == 0) return;
@@ -976,10 +1016,10 @@ __global__ __launch_bounds__(kThreads, 1) void k_head_score(HeadScoreArgs p, int
 
   auto epilogue = [&](int tile_v0, int tile_t0, Acc& acc, auto) { tile_done(tile_v0, tile_t0, acc, std::integral_constant<int, CB>{}); };
 
-  // Up to 128 scored tokens (the label token of each sequence of a batch): one narrow token tile.
   if constexpr (kGather) {
-    if (n_tok <= kNarrowTokens) {
-      if ((int64_t)p.vocab * p.ldw * 2 > kInfinityCache) narrow_head<true>(p, n_tm, n_tok, lds, tile_done);
+    const int n_tt = (n_tok + kNarrowTokens - 1) / kNarrowTokens;
+    if (n_tt < 64 && ((narrow >> n_tt) & 1)) {
+      if (n_tok <= kNarrowTokens && (int64_t)p.vocab * p.ldw * 2 > kInfinityCache) narrow_head<true>(p, n_tm, n_tok, lds, tile_done);
       else narrow_head<false>(p, n_tm, n_tok, lds, tile_done);
       return;
     }
@@ -999,7 +1039,8 @@ static hipError_t launch_head_variant(const HeadScoreArgs& a, hipStream_t st) {
   // the grid is sized for every token being scored; with fewer, the surplus workgroups find no tile
   const int n_tm = (a.vocab + BM - 1) / BM, n_tn = (a.T + BN - 1) / BN;
   const int tn_super = token_super_block(n_tn, (int64_t)a.T * a.d * 2);
-  hipLaunchKernelGGL(k_head_score<kGather>, dim3(gemm_grid(n_tm * n_tn)), dim3(kThreads), kGemmLds, st, a, n_tm, tn_super);
+  const int grid = gemm_grid(n_tm * n_tn);
+  hipLaunchKernelGGL(k_head_score<kGather>, dim3(grid), dim3(kThreads), kGemmLds, st, a, n_tm, tn_super, narrow_counts(n_tm, grid));
   return hipGetLastError();
 }
 

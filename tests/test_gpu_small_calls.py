@@ -243,6 +243,34 @@ def test_few_scored_tokens_have_the_bits_of_a_full_call(vocab, d, pitch, scored)
     assert_close(to_np(full), zo.token_nll(w.X, w.head, w.targets), 1e-4, "tok_nll", atol=1e-4)
 
 
+@pytest.mark.parametrize("d", [64, 192, 320])
+def test_some_hundred_scored_tokens_have_the_bits_of_a_full_call(d):
+    """Several narrow token tiles (129 to 640 tokens against 274 vocabulary tiles: three to six rounds of 256 workgroups, the last
+    tile of one token and of all), against the wide tiles that 1201 tokens take, with 1, 3 and 5 K tiles."""
+    vocab, T = 70000, 1201
+    rng = np.random.default_rng(d)
+    cu = np.array([0, 100, 100, 750, T], np.int32)
+    w = wl.Workload("some", 9, "bf16", 4, 1e-3, cu, np.array([0, 1, -1, 0], np.int32), np.zeros(2, np.int32),
+                    np.array([1, -1], np.float32), np.arange(1, dtype=np.uint64), [], True,
+                    wl.as_bf16_values(rng.standard_normal((T, d)).astype(np.float32)),
+                    wl.as_bf16_values((rng.standard_normal((vocab, d)) / np.sqrt(d)).astype(np.float32)),
+                    rng.integers(0, vocab, T).astype(np.int32), 0)
+    g = DeviceWorkload(w, DEV)
+    g.score(H=g.X)
+    full, targets = g.tok_nll.clone(), g.targets
+    some = np.r_[0:40, T - 40:T]
+    assert_close(to_np(full)[some], zo.token_nll(w.X[some], w.head, w.targets[some]), 1e-4, "tok_nll", atol=1e-4)
+    for scored in (129, 256, 300, 640):
+        keep = torch.from_numpy(np.sort(rng.choice(T, scored, replace=False))).to(DEV)
+        g.targets = torch.full_like(targets, -1)
+        g.targets[keep] = targets[keep]
+        g.tok_nll.fill_(float("nan"))
+        g.score(H=g.X)
+        torch.cuda.synchronize()
+        assert torch.equal(g.tok_nll[keep], full[keep]), scored
+        assert int((g.tok_nll != 0).sum()) <= scored
+
+
 @pytest.mark.parametrize("S,K", [(1025, 3), (1500, 70), (300, 70), (1024, 64)])
 def test_tables_of_many_sequences_and_directions(S, K):
     """More than 1024 sequences (tables in global memory instead of LDS) and more than 64 directions (slot lists searched
