@@ -105,6 +105,28 @@ def test_add_norm_matches_oracle(dtype, d, pad, kind):
     np.testing.assert_array_equal(got_y4, got_y)
 
 
+@pytest.mark.parametrize("d", [8, 1016, 1032, 2056, 3080, 4104, 5128, 6152, 7176, 8192])
+@pytest.mark.parametrize("kind", [ob.LAYER_NORM, ob.RMS_NORM])
+def test_add_norm_at_the_edges_of_its_row_widths(d, kind):
+    """One width past and one before the kernels' steps of 1024, with more rows than one round of
+    workgroups takes: the rows repeat, so every row of a later trip has the bits of a first one."""
+    g = _rng(d * 10 + kind + 1)
+    few, T = 3, 8 * 4 * torch.cuda.get_device_properties(0).multi_processor_count + 6
+    T = T if d <= 2056 else T // 2
+    x, res = g.normal(size=(few, d)) * 2 + 0.3, g.normal(size=(few, d))
+    gamma = 1 + 0.2 * g.normal(size=d)
+    beta = 0.1 * g.normal(size=d) if kind == ob.LAYER_NORM else None
+    gv, bv = (None if v is None else np.asarray(v, np.float32).astype(np.float64) for v in (gamma, beta))
+    rows = np.arange(T) % few
+    for r in (res, None):
+        want_h, want_y = ob.add_norm(_vals(x, "bf16"), None if r is None else _vals(r, "bf16"), gv, bv, kind, 1e-5, "bf16")
+        got_h, got_y = _run_add_norm(x[rows], None if r is None else r[rows], gamma, beta, kind, 1e-5, "bf16", pad=8)
+        assert_close(got_y[:few], want_y, 2e-2, "y")
+        np.testing.assert_array_equal(got_y, got_y[:few][rows])
+        if r is not None:
+            np.testing.assert_array_equal(got_h, want_h[rows])
+
+
 def test_add_norm_moments_of_a_shifted_row():
     """A common offset of 30 standard deviations must not spoil the variance: the one-pass formula
     E[x^2] - E[x]^2 loses about 900 * 2^-24 of it in fp32, the two-pass moments do not."""
