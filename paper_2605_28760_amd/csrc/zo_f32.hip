@@ -511,9 +511,10 @@ int64_t tiles(int rows, int tm, int cols, int tn) { return (int64_t)((rows + tm 
 // 1080 rows, 209 wide 44.8 -> 42.0, 540 rows, 510 wide 79.4 -> 78.4; four, 872 rows, 344 wide 57.7 -> 66.8, 4650 rows, 392 wide 70 -> 78.
 // Tiles of 32x32 have to be resident all at once (two or three per compute unit, by their LDS): in a second round the start of a
 // tile's side waves shows (1998 rows, 343 wide, three blocks 75 -> 80; 1466 rows, 560 wide, one block 67.7 -> 69.2).
+// Inputs without columns go the other way: the factors are drawn with the slabs of X, of which there are none.
 static bool fused_f32(const ProbeF32Args& a, bool large_tiles) {
   const int64_t blocks = (int64_t)a.batch.K * ((a.r + 15) / 16) + (a.R + 15) / 16;
-  if (!a.has_side || blocks > kFusedBlocks || a.r + a.R > kFusedColumns || a.batch.S > kFusedTable || a.batch.C > kFusedTable) return false;
+  if (!a.has_side || a.n == 0 || blocks > kFusedBlocks || a.r + a.R > kFusedColumns || a.batch.S > kFusedTable || a.batch.C > kFusedTable) return false;
   if (large_tiles) return true;
   const int64_t lds = sizeof(float) * (int64_t)FusedLds<TileF32<32, 32, 2, 2, 128>, 32, 32>(a).end;
   return tiles(a.m, 32, a.T, 32) <= compute_units() * (160 * 1024 / lds);

@@ -172,6 +172,31 @@ def test_fp32_side_columns_have_the_same_bits_on_either_way(n, m, dirs, r, R, lo
     assert_close(to_np(b), oracle_layer(w, 0, w.layers[0].X), 1e-5, "Y")
 
 
+@pytest.mark.parametrize("m,act", [(33, 1), (300, 0), (64, 2)])
+def test_fp32_linear_of_inputs_without_columns(m, act):
+    """Every row is act(bias), whatever the compute units' LDS holds (NaN, from a bf16 linear on whole tiles before)."""
+    dirty = _layer(m, [256 * 64], [0], 4096, 192, 4, 0, 0, False)
+    for l in dirty.layers:
+        l.X, l.W = np.full_like(l.X, np.nan), np.full_like(l.W, np.nan)
+    dirty = DeviceWorkload(dirty, DEV)
+    lens, r = [5, 0, 70, 33, 2], 4
+    cu = np.zeros(len(lens) + 1, np.int32)
+    cu[1:] = np.cumsum(lens)
+    T = int(cu[-1])
+    b = DeviceBatch(cu, np.array([0, 1, -1, 2, 1], np.int32), np.array([0, 0, -1], np.int32), np.array([1, -1, 0], np.float32),
+                    np.array([9], np.uint64), DEV)
+    X, W, bias = torch.zeros(T, 1, device=DEV), torch.zeros(m, 1, device=DEV), torch.randn(m, device=DEV)
+    m_out = m // 2 if act == 2 else m
+    Y = torch.full((T, m_out), 7.0, device=DEV)
+    n_ws = zb.zo_probe_linear_workspace_bytes(T, b.S, b.K, m, 0, r, 0, zb.ZO_F32)
+    ws = torch.full((n_ws,), 255, device=DEV, dtype=torch.uint8)
+    dirty.probe_linear(0)
+    zb.zo_probe_linear(b.struct, X, 1, W, 1, bias, m, 0, zb.ZO_F32, r, 0.5, 2, None, act, Y, m_out, zb.ZO_F32, ws, n_ws)
+    torch.cuda.synchronize()
+    want = torch.relu(bias) if act == 1 else bias if act == 0 else torch.nn.functional.silu(bias[0::2]) * bias[1::2]
+    assert_close(to_np(Y), np.broadcast_to(to_np(want), (T, m_out)), 1e-6, "Y")
+
+
 @pytest.mark.parametrize("lens", [[1, 31, 32, 33, 64, 0, 96], [127, 128, 129], [160, 161, 255, 257, 1]])
 @pytest.mark.parametrize("scale,grow", [(128 ** -0.5, 0.0), (-(128 ** -0.5), 0.0), (0.0, 0.0), (0.1, 0.02), (0.1, -0.02)])
 def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
