@@ -202,9 +202,31 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
   load_frags(0, lds, 0);
   int slot = 0, st = 0;
   if constexpr (C::KC == 64) {
-    // Stages of two k-steps whose successor S ahead is one of base columns: loads and fragment reads are spread through the
-    // products, one after each group of them: a wave that issues its loads in one burst stands at the memory pipeline's queue
-    // (5120 x 20480 at 1560 tokens on 160x256 tiles 387 -> 350 us, on 128x128 565 -> 493).
+    // Stages of two k-steps.  First the side stages whose successor S ahead is a side stage too: a few, and their loads are
+    // three times as many instructions with the addresses.
+    if constexpr (kSide) {
+      for (; st + C::S < n_side_st; ++st) {
+        const int next = slot == C::S - 1 ? 0 : slot + 1;
+        load_frags(1, lds + slot * C::kStage, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mfmas(0);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_loads(std::integral_constant<int, (C::S - 2) * C::kLoads>{});
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue_side(st + C::S, slot);
+        load_frags(0, lds + next * C::kStage, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        mfmas(1);
+        __builtin_amdgcn_sched_barrier(0);
+        slot = next;
+      }
+    }
+    // Then every stage whose successor is one of base columns: loads and fragment reads are spread through the products, one
+    // after each group of them: a wave that issues its loads in one burst stands at the memory pipeline's queue (5120 x 20480 at
+    // 1560 tokens on 160x256 tiles 387 -> 350 us, on 128x128 565 -> 493; with more side stages than the ring has, 200 bank columns or
+    // 24 directions, 5120 x 20480 at 1552 tokens on 160x256 460 -> 410, 5120 x 5120 at 480 on 128x128 75 -> 60).
     auto spread = [&](auto n_loads_c) __attribute__((always_inline)) {
       constexpr int n_loads = decltype(n_loads_c)::value, n = C::RB * C::CB, n_reads = C::RB + C::CB;
 #pragma unroll
@@ -216,7 +238,7 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
         for (int e = n_loads * i / n; e < n_loads * (i + 1) / n; ++e) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // load
       }
     };
-    for (; st + C::S < n_st && (!kSide || st + C::S >= n_side_st); ++st) {
+    for (; st + C::S < n_st; ++st) {
       const int next = slot == C::S - 1 ? 0 : slot + 1;
       __builtin_amdgcn_sched_barrier(0);
       load_frags(1, lds + slot * C::kStage, 1);
@@ -278,13 +300,13 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
     }
     // The stage's last k-step multiplies what is already in registers: once every wave has read its fragments
     // the slot can take the stage S ahead, and the next stage's first fragments are read under the products.
-    // (Stages of more than two k-steps: side stages only, see above.)
+    // (Only side stages of more than two k-steps: the others are taken above.)
     if (st + C::S <= n_st) wait_loads(std::integral_constant<int, (C::S - 2) * C::kLoads>{});
     else wait_loads(std::integral_constant<int, 0>{});
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (st + C::S < n_st && (kSteps == 2 || (kSide && st + C::S < n_side_st))) issue(st + C::S, slot);
+    if (kSteps > 2 && kSide && st + C::S < n_side_st) issue_side(st + C::S, slot);
     if (st + 1 < n_st) load_frags(0, lds + next * C::kStage, 0);
     __builtin_amdgcn_sched_barrier(0);
     mfmas(1);

@@ -119,6 +119,30 @@ def test_tiles_of_160_weight_rows_have_the_bits_of_the_large_one(n, r, R, act, b
     assert_close(to_np(y)[some], want, 4e-2 if act == 2 else 2e-2, "Y")
 
 
+@pytest.mark.parametrize("n", [64, 192, 640])
+@pytest.mark.parametrize("m,rows,filler", [(4112, [300, 890], 1300), (5072, [897, 1990], 2113)])
+def test_more_side_stages_than_the_ring_holds(n, m, rows, filler):
+    """The four tiles with stages of 64 columns behind 9 side K tiles, more than any of their rings: no base column in the ring when
+    the walk begins, and fewer base stages than the ring, as many, more."""
+    tile_of = zb.lib()["_ZN2zo9gemm_tileEii"]   # zo::gemm_tile(rows, weight rows)
+    assert [tile_of(x, m) for x in rows] == ([4, 6] if m == 4112 else [7, 8]) and tile_of(sum(rows) + filler, m) == -1
+    lens, group = [], []
+    for i, x in enumerate(rows + [filler]):
+        while x > 0:
+            lens.append(min(x, 70))
+            group.append(i)
+            x -= lens[-1]
+    w = _layer(n + m, lens, [i % 8 - 1 for i in range(len(lens))], m, n, 33, 330, 0, True)
+    y = DeviceWorkload(w, DEV, out_dtype="f32").probe_linear(0)
+    for i in (0, 1):
+        sub = wl.subset_sequences(w, np.flatnonzero(np.array(group) == i)[::-1].copy())
+        got = DeviceWorkload(sub, DEV, out_dtype="f32").probe_linear(0)
+        torch.cuda.synchronize()
+        assert sub.T == rows[i] and torch.equal(y[torch.from_numpy(np.asarray(sub.meta["rows"])).to(DEV)], got), "tile %d" % i
+    some = np.r_[0:20, rows[0] - 8:rows[0] + 8, w.T - 20:w.T]
+    assert_close(to_np(y)[some], oracle_layer(w, 0, w.layers[0].X, rows=some, out_dtype="f32"), 2e-2, "Y")
+
+
 # widths with and without whole groups of four columns, K slabs that end early, tiles of 32 and of 64 (the second row
 # count of a pair takes the larger tile), a vocabulary that ends inside a tile and inside a wave's rows
 @pytest.mark.parametrize("n,m,vocab,r,R,act", [(256, 256, 512, 4, 0, 0), (130, 200, 77, 3, 9, 1), (63, 96, 1000, 10, 0, 2),
