@@ -780,8 +780,8 @@ hipError_t launch_probe_gemm_bf16(const ProbeGemmArgs& a, hipStream_t st) {
 // ---------------------------------------------------------------------------------------
 int head_vocab_tiles_bf16(int vocab) { return (vocab + BM - 1) / BM; }
 
-// The head against at most 128 tokens.  Half of a 256-token tile's matrix instructions would be padding, and the call
-// is then bound by them (147 us for 128 tokens against 50272 x 5120) instead of by the weights' way from HBM.  A tile of
+// The head against narrow tiles of 128 tokens.  For at most 128 tokens half of a 256-token tile's matrix instructions would be
+// padding, and the call is then bound by them (147 us for 128 tokens against 50272 x 5120) instead of by the weights' way from HBM.  A tile of
 // 256 vocabulary rows x 128 tokens: a wave still owns 128 rows of its tokens, so every sum has the order (and the
 // bits) of the wide tile; the 48 KiB of a stage leave room for three, with every K tile requested two periods ahead.
 // One tile per workgroup at a time.  Weights that do not fit the Infinity Cache are read with the
@@ -792,21 +792,25 @@ constexpr int64_t kInfinityCache = 256ll << 20;
 constexpr int kNarrowStage = kOperandStage + kNarrowTokens * BK * 2;   // 48 KiB: 256 weight rows, 128 tokens
 static_assert(3 * kNarrowStage + 4 * BN * 4 <= kGemmLds, "three stages and the exchange buffers");
 
-//
-// Several narrow tiles are taken for a few hundred tokens whose wide tiles would fill their rounds badly: by rounds and time per
-// round and K tile (10 ns), 5 % ahead and up to eight rounds (beyond, the chip's power and not the last round counts: 6188
-// tokens against 32000 x 4096 1210 us wide, 1413 narrow).  Whole calls, us, wide -> narrow: 151936 x 4096 at 333 tokens 531 -> 466,
-// 32000 x 4096 at 224 124 -> 93, at 544 203 -> 181, 27246 x 1152 at 1066 94 -> 85; 50272 x 5120 at 1125 530 -> 553 (not taken).
-constexpr int kCostNarrow = 92, kCostWide = 163, kNarrowRounds = 8;
+// Several narrow tiles are taken for a few hundred tokens whose wide tiles would fill their rounds badly: where they need at most
+// half as many rounds again as the wide ones, and up to eight (beyond, the chip's power and not the last round counts: 6188 tokens
+// against 32000 x 4096 1210 us wide, 1413 narrow).  A narrow round takes 0.60 to 0.66 of a wide one.  Whole calls, us, wide ->
+// narrow, by rounds (wide, narrow): (1, 1) 12288 x 4096 at 382 tokens 89 -> 59; (2, 2) 42140 x 4096 at 384 212 -> 141; (5, 4) 102044 x
+// 4096 at 382 413 -> 328; (4, 3) 50432 x 2048 at 580 161 -> 137; (5, 7) 151964 x 5120 at 324 655 -> 585; (2, 3) 32000 x 4096 at 708 210
+// -> 190; (4, 6) 50432 x 4096 at 836 380 -> 346, 50432 x 512 at 836 70.4 -> 67.2.  Not taken: (5, 8) 100764 x 4096 at 640 519 -> 489, but
+// 45212 x 5120 at 1406 577 -> 595 and 52636 x 4096 at 1152 449 -> 457; (3, 5) 151964 x 4096 at 196 370 -> 347, 32000 x 5120 at 1152 371
+// -> 370, 32000 x 512 at 1092 57 -> 59, 152064 x 5120 at 256 444 -> 453; (4, 7) 50332 x 4096 at 964 391 -> 390, 34204 x 4096 at 1604
+// 384 -> 420; (1, 2) 31900 x 4096 at 384 122 -> 132.
+constexpr int kNarrowRounds = 8;
 
 // Bit k: k narrow tiles of tokens are taken.  (Worked out on the host for every number of them: the tokens to score are only known
 // on the device, and the divisions there cost a call 0.9 us.)
-static uint64_t narrow_counts(int n_tm, int workgroups) {
+uint64_t head_narrow_counts(int n_tm, int workgroups) {
   uint64_t mask = 2;
   for (int k = 2; k < 64; ++k) {
     const int64_t narrow = ((int64_t)n_tm * k + workgroups - 1) / workgroups;
     const int64_t wide = ((int64_t)n_tm * ((k + 1) / 2) + workgroups - 1) / workgroups;
-    if (narrow <= kNarrowRounds && narrow * kCostNarrow * 20 < wide * kCostWide * 19) mask |= 1ull << k;
+    if (narrow <= kNarrowRounds && narrow * 2 <= wide * 3) mask |= 1ull << k;
   }
   return mask;
 }
@@ -1040,7 +1044,7 @@ static hipError_t launch_head_variant(const HeadScoreArgs& a, hipStream_t st) {
   const int n_tm = (a.vocab + BM - 1) / BM, n_tn = (a.T + BN - 1) / BN;
   const int tn_super = token_super_block(n_tn, (int64_t)a.T * a.d * 2);
   const int grid = gemm_grid(n_tm * n_tn);
-  hipLaunchKernelGGL(k_head_score<kGather>, dim3(grid), dim3(kThreads), kGemmLds, st, a, n_tm, tn_super, narrow_counts(n_tm, grid));
+  hipLaunchKernelGGL(k_head_score<kGather>, dim3(grid), dim3(kThreads), kGemmLds, st, a, n_tm, tn_super, head_narrow_counts(n_tm, grid));
   return hipGetLastError();
 }
 

@@ -252,3 +252,19 @@ def test_bank_update_multi_validation():
     upd([])                                             # no layers: nothing to do
     upd([good], K=0, col0=[])                           # no directions either
     assert C.sizeof(zb.zo_layer_bank) == 40
+
+
+def test_narrow_head_tiles_are_taken_only_where_their_rounds_are_at_most_half_as_many_again():
+    """Rounds of 256 workgroups, (wide, narrow): the classes that measured faster, the ones that did not, and a single tile always."""
+    taken = zb.lib()["_ZN2zo18head_narrow_countsEii"]   # zo::head_narrow_counts(vocabulary tiles, workgroups), one bit per count
+    taken.restype = C.c_uint64
+    up = lambda a, b: -(-a // b)
+    seen = set()
+    for n_tm in range(1, 700):
+        bits = taken(n_tm, 256)
+        assert bits & 3 == 2
+        for k in range(2, 64):
+            rounds = up(n_tm * up(k, 2), 256), up(n_tm * k, 256)
+            seen.add(rounds)
+            assert (bits >> k & 1) == (rounds[1] <= 8 and rounds[1] <= 1.5 * rounds[0]), (n_tm, k, rounds)
+    assert {(1, 1), (2, 3), (4, 6), (5, 7), (3, 5), (5, 8), (4, 7), (1, 2)} <= seen

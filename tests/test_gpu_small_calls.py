@@ -1,5 +1,7 @@
 """Calls with few rows, which run on smaller tiles and their own side-down pass: the kernels a call takes must not
 show in its results."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -309,6 +311,9 @@ def test_some_hundred_scored_tokens_have_the_bits_of_a_full_call(d):
     full, targets = g.tok_nll.clone(), g.targets
     some = np.r_[0:40, T - 40:T]
     assert_close(to_np(full)[some], zo.token_nll(w.X[some], w.head, w.targets[some]), 1e-4, "tok_nll", atol=1e-4)
+    taken = zb.lib()["_ZN2zo18head_narrow_countsEii"]   # zo::head_narrow_counts(vocabulary tiles, workgroups), one bit per count
+    taken.restype = ctypes.c_uint64
+    assert [taken(274, 256) >> k & 1 for k in (2, 3, 5, 10)] == [1, 1, 1, 0]   # (10: the full call)
     for scored in (129, 256, 300, 640):
         keep = torch.from_numpy(np.sort(rng.choice(T, scored, replace=False))).to(DEV)
         g.targets = torch.full_like(targets, -1)
