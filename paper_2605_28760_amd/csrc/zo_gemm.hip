@@ -815,6 +815,16 @@ uint64_t head_narrow_counts(int n_tm, int workgroups) {
   return mask;
 }
 
+// Workgroups of a gathered call: one per wide tile of all T tokens, or one per narrow tile where those would be taken for all of them.
+// (They then take one round and the wide ones too, so no smaller number of scored tokens goes to wide tiles on the
+// larger grid, whose raster leaves XCDs out.)  Counted by wide tiles, 32000 x 4096 had 128 workgroups for 129 to 256 rows and
+// two narrow tiles were two rounds on them: 224 rows, all scored, 123 us -> 93.
+int head_gather_grid(int T, int n_tm) {
+  const int k = (T + kNarrowTokens - 1) / kNarrowTokens;
+  const int wide = gemm_grid(n_tm * ((k + 1) / 2)), narrow = gemm_grid(n_tm * min(k, 64));
+  return k < 64 && ((head_narrow_counts(n_tm, narrow) >> k) & 1) ? narrow : wide;
+}
+
 template <bool kStream, class Done>
 __device__ __forceinline__ void narrow_head(const HeadScoreArgs& p, int n_tm, int n_tok, char* lds, Done done) {
   constexpr int kCB = 2;
@@ -1043,7 +1053,7 @@ static hipError_t launch_head_variant(const HeadScoreArgs& a, hipStream_t st) {
   // the grid is sized for every token being scored; with fewer, the surplus workgroups find no tile
   const int n_tm = (a.vocab + BM - 1) / BM, n_tn = (a.T + BN - 1) / BN;
   const int tn_super = token_super_block(n_tn, (int64_t)a.T * a.d * 2);
-  const int grid = gemm_grid(n_tm * n_tn);
+  const int grid = kGather ? head_gather_grid(a.T, n_tm) : gemm_grid(n_tm * n_tn);
   hipLaunchKernelGGL(k_head_score<kGather>, dim3(grid), dim3(kThreads), kGemmLds, st, a, n_tm, tn_super, head_narrow_counts(n_tm, grid));
   return hipGetLastError();
 }

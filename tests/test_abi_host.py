@@ -268,3 +268,20 @@ def test_narrow_head_tiles_are_taken_only_where_their_rounds_are_at_most_half_as
             seen.add(rounds)
             assert (bits >> k & 1) == (rounds[1] <= 8 and rounds[1] <= 1.5 * rounds[0]), (n_tm, k, rounds)
     assert {(1, 1), (2, 3), (4, 6), (5, 7), (3, 5), (5, 8), (4, 7), (1, 2)} <= seen
+
+
+def test_head_grid_has_room_for_the_narrow_tiles_a_call_takes():
+    """A call whose tokens are all scored takes narrow tiles wherever its rounds on a full chip say so, whatever the number of
+    unscored rows beside them; where the grid is larger than the wide tiles, every count up to T takes narrow ones."""
+    taken, grid_of = zb.lib()["_ZN2zo18head_narrow_countsEii"], zb.lib()["_ZN2zo16head_gather_gridEii"]   # grid_of(T, vocabulary tiles)
+    taken.restype = C.c_uint64
+    up = lambda a, b: -(-a // b)
+    assert grid_of(224, 125) == 256 and taken(125, 256) >> 2 & 1
+    for n_tm in list(range(1, 300, 7)) + [594]:
+        for T in (1, 127, 128, 129, 224, 256, 257, 500, 900, 2000, 9000):
+            grid, k, wide = grid_of(T, n_tm), up(T, 128), min(256, up(n_tm * up(T, 256), 8) * 8)
+            assert grid % 8 == 0 and wide <= grid <= 256
+            if k < 64:
+                assert (taken(n_tm, grid) ^ taken(n_tm, 256)) >> k & 1 == 0
+            if grid > wide:
+                assert all(taken(n_tm, grid) >> j & 1 for j in range(1, k + 1))

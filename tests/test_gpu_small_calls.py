@@ -325,6 +325,32 @@ def test_some_hundred_scored_tokens_have_the_bits_of_a_full_call(d):
         assert int((g.tok_nll != 0).sum()) <= scored
 
 
+@pytest.mark.parametrize("T", [129, 224, 256, 500, 896])
+def test_scoring_every_token_on_narrow_tiles_has_the_bits_of_a_larger_call(T):
+    """A vocabulary of 36 tiles: 2 to 7 narrow token tiles, all in one round of a grid larger than the wide tiles need, against wide
+    ones (1500 tokens)."""
+    vocab, d, full = 9100, 192, 1500
+    taken, grid_of = zb.lib()["_ZN2zo18head_narrow_countsEii"], zb.lib()["_ZN2zo16head_gather_gridEii"]
+    taken.restype = ctypes.c_uint64
+    grid = grid_of(T, 36)
+    assert grid == 8 * (-(-36 * -(-T // 128) // 8)) and taken(36, grid) >> -(-T // 128) & 1 and not taken(36, grid_of(full, 36)) >> 12 & 1
+    rng = np.random.default_rng(T)
+    head = wl.as_bf16_values((rng.standard_normal((vocab, d)) / np.sqrt(d)).astype(np.float32))
+    X = wl.as_bf16_values(rng.standard_normal((full, d)).astype(np.float32))
+    targets = rng.integers(0, vocab, full).astype(np.int32)
+    nll = []
+    for n in (full, T):
+        w = wl.Workload("all", 9, "bf16", 4, 1e-3, np.array([0, n // 3, n], np.int32), np.array([0, 1], np.int32), np.zeros(2, np.int32),
+                        np.array([1, -1], np.float32), np.arange(1, dtype=np.uint64), [], True, X[:n], head, targets[:n], 0)
+        g = DeviceWorkload(w, DEV)
+        g.tok_nll.fill_(float("nan"))
+        g.score(H=g.X)
+        nll.append(g.tok_nll)
+    torch.cuda.synchronize()
+    assert torch.equal(nll[0][:T], nll[1])
+    assert_close(to_np(nll[1])[-40:], zo.token_nll(X[T - 40:T], head, targets[T - 40:T]), 1e-4, "tok_nll", atol=1e-4)
+
+
 @pytest.mark.parametrize("S,K", [(1025, 3), (1500, 70), (300, 70), (1024, 64)])
 def test_tables_of_many_sequences_and_directions(S, K):
     """More than 1024 sequences (tables in global memory instead of LDS) and more than 64 directions (slot lists searched
