@@ -780,12 +780,13 @@ hipError_t launch_probe_gemm_bf16(const ProbeGemmArgs& a, hipStream_t st) {
 // ---------------------------------------------------------------------------------------
 int head_vocab_tiles_bf16(int vocab) { return (vocab + BM - 1) / BM; }
 
-// The head against narrow tiles of 128 tokens.  For at most 128 tokens half of a 256-token tile's matrix instructions would be
-// padding, and the call is then bound by them (147 us for 128 tokens against 50272 x 5120) instead of by the weights' way from HBM.  A tile of
-// 256 vocabulary rows x 128 tokens: a wave still owns 128 rows of its tokens, so every sum has the order (and the
-// bits) of the wide tile; the 48 KiB of a stage leave room for three, with every K tile requested two periods ahead.
-// One tile per workgroup at a time.  Weights that do not fit the Infinity Cache are read with the
-// non-temporal hint (151936 x 4096: 336 -> 322 us; with it, 32000 x 1024, which stays there from call to call, 38.5 -> 40).
+// The head against narrow tiles of 128 tokens.  For at most 128 tokens half of a 256-token tile's matrix instructions would
+// be padding, and the call is then bound by them (147 us for 128 tokens against 50272 x 5120) instead of by the weights'
+// way from HBM.  A tile of 256 vocabulary rows x 128 tokens: a wave still owns 128 rows of its tokens, so every sum has
+// the order (and the bits) of the wide tile; the 48 KiB of a stage leave room for three, with every K tile requested two
+// periods ahead.  One tile per workgroup at a time.  With one token tile, weights that do not fit the Infinity Cache are
+// read with the non-temporal hint (151936 x 4096: 336 -> 322 us; with it, 32000 x 1024, which stays there from call to
+// call, 38.5 -> 40).
 constexpr int kNarrowTokens = BN / 2;
 constexpr int kNonTemporalLoad = 2;              // cache-policy operand of a buffer load: the nt bit
 constexpr int64_t kInfinityCache = 256ll << 20;
@@ -797,20 +798,28 @@ static_assert(3 * kNarrowStage + 4 * BN * 4 <= kGemmLds, "three stages and the e
 // against 32000 x 4096 1210 us wide, 1413 narrow).  A narrow round takes 0.60 to 0.66 of a wide one.  Whole calls, us, wide ->
 // narrow, by rounds (wide, narrow): (1, 1) 12288 x 4096 at 382 tokens 89 -> 59; (2, 2) 42140 x 4096 at 384 212 -> 141; (5, 4) 102044 x
 // 4096 at 382 413 -> 328; (4, 3) 50432 x 2048 at 580 161 -> 137; (5, 7) 151964 x 5120 at 324 655 -> 585; (2, 3) 32000 x 4096 at 708 210
-// -> 190; (4, 6) 50432 x 4096 at 836 380 -> 346, 50432 x 512 at 836 70.4 -> 67.2.  Not taken: (5, 8) 100764 x 4096 at 640 519 -> 489, but
-// 45212 x 5120 at 1406 577 -> 595 and 52636 x 4096 at 1152 449 -> 457; (3, 5) 151964 x 4096 at 196 370 -> 347, 32000 x 5120 at 1152 371
-// -> 370, 32000 x 512 at 1092 57 -> 59, 152064 x 5120 at 256 444 -> 453; (4, 7) 50332 x 4096 at 964 391 -> 390, 34204 x 4096 at 1604
-// 384 -> 420; (1, 2) 31900 x 4096 at 384 122 -> 132.
+// -> 190; (4, 6) 50432 x 4096 at 836 380 -> 346, 50432 x 512 at 836 70.4 -> 67.2.  Not taken: (4, 7) 50332 x 4096 at 964 391 -> 390, 34204 x
+// 4096 at 1604 384 -> 420; (1, 2) 31900 x 4096 at 384 122 -> 132.
+// Two classes lie on the line and go by what else differs: an odd number of tiles gains, as half of the last wide one is padding,
+// and rows of the weights 4 or 8 KiB apart, which the wide tile's loads feel more.  Eight for five (always odd) are taken up to
+// seven tiles and from K = 1536 up: 603 vocabulary tiles and three 2560 wide 360 -> 361, 4096 545 -> 503, 8192 1049 -> 955, but 1024
+// wide 158 -> 161, and nine 466 -> 469, eleven 577 -> 595.  Five for three up to five tiles, if odd from 3072 up (350 and three 3584
+// wide 290 -> 284, 5120 409 -> 410, 211 and five 8192 wide 581 -> 550, but 350 and three 2560 wide 221 -> 228), or at those pitches (594
+// and two 4096 wide 370 -> 341 for 140 tokens and 375 -> 361 for 256, 528 and two 2048 wide 201 -> 196; 313 and four 323 -> 322; 208 and six
+// 314 -> 318); elsewhere wide is ahead: 594 and two 2560 wide 253 -> 264, 5120 459 -> 467, 197 and six 5120 wide 387 -> 400.
 constexpr int kNarrowRounds = 8;
 
 // Bit k: k narrow tiles of tokens are taken.  (Worked out on the host for every number of them: the tokens to score are only known
-// on the device, and the divisions there cost a call 0.9 us.)
-uint64_t head_narrow_counts(int n_tm, int workgroups) {
+// on the device, and the divisions there cost a call 0.9 us.)  pitch: of the weights' rows, in bytes.
+uint64_t head_narrow_counts(int n_tm, int workgroups, int d, int pitch) {
   uint64_t mask = 2;
   for (int k = 2; k < 64; ++k) {
     const int64_t narrow = ((int64_t)n_tm * k + workgroups - 1) / workgroups;
     const int64_t wide = ((int64_t)n_tm * ((k + 1) / 2) + workgroups - 1) / workgroups;
-    if (narrow <= kNarrowRounds && narrow * 2 <= wide * 3) mask |= 1ull << k;
+    bool take = narrow * 2 <= wide * 3;
+    if (wide == 5 && narrow == 8) take = k <= 7 && d >= 1536;
+    if (wide == 3 && narrow == 5) take = k <= 5 && ((k % 2 == 1 && d >= 3072) || pitch == 4096 || pitch == 8192);
+    if (take && narrow <= kNarrowRounds) mask |= 1ull << k;
   }
   return mask;
 }
@@ -819,10 +828,10 @@ uint64_t head_narrow_counts(int n_tm, int workgroups) {
 // (They then take one round and the wide ones too, so no smaller number of scored tokens goes to wide tiles on the
 // larger grid, whose raster leaves XCDs out.)  Counted by wide tiles, 32000 x 4096 had 128 workgroups for 129 to 256 rows and
 // two narrow tiles were two rounds on them: 224 rows, all scored, 123 us -> 93.
-int head_gather_grid(int T, int n_tm) {
+int head_gather_grid(int T, int n_tm, int d, int pitch) {
   const int k = (T + kNarrowTokens - 1) / kNarrowTokens;
   const int wide = gemm_grid(n_tm * ((k + 1) / 2)), narrow = gemm_grid(n_tm * min(k, 64));
-  return k < 64 && ((head_narrow_counts(n_tm, narrow) >> k) & 1) ? narrow : wide;
+  return k < 64 && ((head_narrow_counts(n_tm, narrow, d, pitch) >> k) & 1) ? narrow : wide;
 }
 
 template <bool kStream, class Done>
@@ -1053,8 +1062,9 @@ static hipError_t launch_head_variant(const HeadScoreArgs& a, hipStream_t st) {
   // the grid is sized for every token being scored; with fewer, the surplus workgroups find no tile
   const int n_tm = (a.vocab + BM - 1) / BM, n_tn = (a.T + BN - 1) / BN;
   const int tn_super = token_super_block(n_tn, (int64_t)a.T * a.d * 2);
-  const int grid = kGather ? head_gather_grid(a.T, n_tm) : gemm_grid(n_tm * n_tn);
-  hipLaunchKernelGGL(k_head_score<kGather>, dim3(grid), dim3(kThreads), kGemmLds, st, a, n_tm, tn_super, head_narrow_counts(n_tm, grid));
+  const int pitch = (int)(a.ldw * 2);
+  const int grid = kGather ? head_gather_grid(a.T, n_tm, a.d, pitch) : gemm_grid(n_tm * n_tn);
+  hipLaunchKernelGGL(k_head_score<kGather>, dim3(grid), dim3(kThreads), kGemmLds, st, a, n_tm, tn_super, head_narrow_counts(n_tm, grid, a.d, pitch));
   return hipGetLastError();
 }
 

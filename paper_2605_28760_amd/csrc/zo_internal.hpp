@@ -177,8 +177,8 @@ struct HeadScoreArgs {
   const int32_t* rows; const int32_t* n_rows;
 };
 int head_vocab_tiles_bf16(int vocab);
-uint64_t head_narrow_counts(int n_tm, int workgroups);   // bit k: k narrow tiles of 128 scored tokens are taken
-int head_gather_grid(int T, int n_tm);                   // workgroups of a call that scores some of T tokens
+uint64_t head_narrow_counts(int n_tm, int workgroups, int d, int pitch);   // bit k: k narrow tiles of 128 scored tokens are taken
+int head_gather_grid(int T, int n_tm, int d, int pitch);                   // workgroups of a call that scores some of T tokens
 hipError_t launch_head_score_bf16(const HeadScoreArgs& a, hipStream_t st);
 
 // ---- zo_f32.hip (fp32 operands) ---------------------------------------------------------

@@ -254,34 +254,48 @@ def test_bank_update_multi_validation():
     assert C.sizeof(zb.zo_layer_bank) == 40
 
 
-def test_narrow_head_tiles_are_taken_only_where_their_rounds_are_at_most_half_as_many_again():
-    """Rounds of 256 workgroups, (wide, narrow): the classes that measured faster, the ones that did not, and a single tile always."""
-    taken = zb.lib()["_ZN2zo18head_narrow_countsEii"]   # zo::head_narrow_counts(vocabulary tiles, workgroups), one bit per count
-    taken.restype = C.c_uint64
+def _narrow_counts(n_tm, workgroups, d, pitch=None):
+    """zo::head_narrow_counts(vocabulary tiles, workgroups, K, bytes per weight row): one bit per number of narrow tiles"""
+    f = zb.lib()["_ZN2zo18head_narrow_countsEiiii"]
+    f.restype = C.c_uint64
+    return f(n_tm, workgroups, d, 2 * d if pitch is None else pitch)
+
+
+@pytest.mark.parametrize("d", [512, 2048, 2560, 3072, 4096, 5120])
+def test_narrow_head_tiles_are_taken_only_where_they_measured_faster(d):
+    """Rounds of 256 workgroups, (wide, narrow): at most half as many again; of the two classes beyond that some, by the number
+    of tiles, K and the pitch of the weights; a single tile always."""
     up = lambda a, b: -(-a // b)
     seen = set()
     for n_tm in range(1, 700):
-        bits = taken(n_tm, 256)
+        bits = _narrow_counts(n_tm, 256, d)
         assert bits & 3 == 2
         for k in range(2, 64):
-            rounds = up(n_tm * up(k, 2), 256), up(n_tm * k, 256)
+            wide, narrow = rounds = up(n_tm * up(k, 2), 256), up(n_tm * k, 256)
             seen.add(rounds)
-            assert (bits >> k & 1) == (rounds[1] <= 8 and rounds[1] <= 1.5 * rounds[0]), (n_tm, k, rounds)
+            want = narrow <= 8 and narrow <= 1.5 * wide
+            if rounds == (5, 8):
+                want = k <= 7 and d >= 1536
+            if rounds == (3, 5):
+                want = k <= 5 and ((k % 2 == 1 and d >= 3072) or d in (2048, 4096))
+            assert (bits >> k & 1) == want, (n_tm, k, rounds)
     assert {(1, 1), (2, 3), (4, 6), (5, 7), (3, 5), (5, 8), (4, 7), (1, 2)} <= seen
+    # the pitch counts, not the width
+    assert _narrow_counts(594, 256, 4096, 8192) >> 2 & 1 and not _narrow_counts(594, 256, 4096, 8320) >> 2 & 1
 
 
 def test_head_grid_has_room_for_the_narrow_tiles_a_call_takes():
     """A call whose tokens are all scored takes narrow tiles wherever its rounds on a full chip say so, whatever the number of
     unscored rows beside them; where the grid is larger than the wide tiles, every count up to T takes narrow ones."""
-    taken, grid_of = zb.lib()["_ZN2zo18head_narrow_countsEii"], zb.lib()["_ZN2zo16head_gather_gridEii"]   # grid_of(T, vocabulary tiles)
-    taken.restype = C.c_uint64
+    grid_of = zb.lib()["_ZN2zo16head_gather_gridEiiii"]   # zo::head_gather_grid(T, vocabulary tiles, K, bytes per weight row)
     up = lambda a, b: -(-a // b)
-    assert grid_of(224, 125) == 256 and taken(125, 256) >> 2 & 1
+    assert grid_of(224, 125, 4096, 8192) == 256 and _narrow_counts(125, 256, 4096) >> 2 & 1
     for n_tm in list(range(1, 300, 7)) + [594]:
-        for T in (1, 127, 128, 129, 224, 256, 257, 500, 900, 2000, 9000):
-            grid, k, wide = grid_of(T, n_tm), up(T, 128), min(256, up(n_tm * up(T, 256), 8) * 8)
-            assert grid % 8 == 0 and wide <= grid <= 256
-            if k < 64:
-                assert (taken(n_tm, grid) ^ taken(n_tm, 256)) >> k & 1 == 0
-            if grid > wide:
-                assert all(taken(n_tm, grid) >> j & 1 for j in range(1, k + 1))
+        for d in (1024, 4096, 5120):
+            for T in (1, 127, 128, 129, 224, 256, 257, 500, 900, 2000, 9000):
+                grid, k, wide = grid_of(T, n_tm, d, 2 * d), up(T, 128), min(256, up(n_tm * up(T, 256), 8) * 8)
+                assert grid % 8 == 0 and wide <= grid <= 256
+                if k < 64:
+                    assert (_narrow_counts(n_tm, grid, d) ^ _narrow_counts(n_tm, 256, d)) >> k & 1 == 0
+                if grid > wide:
+                    assert all(_narrow_counts(n_tm, grid, d) >> j & 1 for j in range(1, k + 1))

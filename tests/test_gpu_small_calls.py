@@ -311,9 +311,9 @@ def test_some_hundred_scored_tokens_have_the_bits_of_a_full_call(d):
     full, targets = g.tok_nll.clone(), g.targets
     some = np.r_[0:40, T - 40:T]
     assert_close(to_np(full)[some], zo.token_nll(w.X[some], w.head, w.targets[some]), 1e-4, "tok_nll", atol=1e-4)
-    taken = zb.lib()["_ZN2zo18head_narrow_countsEii"]   # zo::head_narrow_counts(vocabulary tiles, workgroups), one bit per count
+    taken = zb.lib()["_ZN2zo18head_narrow_countsEiiii"]   # zo::head_narrow_counts(vocabulary tiles, workgroups, K, pitch), one bit per count
     taken.restype = ctypes.c_uint64
-    assert [taken(274, 256) >> k & 1 for k in (2, 3, 5, 10)] == [1, 1, 1, 0]   # (10: the full call)
+    assert [taken(274, 256, d, 2 * d) >> k & 1 for k in (2, 3, 5, 10)] == [1, 1, 1, 0]   # (10: the full call)
     for scored in (129, 256, 300, 640):
         keep = torch.from_numpy(np.sort(rng.choice(T, scored, replace=False))).to(DEV)
         g.targets = torch.full_like(targets, -1)
@@ -330,10 +330,11 @@ def test_scoring_every_token_on_narrow_tiles_has_the_bits_of_a_larger_call(T):
     """A vocabulary of 36 tiles: 2 to 7 narrow token tiles, all in one round of a grid larger than the wide tiles need, against wide
     ones (1500 tokens)."""
     vocab, d, full = 9100, 192, 1500
-    taken, grid_of = zb.lib()["_ZN2zo18head_narrow_countsEii"], zb.lib()["_ZN2zo16head_gather_gridEii"]
+    taken, grid_of = zb.lib()["_ZN2zo18head_narrow_countsEiiii"], zb.lib()["_ZN2zo16head_gather_gridEiiii"]
     taken.restype = ctypes.c_uint64
-    grid = grid_of(T, 36)
-    assert grid == 8 * (-(-36 * -(-T // 128) // 8)) and taken(36, grid) >> -(-T // 128) & 1 and not taken(36, grid_of(full, 36)) >> 12 & 1
+    K, grid = (d, 2 * d), grid_of(T, 36, d, 2 * d)
+    assert grid == 8 * (-(-36 * -(-T // 128) // 8)) and taken(36, grid, *K) >> -(-T // 128) & 1
+    assert not taken(36, grid_of(full, 36, *K), *K) >> 12 & 1
     rng = np.random.default_rng(T)
     head = wl.as_bf16_values((rng.standard_normal((vocab, d)) / np.sqrt(d)).astype(np.float32))
     X = wl.as_bf16_values(rng.standard_normal((full, d)).astype(np.float32))
