@@ -162,11 +162,21 @@ __device__ __forceinline__ int wave_seq_of_row(const int32_t* cu, int S, int t, 
 }
 
 // The side K tiles of every token tile of the bf16 GEMM.  A tile's slot list names the distinct directions of the
-// sequences that intersect it, in order of first appearance, SPD slots each.  One workgroup, a wave per tile: its lanes look
-// at 64 of the tile's sequences at a time and take the directions off one by one.  Where a tile's slots lie needs no
-// knowledge of the tiles before it: with s the first sequence of tile i, at most s + i (tile, sequence) intersections do.
+// sequences that intersect it, in order of first appearance, SPD slots each.  One workgroup.  Where a tile's slots lie needs
+// no knowledge of the tiles before it: with s the first sequence of tile i, at most s + i (tile, sequence) intersections do.
+//
+// Up to kFewTiles tiles are taken one by a wave, whose lanes share the searches and the sequences: the shortest chain.  A
+// wave needs 0.4 us and more for a tile, so with more tiles (kMany) a thread searches for each, and walks its sequences too
+// unless a tile has many of them (with more than 64 directions, fewer: each is looked up in the tile's list).  Linears of 64 x
+// 64, us, a wave for each tile / a thread: up to 64 directions, 36 tiles of 8 sequences 16.5 / 16.8; 64 of 1 24.0 / 21.6, of 8 20.7 /
+// 19.8, of 16 20.4 / 21.5; 128 of 16 28.4 / 26.7, of 32 30.4 / 32.9; 512 of one sequence in four 63 / 42.6, of 32 90 / 76, of 64 98 /
+// 108; 1024 of 16 160 / 99; beyond 64 directions, 64 of 8 24.2 / 25.3; 128 of 8 30.2 / 27.8, of 16 36.5 / 39.4; 1024 of 16 232 / 171,
+// of 64 585 / 1052.  (The chain of a small call is in a kernel of its own: beside this code it took 0.4 us longer.)
+constexpr int kFewTiles = 32;
+
+template <bool kMany>
 __device__ __forceinline__ void tile_tables_block(const BatchDev& b, const SeqTables& t) {
-  constexpr int kCached = 1024;   // sequences whose bounds and kinds are kept in LDS
+  constexpr int kCached = kMany ? 4096 : 1024;   // sequences whose bounds and kinds are kept in LDS
   __shared__ int s_wave[16], s_cu[kCached + 1], s_kind[kCached];
   __shared__ int s_tile[1024], s_slot0[1024];   // directions of a tile (bit 31: it holds a candidate's row), its first slot
   __shared__ int s_dirs[16][kTileN];    // a wave's tile: the directions met so far
@@ -178,10 +188,15 @@ __device__ __forceinline__ void tile_tables_block(const BatchDev& b, const SeqTa
     candidate_kind(b.seq_cand[s], b.C, b.K, 1.0f, b.cand_dir, b.cand_sign, kind, scale);
     return kind;
   };
-  if (cached && tid < b.S) {
-    s_cu[tid] = b.cu[tid];
-    if (tid == b.S - 1) s_cu[b.S] = b.cu[b.S];
-    s_kind[tid] = kind_of(tid);
+  auto keep = [&](int s) {
+    s_cu[s] = b.cu[s];
+    if (s == b.S - 1) s_cu[b.S] = b.cu[b.S];
+    s_kind[s] = kind_of(s);
+  };
+  if constexpr (kMany) {
+    for (int s = tid; cached && s < b.S; s += 1024) keep(s);
+  } else {
+    if (cached && tid < b.S) keep(tid);
   }
   __syncthreads();
   const int32_t* cu = cached ? s_cu : b.cu;
@@ -190,31 +205,79 @@ __device__ __forceinline__ void tile_tables_block(const BatchDev& b, const SeqTa
   int kt_carry = 0;
   for (int base = 0; base < t.n_tn; base += 1024) {
     const int n_here = min(t.n_tn - base, 1024);
-    for (int i = wave; i < n_here; i += 16) {
-      const int tn = base + i, t0 = tn * kTileN, t1 = min(b.T, t0 + kTileN);
-      const int s_first = wave_seq_of_row(cu, b.S, t0, lane), s_last = wave_seq_of_row(cu, b.S, t1 - 1, lane);
-      const int slot0 = (by_sequence ? s_first + tn : tn * per_tile) * t.SPD;
-      int q = 0;
-      bool any = false;
-      for (int s0 = s_first; s0 <= s_last; s0 += 64) {
-        const int s = min(s0 + lane, s_last);
-        const bool rows = s0 + lane <= s_last && min(cu[s + 1], t1) > max(cu[s], t0);
-        const int kind = rows ? (cached ? s_kind[s] : kind_of(s)) : kKindForeground;
-        any |= __ballot(kind >= kKindCentre) != 0;
-        uint64_t left = __ballot(kind >= 0);
-        for (int j = 0; j < (s0 > s_first ? q : 0); ++j) left &= ~__ballot(kind == s_dirs[wave][j]);
-        while (left) {
-          const int k = __builtin_amdgcn_readlane(kind, __ffsll((unsigned long long)left) - 1);
-          left &= ~__ballot(kind == k);
-          if (slot0 + (q + 1) * t.SPD > t.slot_cap) break;   // cannot happen: the cap is a bound
-          if (lane < t.SPD) t.tile_slots[slot0 + q * t.SPD + lane] = k * t.SPD + lane;
-          s_dirs[wave][q++] = k;   // (every lane the same value)
+    const int tn_own = base + tid;   // a thread's tile: its first and last sequence
+    int s_first = 0, s_last = 0;
+    bool by_wave = true;
+    if constexpr (kMany) {
+      if (tid < n_here) {
+        const int t0 = tn_own * kTileN;
+        s_first = seq_of_row(cu, b.S, t0);
+        s_last = seq_of_row(cu, b.S, min(b.T, t0 + kTileN) - 1);
+        s_slot0[tid] = s_first;
+        s_tile[tid] = s_last;
+      }
+      const int most = b.K > 64 ? min(n_here / 12, 20) : min(n_here / 6 + 1, 60);
+      by_wave = __syncthreads_or(s_last - s_first >= most);
+    }
+    if (by_wave) {
+      // the wave's lanes look at 64 of the tile's sequences at a time and tell one by one which bring a direction
+      for (int i = wave; i < n_here; i += 16) {
+        const int tn = base + i, t0 = tn * kTileN, t1 = min(b.T, t0 + kTileN);
+        const int first = kMany ? __builtin_amdgcn_readfirstlane(s_slot0[i]) : wave_seq_of_row(cu, b.S, t0, lane);
+        const int last = kMany ? __builtin_amdgcn_readfirstlane(s_tile[i]) : wave_seq_of_row(cu, b.S, t1 - 1, lane);
+        const int slot0 = (by_sequence ? first + tn : tn * per_tile) * t.SPD;
+        int q = 0;
+        bool any = false;
+        for (int s0 = first; s0 <= last; s0 += 64) {
+          const int s = min(s0 + lane, last);
+          const bool rows = s0 + lane <= last && min(cu[s + 1], t1) > max(cu[s], t0);
+          const int kind = rows ? (cached ? s_kind[s] : kind_of(s)) : kKindForeground;
+          any |= __ballot(kind >= kKindCentre) != 0;
+          uint64_t left = __ballot(kind >= 0);
+          for (int j = 0; j < (s0 > first ? q : 0); ++j) left &= ~__ballot(kind == s_dirs[wave][j]);
+          uint64_t first_of = 0;   // lanes whose sequence brings a direction
+          while (left) {
+            const int at = __ffsll((unsigned long long)left) - 1;
+            first_of |= 1ull << at;
+            left &= ~__ballot(kind == __builtin_amdgcn_readlane(kind, at));
+          }
+          const int nth = q + __popcll(first_of & ((1ull << lane) - 1ull));
+          if (((first_of >> lane) & 1) && slot0 + (nth + 1) * t.SPD <= t.slot_cap) {   // (the cap is a bound)
+            s_dirs[wave][nth] = kind;
+            for (int blk = 0; blk < t.SPD; ++blk) t.tile_slots[slot0 + nth * t.SPD + blk] = kind * t.SPD + blk;
+          }
+          q += __popcll(first_of);
+        }
+        if (lane == 0) {
+          s_tile[i] = q | (any ? 1 << 31 : 0);
+          s_slot0[i] = slot0;
         }
       }
-      if (lane == 0) {
-        s_tile[i] = q | (any ? 1 << 31 : 0);
-        s_slot0[i] = slot0;
+    } else if (tid < n_here) {
+      const int t0 = tn_own * kTileN, t1 = min(b.T, t0 + kTileN);
+      const int slot0 = (by_sequence ? s_first + tn_own : tn_own * per_tile) * t.SPD;
+      int q = 0;
+      bool any = false;
+      uint64_t met = 0;   // directions met so far, when there are at most 64
+      for (int s = s_first; s <= s_last; ++s) {
+        if (min(cu[s + 1], t1) <= max(cu[s], t0)) continue;   // no row of s in this tile
+        const int kind = cached ? s_kind[s] : kind_of(s);
+        any |= kind >= kKindCentre;
+        if (kind < 0) continue;
+        bool seen = false;
+        if (b.K <= 64) {
+          seen = (met >> kind) & 1;
+          met |= 1ull << kind;
+        } else {
+          for (int j = 0; j < q && !seen; ++j) seen = t.tile_slots[slot0 + j * t.SPD] == kind * t.SPD;
+        }
+        if (!seen && slot0 + (q + 1) * t.SPD <= t.slot_cap) {
+          for (int blk = 0; blk < t.SPD; ++blk) t.tile_slots[slot0 + q * t.SPD + blk] = kind * t.SPD + blk;
+          ++q;
+        }
       }
+      s_tile[tid] = q | (any ? 1 << 31 : 0);
+      s_slot0[tid] = slot0;
     }
     __syncthreads();
     const int tn = base + tid, met = tid < n_here ? s_tile[tid] : 0;   // (n_here <= 64: only the first wave's scan counts)
@@ -416,10 +479,11 @@ struct ProbePrepArgs {
   int nb_tok, nb_U, nb_Vt, nb_P, nb_Vbt, vbt_tiles_n;
 };
 
+template <bool kMany>   // more than kFewTiles token tiles
 __global__ __launch_bounds__(1024) void k_probe_prep(ProbePrepArgs a) {
   int blk = blockIdx.x;
   if (blk == 0) { seq_tables_block(a.b, a.eps, a.tabs); return; }
-  if (blk == 1) { tile_tables_block(a.b, a.tabs); return; }
+  if (blk == 1) { tile_tables_block<kMany>(a.b, a.tabs); return; }
   blk -= 2;
   if (blk < a.nb_tok) { tok_index_at(a.b, blk * 1024 + threadIdx.x, a.tabs.tok_seq, nullptr); return; }
   blk -= a.nb_tok;
@@ -461,7 +525,8 @@ hipError_t launch_probe_prep_bf16(const BatchDev& b, float eps, const SeqTables&
   a.vbt_tiles_n = (n + 31) / 32;
   a.nb_Vbt = Rp == 0 ? 0 : tabs.frag_major ? blocks((int64_t)(n / 8) * Rp) : a.vbt_tiles_n * ((Rp + 31) / 32);
   const int64_t total = 2 + (int64_t)a.nb_tok + a.nb_U + a.nb_Vt + a.nb_P + a.nb_Vbt;
-  hipLaunchKernelGGL(k_probe_prep, dim3((unsigned)total), dim3(1024), 0, st, a);
+  if (tabs.n_tn > kFewTiles) hipLaunchKernelGGL(k_probe_prep<true>, dim3((unsigned)total), dim3(1024), 0, st, a);
+  else hipLaunchKernelGGL(k_probe_prep<false>, dim3((unsigned)total), dim3(1024), 0, st, a);
   return hipGetLastError();
 }
 

@@ -366,6 +366,35 @@ def test_tables_of_many_sequences_and_directions(S, K):
     assert_close(to_np(y), oracle_layer(w, 0, w.layers[0].X, out_dtype="f32"), 2e-2, "Y")
 
 
+# 33 tiles and more have their tables built by threads or, where a tile has many sequences, by waves: on both sides of that line
+# with few and with more than 64 directions, more sequences than are kept in LDS, more tiles than a workgroup has threads
+@pytest.mark.parametrize("tiles,per_tile,K", [(33, 0.3, 3), (33, 1, 64), (33, 12, 65), (40, 30, 20), (64, 8, 70), (64, 3, 200), (64, 90, 3),
+                                              (200, 30, 17), (200, 100, 16), (1030, 0.6, 2), (1090, 1.5, 90)])
+def test_tables_of_many_token_tiles(tiles, per_tile, K):
+    rng = np.random.default_rng(tiles + K)
+    lens, rows = [], (tiles - 1) * 256 + 100
+    mean = 256 / per_tile
+    while rows > 0:
+        lens.append(int(min(rows, rng.integers(0, 2 * mean + 1))))
+        rows -= lens[-1]
+    w = _layer(tiles, lens, rng.integers(-1, 2 * K + 1, len(lens)).tolist(), 64, 64, 4, 16, 0, False)
+    w.cand_dir = np.append(np.repeat(np.arange(K, dtype=np.int32), 2), np.int32(-1))
+    w.cand_sign = np.append(np.tile(np.array([1, -1], np.float32), K), np.float32(0))
+    w.dir_seed = np.arange(K, dtype=np.uint64) + np.uint64(5)
+    y = DeviceWorkload(w, DEV, out_dtype="f32").probe_linear(0)
+    # rows of every tile: its first and last ones and some between
+    some = np.unique(np.minimum(np.arange(tiles)[:, None] * 256 + np.array([0, 1, 77, 130, 255]), w.T - 1))
+    want = oracle_layer(w, 0, w.layers[0].X, rows=some, out_dtype="f32")
+    assert_close(to_np(y[torch.from_numpy(some).to(DEV)]), want, 2e-2, "Y")
+    # and all rows against calls of a few tiles each
+    cuts = np.searchsorted(w.cu_seqlens, np.arange(0, w.T, 5000))
+    for a, b in list(zip(cuts, np.append(cuts[1:], len(lens))))[::max(1, len(cuts) // 8)]:
+        if w.cu_seqlens[b] > w.cu_seqlens[a]:
+            sub = wl.subset_sequences(w, np.arange(a, b))
+            got = DeviceWorkload(sub, DEV, out_dtype="f32").probe_linear(0)
+            assert torch.equal(got, y[int(w.cu_seqlens[a]):int(w.cu_seqlens[b])])
+
+
 @pytest.mark.parametrize("n,R", [(64, 0), (2560, 40)])
 def test_side_term_of_a_batch_changed_on_the_device(n, R):
     """The host's copies of the tables decide which side-down pass a call takes, never its result: a handle whose device tables were changed (one candidate sequence becomes 40) gives what a new handle gives."""
