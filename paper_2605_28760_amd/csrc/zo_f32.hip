@@ -136,6 +136,42 @@ struct FusedLds {
   }
 };
 
+// Products of 16 side columns and 16 rows of X over the input width: two chains of two instructions (eight products) per 16
+// columns, added, and these sums in double precision.  One chain over the width, the instruction's own accumulation, was three times as
+// far from 64-bit sums as a wave's 64 partial sums had been at 256 columns, and eight times at 16384: relative error of the
+// term alone, rank 4, at 64 / 256 / 2048 / 16384 columns 0.9, 1.3, 3.0e-7 (64 partial sums, from 256 on); 2.9, 8.1, 23e-7 (one chain);
+// 0.8e-7 throughout (this).  It costs a fused call 1 to 4 %, up to 0.4 us of 28.
+template <int kTogether>   // blocks of 16 columns whose instructions may overlap: one takes 16 registers
+struct SideSum {
+  double sum[4] = {0.0, 0.0, 0.0, 0.0};
+
+  // a, x: a lane's four values of the 16-column block b (zeros past the end)
+  template <class A, class X>
+  __device__ __forceinline__ void add(A a, X x) {
+#pragma unroll
+    for (int b0 = 0; b0 < 4; b0 += kTogether) {
+      f32x4 block[kTogether];
+#pragma unroll
+      for (int j = 0; j < kTogether; ++j) {
+        const f32x4 va = a(b0 + j), vx = x(b0 + j), zero = {0.f, 0.f, 0.f, 0.f};
+        f32x4 lo = __builtin_amdgcn_mfma_f32_16x16x4f32(va[0], vx[0], zero, 0, 0, 0);
+        f32x4 hi = __builtin_amdgcn_mfma_f32_16x16x4f32(va[2], vx[2], zero, 0, 0, 0);
+        lo = __builtin_amdgcn_mfma_f32_16x16x4f32(va[1], vx[1], lo, 0, 0, 0);
+        hi = __builtin_amdgcn_mfma_f32_16x16x4f32(va[3], vx[3], hi, 0, 0, 0);
+        block[j] = lo + hi;
+      }
+      // (summed here: left alone, the sums are put off and their operands take 130 registers more)
+#pragma unroll
+      for (int j = 0; j < kTogether; ++j) asm volatile("" : "+v"(block[j]));
+#pragma unroll
+      for (int j = 0; j < kTogether; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += (double)block[j][e];
+    }
+  }
+  __device__ __forceinline__ f32x4 total() const { return f32x4{(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]}; }
+};
+
 template <class C, int TM, int TN, int KC>
 struct SideF32 {
   static constexpr int kWaves = 4, kThreads = kWaves * 64;
@@ -228,9 +264,7 @@ struct SideF32 {
       }
     }
     __syncthreads();
-    f32x4 acc[kItems];
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    SideSum<TM == 32 ? 2 : 4> sum[kItems];
     for (int k0 = 0; k0 < n; k0 += KC) {
       if (k0 > 0) __syncthreads();
       fill(tid, k0);
@@ -242,11 +276,10 @@ struct SideF32 {
         const float* fa = rows + (blk * 16 + (lane & 15)) * C::kPitch + (lane >> 4) * 4;
         const float* fb = slab_x + (cb * 16 + (lane & 15)) * C::kPitch + (lane >> 4) * 4;
 #pragma unroll
-        for (int kb = 0; kb < KC / 16; ++kb) {
-          if (k0 + kb * 16 >= n) break;
-          const f32x4 a = *reinterpret_cast<const f32x4*>(fa + kb * 16), x = *reinterpret_cast<const f32x4*>(fb + kb * 16);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], x[k], acc[i], 0, 0, 0);
+        for (int k64 = 0; k64 < KC; k64 += 64) {
+          if (k0 + k64 >= n) break;
+          sum[i].add([&](int b) { return *reinterpret_cast<const f32x4*>(fa + k64 + b * 16); },
+                     [&](int b) { return *reinterpret_cast<const f32x4*>(fb + k64 + b * 16); });
         }
       }
     }
@@ -271,9 +304,10 @@ struct SideF32 {
       const bool bank = d >= b.K;
       const int j0 = (bank ? blk - b.K * rb : blk - d * rb) * 16 + 4 * (lane >> 4);
       if (bank ? kind < kKindCentre : kind != d) continue;
+      const f32x4 acc = sum[i].total();
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (j0 + e < (bank ? p.R : p.r)) lds[at.cols + tl * (p.r + p.R) + (bank ? p.r : 0) + j0 + e] = bank ? acc[i][e] : acc[i][e] * scale;
+        if (j0 + e < (bank ? p.R : p.r)) lds[at.cols + tl * (p.r + p.R) + (bank ? p.r : 0) + j0 + e] = bank ? acc[e] : acc[e] * scale;
     }
   }
 };
@@ -287,11 +321,11 @@ bool whole_quads(const void* a, int64_t lda, const void* b, int64_t ldb, int K) 
 // kSideDirs; further ones follow in turn), operands straight from memory, 256 columns of X asked for together: such a call is
 // a chain of round trips.  Linear and scoring, a wave per row and 8 columns on the vector ALU -> this: 3671 rows, 632 wide, 8 + 33
 // columns 225 -> 128 us; 2010 rows, 258 wide, four directions, 1 + 33 columns 80 -> 67; 252 rows, 366 wide, 8 + 33 46 -> 42.5.
-// The chain of products is that of SideF32: the same bits.
+// Summed as in SideF32: the same bits.
 constexpr int kSideDirs = 4;
 
 template <bool kVec>
-__global__ __launch_bounds__(64) void k_side_f32(ProbeF32Args p) {
+__global__ __launch_bounds__(64, 2) void k_side_f32(ProbeF32Args p) {
   constexpr int U = 16;                  // blocks of 16 columns of X per trip
   const int NC = p.r + p.R, rb = (p.r + 15) / 16;
   const int lane = threadIdx.x, g = lane >> 4, col = lane & 15;
@@ -315,7 +349,7 @@ __global__ __launch_bounds__(64) void k_side_f32(ProbeF32Args p) {
     const float* v = dir ? p.Vf + (int64_t)k * p.n * p.r + min(j, p.r - 1) : p.Vb + min(j, p.R - 1);
     const int64_t pitch = dir ? p.r : p.R_cap;
     const bool real = j < (dir ? p.r : p.R);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    SideSum<2> sum;
     for (int k0 = 0; k0 < p.n; k0 += 16 * U) {
       f32x4 a[U], b[U];
 #pragma unroll
@@ -334,17 +368,21 @@ __global__ __launch_bounds__(64) void k_side_f32(ProbeF32Args p) {
 #pragma unroll
       for (int u = 0; u < U; ++u) asm volatile("" : "+v"(a[u]), "+v"(b[u]));
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int u = 0; u < U; u += 4) {
         if (k0 + u * 16 >= p.n) break;
+        auto in = [&](int at, bool also, const f32x4& v) {   // what lies past the end of the row, or of the columns, counts as zero
+          f32x4 z;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool in = k0 + u * 16 + g * 4 + i < p.n;
-          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in && real ? a[u][i] : 0.f, in ? b[u][i] : 0.f, acc, 0, 0, 0);
-        }
+          for (int i = 0; i < 4; ++i) z[i] = also && at + i < p.n ? v[i] : 0.f;
+          return z;
+        };
+        sum.add([&](int blk) { return in(k0 + (u + blk) * 16 + g * 4, real, a[u + blk]); },
+                [&](int blk) { return in(k0 + (u + blk) * 16 + g * 4, true, b[u + blk]); });
       }
     }
     if ((mine >> lane) & 1) {
       const float scale = dir ? p.seq_scale[s] : 1.0f;
+      const f32x4 acc = sum.total();
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int jj = j0 + 4 * g + e;

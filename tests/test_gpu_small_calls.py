@@ -223,6 +223,34 @@ def test_fp32_linear_of_inputs_without_columns(m, act):
     assert_close(to_np(Y), np.broadcast_to(to_np(want), (T, m_out)), 1e-6, "Y")
 
 
+@pytest.mark.parametrize("n", [64, 256, 1000, 2048])
+@pytest.mark.parametrize("K,r", [(1, 4), (4, 16)])
+def test_fp32_side_term_alone_against_64_bits(n, K, r):
+    """W = 0: the side term as it is summed along with the products (one direction) and in a launch of its own (four).  Rounding
+    errors are independent, so their squares add: a rounding of a partial sum counts by its share of the sum, and is at most
+    2^-24 (uniform: / sqrt(3) in the root mean square).  64 partial sums of the width, paired off, count n/64 / 2 + 6.5, the scale 1,
+    a chain of r products (r + 1) / 2; one chain over the width would count n / 2."""
+    m, T = 96, 1024
+    cu = (np.arange(2 * K + 1) * (T // (2 * K))).astype(np.int32)
+    seeds = np.arange(K, dtype=np.uint64) + np.uint64(300 + n)
+    b = DeviceBatch(cu, np.arange(2 * K, dtype=np.int32), np.repeat(np.arange(K, dtype=np.int32), 2), np.tile(np.array([1, -1], np.float32), K), seeds, DEV)
+    X = torch.randn(T, n, device=DEV, generator=torch.Generator(device=DEV).manual_seed(n))
+    W, Y = torch.zeros(m, n, device=DEV), torch.empty(T, m, device=DEV)
+    n_ws = zb.zo_probe_linear_workspace_bytes(T, b.S, b.K, m, n, r, 0, zb.ZO_F32)
+    ws = torch.empty(n_ws, device=DEV, dtype=torch.uint8)
+    zb.zo_probe_linear(b.struct, X, n, W, n, None, m, n, zb.ZO_F32, r, 0.5, 2, None, 0, Y, m, zb.ZO_F32, ws, n_ws)
+    U, V = torch.empty(m, r, device=DEV), torch.empty(n, r, device=DEV)   # (the device's own factors: their rounding is not at issue)
+    want = np.empty((T, m))
+    x = X.cpu().numpy().astype(np.float64)
+    for s in range(2 * K):
+        zb.zo_factor_fill(int(seeds[s // 2]), 2, m, r, zb.ZO_F32, U)
+        zb.zo_factor_fill(int(seeds[s // 2]), 3, n, r, zb.ZO_F32, V)
+        u, v = (t.cpu().numpy().astype(np.float64) for t in (U, V))
+        want[cu[s]:cu[s + 1]] = (0.5 - s % 2) * (x[cu[s]:cu[s + 1]] @ v) @ u.T
+    err = np.linalg.norm(to_np(Y).astype(np.float64) - want) / np.linalg.norm(want)
+    assert err <= 2.0 ** -24 / np.sqrt(3) * np.sqrt(n / 128 + 6.5 + 1 + (r + 1) / 2), err
+
+
 @pytest.mark.parametrize("lens", [[1, 31, 32, 33, 64, 0, 96], [127, 128, 129], [160, 161, 255, 257, 1]])
 @pytest.mark.parametrize("scale,grow", [(128 ** -0.5, 0.0), (-(128 ** -0.5), 0.0), (0.0, 0.0), (0.1, 0.02), (0.1, -0.02)])
 def test_attention_at_the_edges_of_its_steps(lens, scale, grow):
