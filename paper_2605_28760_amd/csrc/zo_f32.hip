@@ -317,7 +317,7 @@ bool whole_quads(const void* a, int64_t lda, const void* b, int64_t ldb, int K) 
 }
 
 // Tside[t, :] = [ s_t eps X[t,:] V_{k_t} | X[t,:] Vb ] where the row has such a term, for the calls whose side columns do not
-// ride along with the products (fused_f32).  A wave per 16 rows, 16 columns and direction among the rows (the first
+// ride along with the products (f32_side_rides_along).  A wave per 16 rows, 16 columns and direction among the rows (the first
 // kSideDirs; further ones follow in turn), operands straight from memory, 256 columns of X asked for together: such a call is
 // a chain of round trips.  Linear and scoring, a wave per row and 8 columns on the vector ALU -> this: 3671 rows, 632 wide, 8 + 33
 // columns 225 -> 128 us; 2010 rows, 258 wide, four directions, 1 + 33 columns 80 -> 67; 252 rows, 366 wide, 8 + 33 46 -> 42.5.
@@ -543,19 +543,29 @@ int64_t tiles(int rows, int tm, int cols, int tn) { return (int64_t)((rows + tm 
 
 }  // namespace
 
-// Whether a call's side columns ride along with its products, in one launch.  (No result depends on it.)  A tile draws and
-// multiplies the columns of all directions, whichever its tokens have, so the line lies at three blocks of 16; linear and
-// scoring of a layer, us, three launches -> one: one block, 768 rows, 256 wide 31 -> 26; two, 450 rows, 432 wide 39 -> 33; three,
-// 1080 rows, 209 wide 44.8 -> 42.0, 540 rows, 510 wide 79.4 -> 78.4; four, 872 rows, 344 wide 57.7 -> 66.8, 4650 rows, 392 wide 70 -> 78.
-// Tiles of 32x32 have to be resident all at once (two or three per compute unit, by their LDS): in a second round the start of a
-// tile's side waves shows (1998 rows, 343 wide, three blocks 75 -> 80; 1466 rows, 560 wide, one block 67.7 -> 69.2).
-// Inputs without columns go the other way: the factors are drawn with the slabs of X, of which there are none.
-static bool fused_f32(const ProbeF32Args& a, bool large_tiles) {
-  const int64_t blocks = (int64_t)a.batch.K * ((a.r + 15) / 16) + (a.R + 15) / 16;
-  if (!a.has_side || a.n == 0 || blocks > kFusedBlocks || a.r + a.R > kFusedColumns || a.batch.S > kFusedTable || a.batch.C > kFusedTable) return false;
-  if (large_tiles) return true;
-  const int64_t lds = sizeof(float) * (int64_t)FusedLds<TileF32<32, 32, 2, 2, 128>, 32, 32>(a).end;
-  return tiles(a.m, 32, a.T, 32) <= compute_units() * (160 * 1024 / lds);
+// Whether a call's side columns ride along with its products, in one launch.  (No result depends on it.)  It saves two launches,
+// 4 to 7 us; every tile draws and multiplies the columns of all directions, whichever its tokens have, and converts the
+// bank's.  That has to stay under the products: the line is drawn by tiles per compute unit (one at least) x input columns x
+// drawn and bank columns (read one by one: twice), lower with more blocks of 16; beyond two tiles of 64x64 per unit, or the tiles
+// of 32x32 that are resident by their LDS, the start of a tile's side waves shows as well.  Linear and scoring of a layer, us, one
+// launch / three: one block: 1024 rows, 256 wide (product 1024) 24.1 / 28.7; 510, 621 (7762) 79.2 / 85.9; 3168, 585 (11426) 118.4 / 126.8;
+// 4096, 640, 2.5 tiles of 64x64 90.5 / 84.6; 4096, 1024, 4 tiles 157 / 138; 8192, 2048 1028 / 758.  Two: 1024, 256 (4096) 26.3 / 29.6; 424, 472
+// with 4 + 8 columns (9440) 35.4 / 37.7; 4516, 381 (10144) 115 / 122; 1024, 256 with 16 + 16 (12288) 29.6 / 31.0, 4096, 256 47.5 / 45.5;
+// 2048, 640 (12800) 74.4 / 69.3; 1024, 640 (25600) 62.8 / 50.2; 2048, 1024 with 16 + 16 (98304) 136 / 105.  Three: 510, 398 (4776) 57.4 /
+// 61.1; 594, 304 (7296) 33.4 / 32.7; 558, 436 (10464) 56.9 / 53.8; 597, 488 (20862) 58.8 / 44.4; 4096, 640 (102400) 164 / 101.  Four: 872, 344
+// 66.8 / 57.7.  Inputs without columns go the other way: the factors are drawn with the slabs of X, of which there are none.
+bool f32_side_rides_along(int T, int m, int n, int r, int R, int K, int S, int C) {
+  constexpr int64_t kLimit[kFusedBlocks + 1] = {12000, 12000, 10200, 5500};
+  const int64_t blocks = (int64_t)K * ((r + 15) / 16) + (R + 15) / 16, cus = compute_units();
+  if (n == 0 || blocks > kFusedBlocks || r + R > kFusedColumns || S > kFusedTable || C > kFusedTable) return false;
+  ProbeF32Args a{};
+  a.r = r; a.R = R; a.batch.K = K; a.batch.S = S; a.batch.C = C;
+  int64_t n_tiles = tiles(m, 64, T, 64), most = 2 * cus;
+  if (n_tiles < cus) {
+    n_tiles = tiles(m, 32, T, 32);
+    most = cus * (160 * 1024 / (int64_t)(sizeof(float) * FusedLds<TileF32<32, 32, 2, 2, 128>, 32, 32>(a).end));
+  }
+  return n_tiles <= most && (n_tiles < cus ? cus : n_tiles) * n * (K * r + 2 * R) <= kLimit[blocks] * cus;
 }
 
 template <int TM, int TN, int KC, bool kVec, bool kFused>
@@ -578,7 +588,7 @@ hipError_t launch_probe_f32(const ProbeF32Args& a, hipStream_t st) {
   if (a.T == 0 || a.m == 0) return hipSuccess;
   // 64x64 tiles when they give every compute unit one, 32x32 (a longer K slab, four times the workgroups) otherwise
   const bool large = tiles(a.m, 64, a.T, 64) >= compute_units();
-  const bool fused = fused_f32(a, large);
+  const bool fused = a.has_side && f32_side_rides_along(a.T, a.m, a.n, a.r, a.R, a.batch.K, a.batch.S, a.batch.C);
   const bool vec = whole_quads(a.X, a.ldx, a.W, a.ldw, a.n);
   if (a.has_side && !fused) {
     const hipError_t e = launch_probe_prep_f32(a.batch, a.eps, a.tabs, a.tensor_id, a.m, a.n, a.r, a.Uf, a.Vf, st);

@@ -197,6 +197,7 @@ struct ProbeF32Args {
   float* Tside;                      // [T][r+R]
 };
 hipError_t launch_probe_f32(const ProbeF32Args& a, hipStream_t st);
+bool f32_side_rides_along(int T, int m, int n, int r, int R, int K, int S, int C);   // whether a call with candidates is one launch
 int head_vocab_tiles_f32(int vocab);
 struct HeadScoreF32Args {
   const float* H; int64_t ldh;

@@ -299,3 +299,19 @@ def test_head_grid_has_room_for_the_narrow_tiles_a_call_takes():
                     assert (_narrow_counts(n_tm, grid, d) ^ _narrow_counts(n_tm, 256, d)) >> k & 1 == 0
                 if grid > wide:
                     assert all(_narrow_counts(n_tm, grid, d) >> j & 1 for j in range(1, k + 1))
+
+
+def test_fp32_side_columns_ride_along_only_where_they_stay_under_the_products():
+    """Drawn and bank columns x input width per compute unit, at the edges of the rule (256 compute units)."""
+    f = zb.lib()["_ZN2zo20f32_side_rides_alongEiiiiiiii"]   # f(T, m, n, r, R, directions, sequences, candidates)
+    f.restype = C.c_bool
+    assert f(768, 256, 256, 4, 0, 1, 24, 3)             # the small configuration
+    assert f(500, 300, 3000, 4, 0, 1, 10, 2) and not f(500, 300, 3001, 4, 0, 1, 10, 2)      # one block: 12000
+    assert f(500, 300, 637, 8, 0, 2, 10, 4) and not f(500, 300, 638, 8, 0, 2, 10, 4)        # two: 10200
+    assert f(500, 300, 229, 8, 0, 3, 10, 6) and not f(500, 300, 230, 8, 0, 3, 10, 6)        # three: 5500
+    assert not f(100, 100, 16, 1, 0, 4, 10, 8)          # four blocks
+    assert f(500, 300, 510, 4, 8, 1, 10, 2) and not f(500, 300, 511, 4, 8, 1, 10, 2)        # a bank column counts twice
+    assert f(8192, 256, 64, 4, 0, 1, 10, 2) and not f(8193, 256, 64, 4, 0, 1, 10, 2)        # two tiles of 64 x 64 per unit
+    assert f(2048, 384, 64, 4, 0, 1, 10, 2) and not f(2049, 384, 64, 4, 0, 1, 10, 2)        # three of 32 x 32 by their LDS
+    assert not f(4096, 640, 640, 16, 16, 2, 16, 4) and not f(8192, 2048, 2048, 4, 0, 1, 16, 2)
+    assert not f(100, 100, 0, 4, 0, 1, 10, 2) and not f(100, 100, 16, 4, 0, 1, 1025, 2) and not f(100, 100, 16, 4, 0, 1, 10, 1025)

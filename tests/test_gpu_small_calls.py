@@ -223,6 +223,46 @@ def test_fp32_linear_of_inputs_without_columns(m, act):
     assert_close(to_np(Y), np.broadcast_to(to_np(want), (T, m_out)), 1e-6, "Y")
 
 
+# the larger tiles (which call takes which way is asserted, for 256 compute units): widths with and without whole groups of four,
+# one to three blocks of 16 columns, with a bank, of a bank alone
+@pytest.mark.parametrize("T,n,m,dirs,r,R", [(8100, 256, 256, 1, 4, 0), (6000, 130, 200, 2, 3, 0), (17000, 64, 64, 1, 16, 9),
+                                            (5400, 100, 333, 3, 5, 0), (8100, 64, 256, 1, 4, 17), (16000, 63, 96, 0, 1, 32)])
+def test_fp32_side_columns_of_larger_tiles_have_the_same_bits_on_either_way(T, n, m, dirs, r, R):
+    rides = zb.lib()["_ZN2zo20f32_side_rides_alongEiiiiiiii"]   # zo::f32_side_rides_along(T, m, n, r, R, K, S, C)
+    rides.restype = ctypes.c_bool
+    lens = [1, 33, 0, 70, 16, 2] + [250] * ((T - 122) // 250) + [(T - 122) % 250]
+    w = _layer(n * m, lens, [i % (2 * dirs + 2) - 1 for i in range(len(lens))], m, n, r, R, 0, True)
+    w.dtype, w.eps, w.dir_seed = "f32", 1e-2, w.dir_seed[:dirs]
+    w.cand_dir = np.append(np.repeat(np.arange(dirs, dtype=np.int32), 2), np.int32(-1))
+    w.cand_sign = np.append(np.tile(np.array([1, -1], np.float32), dirs), np.float32(0))
+    assert w.T == T and rides(T, m, n, r, R, dirs, len(lens), 2 * dirs + 1)
+    a = DeviceWorkload(w, DEV).probe_linear(0)
+    some = np.r_[0:130, T // 2:T // 2 + 70, T - 70:T]
+    assert_close(to_np(a)[some], oracle_layer(w, 0, w.layers[0].X, rows=some), 1e-5, "Y")
+    empty = 1100
+    w.cu_seqlens = np.concatenate([np.zeros(empty, np.int32), w.cu_seqlens])
+    w.seq_cand = np.concatenate([np.arange(empty, dtype=np.int32) % (2 * dirs + 2) - 1, w.seq_cand]).astype(np.int32)
+    assert not rides(T, m, n, r, R, dirs, len(lens) + empty, 2 * dirs + 1)
+    b = DeviceWorkload(w, DEV).probe_linear(0)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dirs,r,R", [(9, 3, 5), (16, 1, 0), (7, 17, 0)])
+def test_fp32_rows_of_many_directions_in_one_block(dirs, r, R):
+    """A side launch takes 16 rows at a time, and up to four directions among them in parallel: sequences of one and two rows
+    over more directions than that, foreground and centre ones and an empty one among them."""
+    lens = [1, 2, 1, 1, 0, 1, 2] * 30
+    rng = np.random.default_rng(dirs)
+    w = _layer(dirs, lens, rng.integers(-1, 2 * dirs + 1, len(lens)).tolist(), 40, 70, r, R, 0, False)
+    w.dtype, w.eps, w.dir_seed = "f32", 1e-2, np.arange(dirs, dtype=np.uint64) + np.uint64(11)
+    w.cand_dir = np.append(np.repeat(np.arange(dirs, dtype=np.int32), 2), np.int32(-1))
+    w.cand_sign = np.append(np.tile(np.array([1, -1], np.float32), dirs), np.float32(0))
+    assert max(len(set(np.repeat(w.seq_cand // 2, lens)[i:i + 16])) for i in range(0, w.T, 16)) > 4
+    y = DeviceWorkload(w, DEV).probe_linear(0)
+    assert_close(to_np(y), oracle_layer(w, 0, w.layers[0].X), 1e-5, "Y")
+
+
 @pytest.mark.parametrize("n", [64, 256, 1000, 2048])
 @pytest.mark.parametrize("K,r", [(1, 4), (4, 16)])
 def test_fp32_side_term_alone_against_64_bits(n, K, r):
