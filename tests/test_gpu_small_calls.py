@@ -509,3 +509,28 @@ def test_side_images_are_cleared_where_they_are_used(n, r, R, lens, K):
     assert_close(to_np(got), oracle_layer(w, 0, w.layers[0].X, out_dtype="f32"), 2e-2, "Y")
     if S == 400:
         assert int((g.ws == 255).sum()) > 160 * 256 * 64 * 2
+
+
+@pytest.mark.parametrize("C,K", [(1, 1), (64, 64), (65, 40), (141, 70), (300, 130), (40, 200)])
+@pytest.mark.parametrize("reduction", [0, 1])
+def test_estimate_of_tables_of_any_length(C, K, reduction):
+    """The candidate table is read 64 entries at a time by a workgroup per 64 directions: tables on both sides of that, in any
+    order, with directions that lack a sign or have several candidates of one, centres and candidates without a token."""
+    rng = np.random.default_rng(1000 * C + K)
+    cand_dir = rng.permutation(np.arange(C) // 2 % K).astype(np.int32)
+    cand_sign = rng.choice(np.array([1, -1, 0], np.float32), C, p=[0.45, 0.45, 0.1])
+    cand_dir[cand_sign == 0] = -1
+    cu = np.arange(C + 1, dtype=np.int32)
+    b = DeviceBatch(cu, np.arange(C, dtype=np.int32), cand_dir, cand_sign, np.arange(K, dtype=np.uint64), DEV)
+    cnt = rng.integers(0, 5, C).astype(np.int32)
+    total = rng.uniform(0.5, 9.0, C).astype(np.float32)
+    total[cnt == 0] = 0
+    loss, grad = torch.full((C,), -7.0, device=DEV), torch.full((K,), -7.0, device=DEV)
+    zb.zo_estimate(b.struct, torch.from_numpy(total).to(DEV), torch.from_numpy(cnt).to(DEV), 0.25, reduction, loss, grad)
+    torch.cuda.synchronize()
+    want_loss, want_grad = zo.estimate(zo.Batch(cu, np.arange(C, dtype=np.int32), cand_dir, cand_sign, np.arange(K, dtype=np.uint64)),
+                                       total, cnt, 0.25, reduction)
+    # a loss is one rounding (2^-24) from the quotient, a difference of two below 9 within three of 2^-24 * 9, doubled by 1 / (2 eps)
+    assert np.all(np.abs(to_np(loss) - want_loss) <= 2.0 ** -24 * np.abs(want_loss))
+    assert np.all(np.abs(to_np(grad) - want_grad) <= 2 * 3 * 9 * 2.0 ** -24)
+    assert np.array_equal(to_np(grad) == 0, want_grad == 0)
