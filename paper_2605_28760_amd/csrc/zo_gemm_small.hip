@@ -80,8 +80,9 @@ __global__ __launch_bounds__(C::kWaves * 64, 1) void k_probe_gemm_small(ProbeGem
   const int n_side_st = (n_side + C::kSideTiles - 1) / C::kSideTiles;
   const int n_st = n_side_st + (p.n + C::KC - 1) / C::KC;
 
-  // Load j of a wave fills a 1 KiB block of the A part, then of the B part, of a stage; lane i lands at byte 16 i of it.  Rows past the end of a matrix repeat its last row (never stored), columns past
-  // the end of a row in its last stage are whatever follows (never multiplied; the windows bound every access).
+  // Load j of a wave fills a 1 KiB block of the A part, then of the B part, of a stage; lane i lands at byte 16 i of it.
+  // Rows past the end of a matrix repeat its last row (never stored), columns past the end of a row in its last stage are
+  // whatever follows (never multiplied; the windows bound every access).
   constexpr int kRowsPerLoad = 64 / C::CPR;
   const int lrow = lane / C::CPR, lchunk = lane % C::CPR;
   auto block_of = [&](int j) {
@@ -402,10 +403,11 @@ int64_t tile_cost(int T, int m, int tile) {   // tile -1: the 256x256 kernel
 
 }  // namespace
 
-// The tile of this file that finishes the call soonest by the costs above, or -1 when the 256x256 kernel does.
+// The tile of up to 128 weight rows that finishes the call soonest by the costs above, or -1 when the 256x256 kernel does.
 // (Which one is taken does not enter the result.)  GEMM alone, before -> after, us: 4096 x 4096 at 96 tokens
 // 45 -> 14, at 384 45 -> 24, at 768 45 -> 34; 5120 x 20480 at 32 tokens 207 -> 56, at 512 259 -> 193;
-// 1024 x 3072 at 1475 tokens 36 -> 19; from about 1500 tokens at 4096 rows up the large kernel is the faster one.
+// 1024 x 3072 at 1475 tokens 36 -> 19; from about 1500 tokens at 4096 rows up the large kernel is faster than any of these
+// (not than the tiles of 160 rows, below).
 int small_gemm_tile(int T, int m) {
   int best = -1;
   for (int i = 0; i < kTiles; ++i)
