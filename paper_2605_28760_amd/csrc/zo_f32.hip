@@ -137,19 +137,21 @@ struct FusedLds {
 };
 
 // Products of 16 side columns and 16 rows of X over the input width: two chains of two instructions (eight products) per 16
-// columns, added, and these sums in double precision.  One chain over the width, the instruction's own accumulation, was three times as
-// far from 64-bit sums as a wave's 64 partial sums had been at 256 columns, and eight times at 16384: relative error of the
-// term alone, rank 4, at 64 / 256 / 2048 / 16384 columns 0.9, 1.3, 3.0e-7 (64 partial sums, from 256 on); 2.9, 8.1, 23e-7 (one chain);
-// 0.8e-7 throughout (this).  It costs a fused call 1 to 4 %, up to 0.4 us of 28.
-template <int kTogether>   // blocks of 16 columns whose instructions may overlap: one takes 16 registers
+// columns, the sums of 32 columns added, and these in double precision.  One chain over the width, the instruction's own accumulation,
+// was further from 64-bit sums than a wave's 64 partial sums had been: relative error of the term alone, rank 4, at 64 / 256 / 2048 /
+// 16384 columns 0.8, 0.9, 1.3, 3.0e-7 (64 partial sums); 1.5, 2.9, 8.0, 23e-7 (one chain); 0.8e-7 throughout (this).  It costs a
+// fused call up to 1.5 %, 0.4 us of 28.  (Every 16 columns in double: no closer, and twice that.  The last columns are
+// taken by blocks, as 64 at a time 5285 rows of 81 columns took 0.6 us more, linear and scoring 31.6 instead of 31.0.)
+template <int kTogether>   // blocks of 16 columns whose instructions may overlap, two or four: one takes 16 registers
 struct SideSum {
   double sum[4] = {0.0, 0.0, 0.0, 0.0};
 
-  // a, x: a lane's four values of the 16-column block b (zeros past the end)
+  // a, x: a lane's four values of the 16-column block b (zeros past the end); left: columns up to the end
   template <class A, class X>
-  __device__ __forceinline__ void add(A a, X x) {
+  __device__ __forceinline__ void add(int left, A a, X x) {
 #pragma unroll
     for (int b0 = 0; b0 < 4; b0 += kTogether) {
+      if (b0 > 0 && b0 * 16 >= left) break;
       f32x4 block[kTogether];
 #pragma unroll
       for (int j = 0; j < kTogether; ++j) {
@@ -164,9 +166,9 @@ struct SideSum {
 #pragma unroll
       for (int j = 0; j < kTogether; ++j) asm volatile("" : "+v"(block[j]));
 #pragma unroll
-      for (int j = 0; j < kTogether; ++j)
+      for (int j = 0; j < kTogether; j += 2)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] += (double)block[j][e];
+        for (int e = 0; e < 4; ++e) sum[e] += (double)(block[j][e] + block[j + 1][e]);
     }
   }
   __device__ __forceinline__ f32x4 total() const { return f32x4{(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]}; }
@@ -278,7 +280,7 @@ struct SideF32 {
 #pragma unroll
         for (int k64 = 0; k64 < KC; k64 += 64) {
           if (k0 + k64 >= n) break;
-          sum[i].add([&](int b) { return *reinterpret_cast<const f32x4*>(fa + k64 + b * 16); },
+          sum[i].add(n - k0 - k64, [&](int b) { return *reinterpret_cast<const f32x4*>(fa + k64 + b * 16); },
                      [&](int b) { return *reinterpret_cast<const f32x4*>(fb + k64 + b * 16); });
         }
       }
@@ -376,7 +378,7 @@ __global__ __launch_bounds__(64, 2) void k_side_f32(ProbeF32Args p) {
           for (int i = 0; i < 4; ++i) z[i] = also && at + i < p.n ? v[i] : 0.f;
           return z;
         };
-        sum.add([&](int blk) { return in(k0 + (u + blk) * 16 + g * 4, real, a[u + blk]); },
+        sum.add(p.n - k0 - u * 16, [&](int blk) { return in(k0 + (u + blk) * 16 + g * 4, real, a[u + blk]); },
                 [&](int blk) { return in(k0 + (u + blk) * 16 + g * 4, true, b[u + blk]); });
       }
     }
